@@ -37,10 +37,10 @@ constexpr uint8_t NO_SLOT = 0xFF;
 constexpr int RHO_BITS = 12;
 constexpr uint32_t RHO_TABLE = 1u << RHO_BITS;
 constexpr uint32_t RHO_MULTI = 0x10000u;       // entry.y >= this: >1 threshold in bucket
-// Range sweep: half as many buckets, each holding up to two boundaries (a
-// group's two boundaries usually share a bucket); same bytes as RHO_TABLE.
-constexpr int RANGE_BITS = 11;
-constexpr uint32_t RANGE_TABLE = 1u << RANGE_BITS;
+// Range sweep: one byte per bucket (codes up to 2 K, K <= 127); same bytes as
+// RHO_TABLE.
+constexpr uint32_t CODE_TABLE = 1u << 15;
+static_assert(CODE_TABLE == RHO_TABLE * sizeof(uint2), "the sweeps' tables share one buffer");
 
 constexpr int LMIN_MAX = 16;
 
@@ -104,7 +104,6 @@ struct SeriesWork {
     uint32_t esorted[RANK_MAX];   // ascending thresholds / boundaries
     uint32_t dmap[RQA_MAX_K];     // caller index -> distinct threshold index
     uint32_t Kp;                  // thresholds / boundaries in esorted
-    uint32_t zbase;               // rank offset: 1 when the first range starts at key 0
     uint32_t shift, emin, emax;   // rank-table geometry
     uint32_t multi;               // some bucket of the rank table holds several thresholds
     uint64_t hrho[RANK_MAX + 2];  // cells with rank rho

@@ -1105,19 +1105,16 @@ hipError_t launch_select_scan(hipStream_t st, const DevBufs& b, int pass)
 
 // ------------------------------------------------------------------ sweep
 
-// Rank of a key among the sorted thresholds e_0 < ... < e_{Kp-1}, plus a
-// per-series base z: rho = z + #{e < key}.  Given thresholds: z = 0 and the
-// pair recurs at threshold j iff rho <= j.  Range sweep: the thresholds are
-// the group boundaries (first value - 1, last value) and z = 1 when the first
-// group starts at key 0, so rho is odd exactly for keys inside a group,
-// group (rho - 1) / 2.  The bucket of the key (clamped to [e_0, e_{Kp-1}])
+// Rank of a key among the sorted thresholds e_0 < ... < e_{Kp-1}: rho =
+// #{e < key}, and the pair recurs at threshold j iff rho <= j.  The bucket of
+// the key (clamped to [e_0, e_{Kp-1}])
 // gives the rank below the bucket and the bucket's first threshold; buckets
 // holding several thresholds compare each of them.
 struct RhoCtx {
     const uint2* table;     // LDS [RHO_TABLE]: x = first threshold in bucket (or ~0), y = rank base
     const uint32_t* es;     // LDS [Kp] thresholds
     float emin, emax;       // smallest and largest threshold
-    uint32_t shift, Kp, z;
+    uint32_t shift, Kp;
 };
 
 // MULTI: some bucket holds more than one threshold (rare; flagged per series).
@@ -1132,7 +1129,7 @@ __device__ __forceinline__ uint32_t rho_of(uint32_t u, const RhoCtx& c)
         if (e.y >= RHO_MULTI) {
             const uint32_t base = e.y & 0xFFFFu, cnt = e.y >> 16;
             r = base;
-            for (uint32_t i = 0; i < cnt; ++i) r += (u > c.es[base - c.z + i]) ? 1u : 0u;
+            for (uint32_t i = 0; i < cnt; ++i) r += (u > c.es[base + i]) ? 1u : 0u;
         }
     }
     return r;
@@ -1160,40 +1157,30 @@ __device__ __forceinline__ uint2 rho_table_entry(uint2 e)
     return e;
 }
 
-// Range sweep: buckets of 2^shift bit patterns hold up to two boundaries
-// (x, y) and the rank base z (z + boundaries below the bucket); w > 0 marks a
-// bucket with w > 2 boundaries, compared one by one (rare).
-struct RangeCtx {
-    const uint4* table;     // LDS [RANGE_TABLE], at LDS byte 0
-    const uint32_t* es;     // LDS [Kp] boundaries
+// Range sweep: one byte per bucket of 2^sh bit patterns (CODE_TABLE buckets).
+// The code of a bucket without any group value is twice the number of groups
+// below it; a bucket that holds values of a group has the odd code 2 g + 1 of
+// its first such group.  Codes are monotone in the key, and an odd code says
+// that the exact place (inside a group or beside it) is still open: such
+// values are rare and are placed exactly out of the main line.  Keys are
+// clamped to [emin, emax], which lie in the buckets just outside the groups.
+struct CodeCtx {
     float emin, emax;
-    uint32_t sh4, Kp, z;    // sh4 = bucket shift - 4 (the shift is at least 4)
+    uint32_t sh;
 };
 
-// Written with the operations gfx950 issues at the double rate (32-bit add,
-// sub, and, or, right shifts): the bucket's byte offset is a right shift and
-// a mask instead of a bit-field extract and a scaled add, and the two
-// compares are sign bits of differences instead of compare-and-select pairs.
-// Keys are at most +inf (0x7F800000) and boundaries at most 0x7FFFFFFF (the
-// absent-boundary value), so b - u cannot wrap and its sign bit is u > b.
-template <bool MULTI>
-__device__ __forceinline__ uint32_t rank_of(uint32_t u, const RangeCtx& c)
+// One clamp, a right shift, a mask and one byte read per key.  A table of
+// exact ranks needs the bucket's boundaries beside the rank: two compares and
+// an add per key, and 16 bytes of LDS read per lane instead of one.  Two
+// N = 1e5 series (1e10 pairs, K = 20, squared Euclidean, m = 3, tau = 5):
+// sweep 4.50 ms with such a table, 3.09 ms with this one.
+__device__ __forceinline__ uint32_t code_of(uint32_t u, const CodeCtx& c)
 {
     const uint32_t cl = __float_as_uint(__builtin_amdgcn_fmed3f(__uint_as_float(u), c.emin, c.emax));
-    const uint32_t off = (cl >> c.sh4) & ((RANGE_TABLE - 1u) << 4);
     // the table sits at LDS byte 0 (k_range_sweep checks it), so its byte
     // offset is the LDS address: no base to add per key
-    const __attribute__((address_space(3))) uint32_t* e = (const __attribute__((address_space(3))) uint32_t*)(size_t)off;
-    const uint32_t ex = e[0], ey = e[1], ez = e[2];
-    uint32_t r = ez + ((ex - u) >> 31) + ((ey - u) >> 31);
-    if constexpr (MULTI) {
-        const uint32_t ew = e[3];
-        if (ew) {
-            r = ez;
-            for (uint32_t i = 0; i < ew; ++i) r += (u > c.es[ez - c.z + i]) ? 1u : 0u;
-        }
-    }
-    return r;
+    const uint32_t off = (cl >> c.sh) & (CODE_TABLE - 1u);
+    return *(const __attribute__((address_space(3))) uint8_t*)(size_t)off;
 }
 
 // Line rank lambda_t: the smallest threshold index at which cell t lies on a
@@ -1230,7 +1217,6 @@ struct SweepBody {
         rc.emax = __uint_as_float(uniform(w.emax));
         rc.shift = uniform(w.shift);
         rc.Kp = uniform(w.Kp);
-        rc.z = 0;
         multi = uniform(w.multi) != 0;
     }
     __device__ void flush(uint32_t s)
@@ -1357,23 +1343,23 @@ struct SweepBody {
     }
 };
 
-// Range sweep.  The ranks are taken against the group boundaries (odd rank:
-// inside group rank/2, see RangeCtx), and only the line ranks are
+// Range sweep.  Keys are looked up in the code table (see CodeCtx), the line
+// code of a cell is the line rule over codes, and only the line codes are
 // histogrammed: C comes from the counting passes plus the fine counters, D
-// from the line ranks below the target's group plus the fine counters of
-// line values inside it.  A key or line value inside a group adds one to
-// the group's fine counter at its offset from the group start (global
-// memory, rare).  lmin = 1 needs no line values (D = C).
-// Range-sweep LDS: rank table (at byte 0), per-column line-rank histograms
-// of rows + 1 rows, the boundaries, then the group starts and fine offsets.
-// A histogram row has 64 columns (one per lane) or, where 64 would cost a
-// CU its third workgroup, 32 (lanes L and L + 32 share a column): the third
-// workgroup is worth more than the shared columns cost (K = 48: sweep 7.36
-// -> 6.07 ms; K = 20, where both layouts fit three: 64 columns 0.3% faster).
+// from the line values below the target's group plus the fine counters of
+// line values inside it.  A value with an odd code is placed exactly
+// (place()): inside a group it adds one to the group's fine counter at its
+// offset from the group start (global memory), and every line value with an
+// odd code counts at its exact rank in hx, so the odd rows of the main
+// histogram are not read.  lmin = 1 needs no line values (D = C).
+// LDS: code table (at byte 0), per-column line-code histograms of rows rows,
+// the exact-rank counts hx, then the group starts and fine offsets.  A
+// histogram row has 64 columns (one per lane) or, where 64 would cost a CU its
+// third workgroup, 32 (lanes L and L + 32 share a column): the third workgroup
+// is worth more than the shared columns cost.
 __host__ __device__ __forceinline__ size_t range_lds_layout(uint32_t rows, uint32_t cols)
 {
-    return RANGE_TABLE * sizeof(uint4) + (size_t)(rows + 1) * cols * 4 + (size_t)(rows - 1) * 4 +
-           2 * (size_t)((rows + 1) / 2 + 1) * 4;
+    return CODE_TABLE + (size_t)rows * cols * 4 + (size_t)rows * 4 + 2 * (size_t)((rows + 1) / 2 + 1) * 4;
 }
 __host__ __device__ __forceinline__ uint32_t range_cols(uint32_t rows)
 {
@@ -1382,14 +1368,13 @@ __host__ __device__ __forceinline__ uint32_t range_cols(uint32_t rows)
 
 template <int NORM, int MC, int TC, int LMC>
 struct RangeBody {
-    uint4* stab;          // LDS [RANGE_TABLE], at byte 0
-    uint32_t* blam;       // LDS [rows+1][cols]: the last row collects cells outside the diagonal
-    uint32_t* ses;        // LDS [rows - 1] boundaries (rows - 1 = 2K >= Kp)
+    uint32_t* blam;       // LDS [rows][cols]; codes are 0 .. 2 ngroups <= rows - 1
+    uint32_t* hx;         // LDS [rows] line values with an odd code, by exact rank
     uint32_t* sglo;       // LDS [gcap] group starts (gcap = K + 2 > ngroups)
     uint32_t* sgoff;      // LDS [gcap] group fine offsets
     uint32_t cols, csh, gcap;  // histogram columns, log2 of a row's bytes
     uint32_t lcol;        // this lane's column byte offset
-    const uint4* rtab;    // global [S][RANGE_TABLE]
+    const uint4* rtab;    // global [S][CODE_TABLE / 16]
     SeriesWork* works;
     uint64_t* fineK;      // global [S][fine_stride]
     uint64_t* fineL;
@@ -1397,61 +1382,89 @@ struct RangeBody {
     unsigned long long* dk;
     unsigned long long* dl;
     uint32_t rows;
-    RangeCtx rc;
+    CodeCtx rc;
     uint32_t lmin;
-    uint32_t spare;       // rank above every boundary (and of cells outside the diagonal)
+    uint32_t spare;       // code above every group (and of cells outside the diagonal)
     uint32_t ngroups, nfine;
-    bool multi;
     bool active = true;
 
     __device__ void begin(uint32_t s)
     {
         const SeriesWork& w = works[s];
         active = uniform(w.range_ok) != 0;
-        for (uint32_t i = threadIdx.x; i < RANGE_TABLE; i += blockDim.x) stab[i] = rtab[(size_t)s * RANGE_TABLE + i];
-        for (uint32_t i = threadIdx.x; i < rows - 1; i += blockDim.x) ses[i] = w.esorted[i];
-        for (uint32_t i = threadIdx.x; i < (rows + 1) * cols; i += blockDim.x) blam[i] = 0u;
+        const uint4* tab = rtab + (size_t)s * (CODE_TABLE / 16);
+        uint4* stab = (uint4*)((unsigned char*)blam - CODE_TABLE);
+        for (uint32_t i = threadIdx.x; i < CODE_TABLE / 16; i += blockDim.x) stab[i] = tab[i];
+        for (uint32_t i = threadIdx.x; i < rows * cols; i += blockDim.x) blam[i] = 0u;
+        for (uint32_t i = threadIdx.x; i < rows; i += blockDim.x) hx[i] = 0u;
         for (uint32_t i = threadIdx.x; i < gcap; i += blockDim.x) {
             sglo[i] = w.g_lo[i];
             sgoff[i] = w.g_off[i];
         }
-        rc.table = stab;
-        rc.es = ses;
         rc.emin = __uint_as_float(uniform(w.emin));
         rc.emax = __uint_as_float(uniform(w.emax));
-        rc.sh4 = uniform(w.shift) - 4u;
-        rc.Kp = uniform(w.Kp);
-        rc.z = uniform(w.zbase);
-        spare = rc.Kp + rc.z;
+        rc.sh = uniform(w.shift);
         ngroups = uniform(w.ngroups);
+        spare = 2u * ngroups;
         nfine = active ? uniform(w.nsub) << uniform(w.range_bits) : 0u;
-        multi = uniform(w.multi) != 0;
         dk = (unsigned long long*)(fineK + (size_t)s * fine_stride);
         dl = (unsigned long long*)(fineL + (size_t)s * fine_stride);
     }
+    // one wave per row (a thread per row would read every column of its row
+    // from the same bank as its neighbours)
     __device__ void flush(uint32_t s)
     {
         if (!active || LMC == 1) return;
         SeriesWork& w = works[s];
-        for (uint32_t j = threadIdx.x; j < spare; j += blockDim.x) {
-            const uint32_t* row = blam + j * cols;
-            uint64_t sum = 0;
-            for (uint32_t l = 0; l < cols; ++l) sum += row[l];
-            if (sum) atomicAdd((unsigned long long*)&w.hlam[j], (unsigned long long)sum);
+        const uint32_t lane = threadIdx.x & 63u;
+        for (uint32_t j = threadIdx.x >> 6; j < spare; j += blockDim.x >> 6) {
+            uint32_t v = (j & 1u) == 0u && lane < cols ? blam[j * cols + lane] : 0u;
+            uint64_t sum = v;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+            sum += hx[j];
+            if (lane == 0 && sum) atomicAdd((unsigned long long*)&w.hlam[j], (unsigned long long)sum);
         }
     }
-    // row lam, this lane's column: one shift-and-add for the byte offset
-    __device__ __forceinline__ void emit(uint32_t lam, int) const
+    // row of a line code, this lane's column: one shift-and-add for the byte offset
+    __device__ __forceinline__ void emit(uint32_t lam) const
     {
         atomicAdd((uint32_t*)((unsigned char*)blam + ((lam << csh) + lcol)), 1u);
     }
-    // count value x of rank r if r is odd (inside group r/2); group and
-    // counter index are checked, so no rank can address outside the counters
-    __device__ __forceinline__ void fine(unsigned long long* dst, uint32_t r, uint32_t x) const
+    // exact place of value x with the odd code c: its rank (2 g + 1 inside
+    // group g, 2 g below group g, 2 ngroups above all) and, inside a group,
+    // its fine counter idx
+    __device__ __forceinline__ uint32_t place(uint32_t x, uint32_t c, uint32_t& idx) const
     {
-        const uint32_t g = min(r >> 1, ngroups);
-        const uint32_t idx = sgoff[g] + (x - sglo[g]);
-        fine_add(dst, idx, (r & 1u) != 0 && g < ngroups && idx < nfine);
+        uint32_t g = min(c >> 1, ngroups);
+        uint32_t lo = sglo[g], off = sgoff[g];
+        for (; g < ngroups; ++g) {
+            const uint32_t nlo = sglo[g + 1], noff = sgoff[g + 1];
+            if (x < lo || x - lo < noff - off) break;
+            lo = nlo;
+            off = noff;
+        }
+        idx = off + (x - lo);
+        return g < ngroups && x >= lo ? 2u * g + 1u : 2u * g;
+    }
+    // count key x with code c in the fine counters if it lies inside a group
+    __device__ __forceinline__ void fine_key(uint32_t c, uint32_t x) const
+    {
+        uint32_t idx = 0, r = 0;
+        if (c & 1u) r = place(x, c, idx);
+        // the index is checked, so no code can address outside the counters
+        fine_add(dk, idx, (r & 1u) != 0 && idx < nfine);
+    }
+    // count line value x with line code c at its exact rank, and in the fine
+    // counters if it lies inside a group
+    __device__ __forceinline__ void fine_line(uint32_t c, uint32_t x) const
+    {
+        uint32_t idx = 0, r = 0;
+        if (c & 1u) {
+            r = place(x, c, idx);
+            atomicAdd(&hx[r], 1u);
+        }
+        fine_add(dl, idx, (r & 1u) != 0 && idx < nfine);
     }
     __device__ __forceinline__ uint32_t key_at(const SeriesScalars& sd, const TileGeo& g, int x) const
     {
@@ -1459,53 +1472,46 @@ struct RangeBody {
         const int i = ok ? x : 0;
         const int j = ok ? x + g.d : g.d0;
         const uint32_t k = __float_as_uint(pair_key<NORM, MC, TC>(sd.y, i, j, sd.m, sd.tau));
-        return ok ? k : 0xFFFFFFFFu;  // outside the diagonal: above every boundary
+        return ok ? k : 0xFFFFFFFFu;  // outside the diagonal: above every group
     }
-    template <bool MULTI>
-    __device__ __forceinline__ uint32_t rank_at(uint32_t key) const
+    __device__ __forceinline__ uint32_t code_at(uint32_t key) const
     {
-        return key == 0xFFFFFFFFu ? spare : rank_of<MULTI>(key, rc);
+        return key == 0xFFFFFFFFu ? spare : code_of(key, rc);
     }
     __device__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
-    {
-        if (multi) tile_impl<true>(sd, tile_id, lane);
-        else tile_impl<false>(sd, tile_id, lane);
-    }
-    template <bool MULTI>
-    __device__ __forceinline__ void tile_impl(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
         const TileGeo g = tile_geo(sd, tile_id, lane);
         constexpr bool kFast = (LMC == 1 || LMC == 2) && MC > 0 && (MC == 1 || TC > 0);
         constexpr int TW = MC == 1 ? 1 : TC;
         int tx = g.t0;  // cells before tx are counted by the walker
-        // lmin = 2: keys and ranks of the cells before and at the next one counted
+        // lmin = 2: keys and codes of the cells before and at the next one counted
         uint32_t km1 = 0, k0 = 0, rm1 = 0, r0 = 0;
         if constexpr (LMC == 2) {
             km1 = key_at(sd, g, g.t0 - 1);
             k0 = key_at(sd, g, g.t0);
-            rm1 = rank_at<MULTI>(km1);
-            r0 = rank_at<MULTI>(k0);
+            rm1 = code_at(km1);
+            r0 = code_at(k0);
         }
         if constexpr (kFast) {
             constexpr int HU = walk_block<NORM, MC, TW>();
             const int tw = walk_end<HU>(g);
             if (tw > g.t0) {
                 // every lane's diagonal covers [t0 - 1, tw + WALK_SLACK]
-                RangeCtx c = rc;
-                c.sh4 = in_vgpr(rc.sh4);
+                CodeCtx c = rc;
+                c.sh = in_vgpr(rc.sh);
                 if constexpr (LMC == 1) {
                     walk<NORM, MC, TW>(sd.y, g.d, g.t0, tw - g.t0, [&](const uint32_t(&k)[HU], int valid) {
                         uint32_t r[HU];
                         uint32_t acc = 0;
 #pragma unroll
                         for (int u = 0; u < HU; ++u) {
-                            r[u] = rank_of<MULTI>(k[u], c);
+                            r[u] = code_of(k[u], c);
                             if (u < valid) acc |= r[u];
                         }
-                        if (__ballot(acc & 1u)) {   // rare: a key of the block lies inside a group
+                        if (__ballot(acc & 1u)) {   // rare: an odd code in the block
 #pragma unroll
                             for (int u = 0; u < HU; ++u)
-                                if (u < valid && __ballot(r[u] & 1u)) fine(dk, r[u], k[u]);
+                                if (u < valid && __ballot(r[u] & 1u)) fine_key(r[u], k[u]);
                         }
                     });
                 } else {
@@ -1513,13 +1519,13 @@ struct RangeBody {
                     // neighbours of the cells counted in the block
                     walk<NORM, MC, TW>(sd.y, g.d, g.t0 + 1, tw - g.t0, [&](const uint32_t(&k)[HU], int valid) {
                         uint32_t r[HU];
-                        // a line value is one of the ranks of its cell and the two
-                        // neighbours, so an odd rank among those of the block and the
-                        // two before it covers every odd key rank and line rank
+                        // a line code is one of the codes of its cell and the two
+                        // neighbours, so an odd code among those of the block and the
+                        // two before it covers every odd key code and line code
                         uint32_t acc = rm1 | r0;
 #pragma unroll
                         for (int u = 0; u < HU; ++u) {
-                            r[u] = rank_of<MULTI>(k[u], c);
+                            r[u] = code_of(k[u], c);
                             acc |= r[u];
                         }
 #pragma unroll
@@ -1527,12 +1533,12 @@ struct RangeBody {
                             if (u < valid) {
                                 const uint32_t cr = u == 0 ? r0 : r[u - 1];
                                 const uint32_t left = u == 0 ? rm1 : (u == 1 ? r0 : r[u - 2]);
-                                emit(max(cr, min(left, r[u])), lane);
+                                emit(max(cr, min(left, r[u])));
                             }
                         }
                         if (__ballot(acc & 1u)) {
-                            // rare: some key or line value of the block lies inside a
-                            // group; walk the block again for the fine counters
+                            // rare: some key or line value of the block has an odd
+                            // code; walk the block again to place them exactly
 #pragma unroll
                             for (int u = 0; u < HU; ++u) {
                                 if (u < valid) {
@@ -1542,14 +1548,14 @@ struct RangeBody {
                                     if (__ballot((cr | lam) & 1u)) {
                                         const uint32_t ck = u == 0 ? k0 : k[u - 1];
                                         const uint32_t lk = u == 0 ? km1 : (u == 1 ? k0 : k[u - 2]);
-                                        fine(dk, cr, ck);
-                                        fine(dl, lam, max(ck, min(lk, k[u])));
+                                        fine_key(cr, ck);
+                                        fine_line(lam, max(ck, min(lk, k[u])));
                                     }
                                 }
                             }
                         }
                         // state for the next block (the walk covers whole blocks
-                        // only, so after it: the keys and ranks at tw - 1 and tw)
+                        // only, so after it: the keys and codes at tw - 1 and tw)
                         km1 = k[HU - 2];
                         k0 = k[HU - 1];
                         rm1 = r[HU - 2];
@@ -1562,18 +1568,18 @@ struct RangeBody {
         if constexpr (LMC == 1) {
             for (int x = tx; x < g.t1; ++x) {
                 const uint32_t k = key_at(sd, g, x);
-                const uint32_t r = rank_at<MULTI>(k);
-                if (__ballot(r & 1u)) fine(dk, r, k);
+                const uint32_t r = code_at(k);
+                if (__ballot(r & 1u)) fine_key(r, k);
             }
         } else if constexpr (LMC == 2) {
             for (int x = tx; x < g.t1; ++x) {
                 const uint32_t kp1 = key_at(sd, g, x + 1);
-                const uint32_t rp1 = rank_at<MULTI>(kp1);
+                const uint32_t rp1 = code_at(kp1);
                 const uint32_t lam = max(r0, min(rm1, rp1));
-                emit(lam, lane);
+                emit(lam);
                 if (__ballot((r0 | lam) & 1u)) {
-                    fine(dk, r0, k0);
-                    fine(dl, lam, max(k0, min(km1, kp1)));
+                    fine_key(r0, k0);
+                    fine_line(lam, max(k0, min(km1, kp1)));
                 }
                 km1 = k0;
                 k0 = kp1;
@@ -1607,11 +1613,11 @@ struct RangeBody {
 #pragma unroll
                     for (int i = 0; i < LMIN_MAX; ++i)
                         if (i >= LMIN_MAX - 1 - h) lkey = min(lkey, wk[i]);
-                    const uint32_t rk = rank_at<MULTI>(kold), lam = rank_at<MULTI>(lkey);
-                    emit(lam, lane);
+                    const uint32_t rk = code_at(kold), lam = code_at(lkey);
+                    emit(lam);
                     if (__ballot((rk | lam) & 1u)) {
-                        fine(dk, rk, kold);
-                        fine(dl, lam, lkey);
+                        fine_key(rk, kold);
+                        fine_line(lam, lkey);
                     }
                 }
             }
@@ -1669,10 +1675,9 @@ k_range_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks, 
     body.csh = body.cols == 64 ? 8u : 7u;
     body.gcap = (rows + 1) / 2 + 1;
     body.lcol = ((uint32_t)threadIdx.x & (body.cols - 1)) * 4u;
-    body.stab = (uint4*)smem;
-    body.blam = (uint32_t*)(smem + RANGE_TABLE * sizeof(uint4));
-    body.ses = body.blam + (size_t)(rows + 1) * body.cols;
-    body.sglo = body.ses + (rows - 1);
+    body.blam = (uint32_t*)(smem + CODE_TABLE);
+    body.hx = body.blam + (size_t)rows * body.cols;
+    body.sglo = body.hx + rows;
     body.sgoff = body.sglo + body.gcap;
     body.rtab = (const uint4*)rtab;
     body.works = works;
@@ -1684,9 +1689,8 @@ k_range_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks, 
     body.rows = rows;
     body.ngroups = 0;
     body.nfine = 0;
-    body.multi = false;
     body.lmin = LMC == 0 ? sds[0].lmin : (uint32_t)LMC;
-    // rank_of addresses the rank table by its offset from LDS byte 0: the
+    // code_of addresses the code table by its offset from LDS byte 0: the
     // kernel's dynamic LDS must start there (it has no static LDS); a launch
     // where it does not marks every series (the host reports a device error)
     if ((uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)smem != 0u) {
@@ -1793,14 +1797,12 @@ __device__ __forceinline__ uint32_t count_below(const uint32_t* es, uint32_t n, 
     return lo;
 }
 
-// Rank table of one series over the ascending thresholds es[0..kp) with rank
-// base z: spans the buckets (key >> shift) from es[0] to es[kp-1] with the
+// Rank table of one series over the ascending thresholds es[0..kp): spans the buckets (key >> shift) from es[0] to es[kp-1] with the
 // smallest shift that fits RHO_TABLE buckets; bucket a (mod RHO_TABLE) stores
-// z + the number of thresholds below a << shift, and the first threshold
+// the number of thresholds below a << shift, and the first threshold
 // inside the bucket (several inside: flagged, the count in the high half).
 // Called by a whole block after es is complete in LDS.
-__device__ void build_rank_table(SeriesWork& w, const uint32_t* es, uint32_t kp, uint32_t z, uint2* tab,
-                                 uint32_t* s_shift)
+__device__ void build_rank_table(SeriesWork& w, const uint32_t* es, uint32_t kp, uint2* tab, uint32_t* s_shift)
 {
     if (threadIdx.x == 0) {
         uint32_t sh = 0;
@@ -1815,7 +1817,6 @@ __device__ void build_rank_table(SeriesWork& w, const uint32_t* es, uint32_t kp,
     for (uint32_t i = threadIdx.x; i < RANK_MAX + 2; i += blockDim.x) { w.hrho[i] = 0; w.hlam[i] = 0; }
     if (threadIdx.x == 0) {
         w.Kp = kp;
-        w.zbase = z;
         w.shift = sh;
         w.emin = emin;
         w.emax = emax;
@@ -1823,12 +1824,12 @@ __device__ void build_rank_table(SeriesWork& w, const uint32_t* es, uint32_t kp,
     const uint32_t a0 = emin >> sh, a1 = emax >> sh;
     for (uint32_t idx = threadIdx.x; idx < RHO_TABLE; idx += blockDim.x) {
         const uint32_t a = a0 + ((idx - a0) & (RHO_TABLE - 1));
-        uint2 e = make_uint2(0xFFFFFFFFu, z);
+        uint2 e = make_uint2(0xFFFFFFFFu, 0u);
         if (a <= a1) {
             const uint64_t lo = (uint64_t)a << sh, hi = (uint64_t)(a + 1) << sh;
             const uint32_t below = count_below(es, kp, lo), inside = count_below(es, kp, hi) - below;
             e.x = inside ? es[below] : 0xFFFFFFFFu;
-            e.y = (inside >= 2) ? ((z + below) | (inside << 16)) : z + below;
+            e.y = (inside >= 2) ? (below | (inside << 16)) : below;
             if (inside >= 2) w.multi = 1u;
         }
         tab[idx] = e;
@@ -1849,7 +1850,7 @@ __global__ void __launch_bounds__(PREP_THREADS) k_sweep_prep(const SeriesDesc* _
     __syncthreads();
     const uint32_t kp = block_sort_unique(s_eps, nullptr, K, es, s_pos, s_flag);
     for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) w.dmap[r] = s_pos[r];
-    build_rank_table(w, es, kp, 0u, rtab + (size_t)s * RHO_TABLE, &s_shift);
+    build_rank_table(w, es, kp, rtab + (size_t)s * RHO_TABLE, &s_shift);
 }
 
 hipError_t launch_sweep_prep(hipStream_t st, const DevBufs& b)
@@ -1936,7 +1937,6 @@ struct HistBody {
         rc.emax = __uint_as_float(uniform(w.emax));
         rc.shift = uniform(w.shift);
         rc.Kp = uniform(w.Kp);
-        rc.z = 0;
         // rho_fast needs a bucket shift of at least 3; narrower tables take
         // the general lookup
         multi = uniform(w.multi) != 0 || rc.shift < 3u;
@@ -2258,47 +2258,54 @@ int hist_blocks_per_cu(int select_variant, uint32_t Kp, uint32_t block)
 }
 
 
-// Range table of one series over the ascending boundaries es[0..kp) with rank
-// base z: RANGE_TABLE buckets of 2^shift bit patterns (shift >= 4) from es[0]
-// to es[kp-1]; each holds the first two boundaries inside it (x, y;
-// 0x7FFFFFFF, above every key, when absent), z + the boundaries below it, and
-// w = the count when more than two lie inside (compared one by one).  Called
-// by a whole block.
-__device__ void build_range_table(SeriesWork& w, const uint32_t* es, uint32_t kp, uint32_t z, uint4* tab,
-                                  uint32_t* s_shift)
+// Code table of one series over its ng >= 1 groups (starts glo[], one past
+// the end gend[], ascending and disjoint, in LDS; see CodeCtx): the smallest
+// shift for which the buckets of all groups and one on either side fit
+// CODE_TABLE; bucket a (mod CODE_TABLE) at byte a.  Called by a whole block.
+__device__ void build_code_table(SeriesWork& w, const uint32_t* glo, const uint64_t* gend, uint32_t ng, uint32_t* tab,
+                                 uint32_t* s_shift)
 {
+    const uint32_t last = (uint32_t)min(gend[ng - 1] - 1ull, (uint64_t)0x7F800000u);  // keys never exceed +inf
     if (threadIdx.x == 0) {
-        uint32_t sh = 4;
-        while (sh < 31 && (es[kp - 1] >> sh) - (es[0] >> sh) >= RANGE_TABLE) ++sh;
+        uint32_t sh = 0;
+        while ((last >> sh) - (glo[0] >> sh) + 3u > CODE_TABLE) ++sh;
         *s_shift = sh;
-        w.multi = 0u;  // set before the barrier; table entries below may raise it
+        // clamp bounds in the buckets next to the groups: a key of such a
+        // bucket has an even code, also where a group shares its bucket with
+        // keys outside
+        const uint32_t a0 = glo[0] >> sh, a1 = last >> sh;
+        w.emin = a0 ? (a0 << sh) - 1u : 0u;
+        w.emax = (uint32_t)min((uint64_t)(a1 + 1u) << sh, (uint64_t)0x7F800000u);
+        w.shift = sh;
+        w.Kp = 2u * ng;
     }
     __syncthreads();
     const uint32_t sh = *s_shift;
-    const uint32_t emin = es[0], emax = es[kp - 1];
-    for (uint32_t i = threadIdx.x; i < RANK_MAX; i += blockDim.x) w.esorted[i] = (i < kp) ? es[i] : 0xFFFFFFFFu;
     for (uint32_t i = threadIdx.x; i < RANK_MAX + 2; i += blockDim.x) { w.hrho[i] = 0; w.hlam[i] = 0; }
-    if (threadIdx.x == 0) {
-        w.Kp = kp;
-        w.zbase = z;
-        w.shift = sh;
-        w.emin = emin;
-        w.emax = emax;
-    }
-    const uint32_t a0 = emin >> sh, a1 = emax >> sh;
-    for (uint32_t idx = threadIdx.x; idx < RANGE_TABLE; idx += blockDim.x) {
-        const uint32_t a = a0 + ((idx - a0) & (RANGE_TABLE - 1));
-        uint4 e = make_uint4(0x7FFFFFFFu, 0x7FFFFFFFu, z, 0u);
-        if (a <= a1) {
-            const uint64_t lo = (uint64_t)a << sh, hi = (uint64_t)(a + 1) << sh;
-            const uint32_t below = count_below(es, kp, lo), inside = count_below(es, kp, hi) - below;
-            e.x = inside >= 1 ? es[below] : 0x7FFFFFFFu;
-            e.y = inside >= 2 ? es[below + 1] : 0x7FFFFFFFu;
-            e.z = z + below;
-            e.w = inside >= 3 ? inside : 0u;
-            if (inside >= 3) w.multi = 1u;
+    const uint32_t a0 = glo[0] >> sh;
+    const uint32_t aL = a0 ? a0 - 1u : 0u;
+    for (uint32_t word = threadIdx.x; word < CODE_TABLE / 4; word += blockDim.x) {
+        uint32_t packed = 0, g = 0, prev = 0xFFFFFFFFu;
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            const uint32_t a = aL + ((4u * word + i - aL) & (CODE_TABLE - 1u));
+            const uint64_t lo = (uint64_t)a << sh, hi = (uint64_t)(a + 1u) << sh;
+            if (a != prev + 1u || i == 0) {
+                // first group that ends above the bucket's start
+                uint32_t b = 0, e = ng;
+                while (b < e) {
+                    const uint32_t mid = (b + e) >> 1;
+                    if (gend[mid] <= lo) b = mid + 1; else e = mid;
+                }
+                g = b;
+            } else {
+                while (g < ng && gend[g] <= lo) ++g;
+            }
+            prev = a;
+            const uint32_t code = 2u * g + (g < ng && (uint64_t)glo[g] < hi ? 1u : 0u);
+            packed |= code << (8u * i);
         }
-        tab[idx] = e;
+        tab[word] = packed;
     }
 }
 
@@ -2307,15 +2314,14 @@ __device__ void build_range_table(SeriesWork& w, const uint32_t* es, uint32_t kp
 // plain scan 2 (a_r = 21-bit prefix << SEL_B3, rbase = keys below the
 // prefix) or after window scan 1 (a_r = fine-bin start, rbase = keys below
 // the fine bin; a series with a target outside its window is left out).
-// Distinct ranges are sorted, adjacent ones merge into groups, and the
-// group boundaries (first value - 1, last value) form the rank table; the
-// fine counters of the ranges are cleared.
+// Distinct ranges are sorted, adjacent ones merge into groups, and the code
+// table is built over the groups; the fine counters of the ranges are cleared.
 __global__ void __launch_bounds__(PREP_THREADS) k_range_prep(const SeriesDesc* __restrict__ sds,
                                                     SeriesWork* __restrict__ works, uint2* __restrict__ rtab,
                                                     uint64_t* __restrict__ fineK, uint64_t* __restrict__ fineL,
                                                     uint32_t fine_stride, uint32_t window)
 {
-    __shared__ uint32_t es[RANK_MAX];
+    __shared__ uint64_t s_gend[RQA_MAX_K];
     __shared__ uint32_t sub[RQA_MAX_K];
     // the per-target inputs and the group arrays in LDS, worked on by one
     // thread per target or range (serially, each step would wait on a round
@@ -2323,7 +2329,7 @@ __global__ void __launch_bounds__(PREP_THREADS) k_range_prep(const SeriesDesc* _
     __shared__ uint32_t s_addr[RQA_MAX_K], s_tsub[RQA_MAX_K], s_tgroup[RQA_MAX_K];
     __shared__ uint32_t s_flag[RQA_MAX_K], s_gid[RQA_MAX_K];
     __shared__ uint32_t s_glo[RQA_MAX_K + 1], s_goff[RQA_MAX_K + 1];
-    __shared__ uint32_t s_kp, s_z, s_shift, s_miss;
+    __shared__ uint32_t s_shift, s_miss;
     const uint32_t s = blockIdx.x;
     const uint32_t K = sds[s].K;
     SeriesWork& w = works[s];
@@ -2366,24 +2372,13 @@ __global__ void __launch_bounds__(PREP_THREADS) k_range_prep(const SeriesDesc* _
         }
         __syncthreads();
         if (j < K) s_tgroup[j] = s_gid[s_tsub[j]];
-        // the rank table's boundaries, per group: its first value - 1 (unless
-        // that value is 0, which only the first group can start at) and its
-        // last value, in group order
-        const uint32_t z = s_glo[0] == 0u ? 1u : 0u;
         if (j < ng) {
-            const uint32_t glo = s_glo[j];
             const uint32_t nj = (j + 1 < ng ? (s_goff[j + 1] >> bits) : ns) - (s_goff[j] >> bits);
-            // keys never exceed +inf
-            const uint64_t last = (uint64_t)glo + ((uint64_t)nj << bits) - 1;
-            const uint32_t at = j == 0 ? 0u : 2u * j - z;
-            if (glo > 0u) es[at] = glo - 1u;
-            es[at + (glo > 0u ? 1u : 0u)] = (uint32_t)(last < 0x7F800000ull ? last : 0x7F800000ull);
+            s_gend[j] = (uint64_t)s_glo[j] + ((uint64_t)nj << bits);
         }
         if (j == 0) {
-            s_glo[ng] = 0;
-            s_goff[ng] = 0;
-            s_kp = 2u * ng - z;
-            s_z = z;
+            s_glo[ng] = 0xFFFFFFFFu;  // above every key
+            s_goff[ng] = ns << bits;
         }
     }
     __syncthreads();
@@ -2414,7 +2409,7 @@ __global__ void __launch_bounds__(PREP_THREADS) k_range_prep(const SeriesDesc* _
         fk[i] = 0;
         fl[i] = 0;
     }
-    build_range_table(w, es, s_kp, s_z, (uint4*)(rtab + (size_t)s * RHO_TABLE), &s_shift);
+    build_code_table(w, s_glo, s_gend, ng, (uint32_t*)(rtab + (size_t)s * RHO_TABLE), &s_shift);
 }
 
 hipError_t launch_range_prep(hipStream_t st, const DevBufs& b, bool window)
@@ -2510,8 +2505,11 @@ hipError_t launch_range_scan(hipStream_t st, const DevBufs& b)
 
 // Window of key bit patterns [lo, hi] (clamped to [0, +inf]) -> the smallest
 // fine-bin shift that covers it with WIN_BINS bins; unusable if the shift
-// exceeds WIN_MAX_SHIFT.
-__device__ void set_window(SeriesWork& w, int64_t lo, int64_t hi, bool valid)
+// exceeds WIN_MAX_SHIFT.  align: start the window at a multiple of the fine
+// bin (a few values lower), so that a fine bin shares its buckets of the range
+// sweep's code table with no key outside it; a caller's window is kept as
+// given.
+__device__ void set_window(SeriesWork& w, int64_t lo, int64_t hi, bool valid, bool align)
 {
     lo = lo < 0 ? 0 : lo;
     hi = hi > 0x7F800000ll ? 0x7F800000ll : hi;
@@ -2524,11 +2522,12 @@ __device__ void set_window(SeriesWork& w, int64_t lo, int64_t hi, bool valid)
         w.win_shift = 0u;
         return;
     }
-    const uint32_t span = (uint32_t)(hi - lo);
     // at least 2: window pass 1 forms a bin's byte offset as a right shift
     // by win_shift - 2 and a mask
     uint32_t sh = 2;
-    while (sh < 31 && (span >> sh) >= WIN_BINS) ++sh;
+    while (sh < 31 && (((uint32_t)hi - (align ? (uint32_t)lo >> sh << sh : (uint32_t)lo)) >> sh) >= WIN_BINS) ++sh;
+    if (align) lo = lo >> sh << sh;
+    const uint32_t span = (uint32_t)(hi - lo);
     w.win_lo = (uint32_t)lo;
     w.win_span = span;
     w.win_shift = sh;
@@ -2556,7 +2555,7 @@ __global__ void k_window_from_offsets(const SeriesDesc* __restrict__ sds, Series
         hi = fmax(hi, sc + ceil((t + d) * 8388608.0));
     }
     valid &= lo > -4.0e9 && hi < 4.0e9;
-    set_window(w, valid ? (int64_t)lo : 0, valid ? (int64_t)hi : -1, valid);
+    set_window(w, valid ? (int64_t)lo : 0, valid ? (int64_t)hi : -1, valid, true);
 }
 
 // Window from the sorted sketch sample: for each target rate q = k/M, the
@@ -2587,14 +2586,14 @@ __global__ void __launch_bounds__(64) k_window_from_sample(const SeriesDesc* __r
         lo = min(lo, __shfl_xor(lo, off));
         hi = max(hi, __shfl_xor(hi, off));
     }
-    if (threadIdx.x == 0) set_window(w, lo, hi, true);
+    if (threadIdx.x == 0) set_window(w, lo, hi, true, true);
 }
 
 // A window given by the caller, the same for every series.
 __global__ void k_window_fixed(SeriesWork* __restrict__ works, uint32_t S, uint32_t lo, uint32_t hi)
 {
     const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < S) set_window(works[s], (int64_t)lo, (int64_t)hi, true);
+    if (s < S) set_window(works[s], (int64_t)lo, (int64_t)hi, true, false);
 }
 
 hipError_t launch_window_fixed(hipStream_t st, const DevBufs& b, uint32_t lo, uint32_t hi)
