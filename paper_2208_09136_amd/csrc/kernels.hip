@@ -18,12 +18,14 @@
 // Along a diagonal d the embedding component k of the pair (x, x + d) is the
 // difference e(s) = y[s] - y[s + d] at s = x + (m-1-k) tau, so each lane keeps
 // |e| or e^2 of the last (m-1) tau steps in registers and needs one new
-// difference per step (the "walker").  Tiles whose every lane stays inside its
-// diagonal take that path without per-lane bounds checks; border tiles and
-// run-time (m, tau) take a plain per-cell path.
+// difference per step (the "walker").  Run-time (m, tau) form the m differences
+// of every cell anew, in blocks of cells.  As long as every lane of the band
+// stays inside its diagonal no bounds are checked; the last blocks clamp their
+// loads and mask their cells.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -173,7 +175,10 @@ __device__ __forceinline__ TileGeo tile_geo(const SeriesScalars& sd, uint32_t ti
 // parts of the other half serve as history, so the ring never moves.  Row
 // samples y[s] are wave-uniform (scalar loads); column samples y[s + d] are
 // one coalesced load per step at an immediate offset from the lane pointer,
-// issued one half-block ahead.
+// issued one half-block ahead.  half() needs every sample of the half-block
+// and of the next one inside the series; half_clamped() clamps the indexes
+// (cells past a lane's diagonal get keys of other cells, which the caller
+// masks).
 template <int NORM, int M, int TAU>
 struct Walker {
     static constexpr int W = (M - 1) * TAU;
@@ -182,15 +187,23 @@ struct Walker {
     float cnext[HU];  // column samples of the next half-block, loaded one half ahead
     const gf32* cp;  // y + d + x (this lane's column samples)
     const cf32* rp;  // y + x (row samples, uniform)
+    const float* y;
+    uint32_t d, x, last;  // last = n - 1; unsigned: d + x + W passes 2^31 next to the largest n
 
-    __device__ __forceinline__ void start(const float* y, int d, int x0)
+    __device__ __forceinline__ float col(uint32_t i) const { return ((const gf32*)y)[min(i, last)]; }
+    __device__ __forceinline__ float row(uint32_t i) const { return ((const cf32*)y)[min(i, last)]; }
+    __device__ __forceinline__ void start(const SeriesScalars& sd, int d_, int x0)
     {
-        cp = (const gf32*)y + (uint32_t)(d + x0);
-        rp = (const cf32*)y + (uint32_t)x0;
+        y = sd.y;
+        d = (uint32_t)d_;
+        x = (uint32_t)x0;
+        last = (uint32_t)sd.n - 1u;
+        cp = (const gf32*)y + (d + x);
+        rp = (const cf32*)y + x;
 #pragma unroll
-        for (int i = 0; i < W; ++i) ring[2 * HU - W + i] = part_of<NORM>(rp[i] - cp[i]);
+        for (int i = 0; i < W; ++i) ring[2 * HU - W + i] = part_of<NORM>(row(x + i) - col(d + x + i));
 #pragma unroll
-        for (int u = 0; u < HU; ++u) cnext[u] = cp[W + u];
+        for (int u = 0; u < HU; ++u) cnext[u] = col(d + x + W + u);
     }
     // part at virtual position v of the half-block that writes half H: v < W is
     // history (tail of the other half), v >= W the new part of step v - W.
@@ -199,20 +212,9 @@ struct Walker {
     {
         return v >= W ? ring[H * HU + (v >= W ? v - W : 0)] : ring[(1 - H) * HU + HU - W + (v < W ? v : 0)];
     }
-    // keys (binary32 bit patterns) of the next HU cells
     template <int H>
-    __device__ __forceinline__ void half(uint32_t (&out)[HU])
+    __device__ __forceinline__ void keys(uint32_t (&out)[HU])
     {
-        float cv[HU];
-#pragma unroll
-        for (int u = 0; u < HU; ++u) cv[u] = cnext[u];
-        // the next half-block's column samples, so their latency overlaps this
-        // half-block's work: at most 2 HU - 1 cells past the requested range,
-        // inside the walker's slack
-#pragma unroll
-        for (int u = 0; u < HU; ++u) cnext[u] = cp[W + HU + u];
-#pragma unroll
-        for (int u = 0; u < HU; ++u) ring[H * HU + u] = part_of<NORM>(rp[W + u] - cv[u]);
 #pragma unroll
         for (int u = 0; u < HU; ++u) {
             float acc = at<H>(u + W);  // component 0: the newest sample
@@ -222,63 +224,146 @@ struct Walker {
         }
         cp += HU;
         rp += HU;
+        x += HU;
+    }
+    // keys (binary32 bit patterns) of the next HU cells
+    template <int H>
+    __device__ __forceinline__ void half(uint32_t (&out)[HU])
+    {
+        float cv[HU];
+#pragma unroll
+        for (int u = 0; u < HU; ++u) cv[u] = cnext[u];
+        // the next half-block's column samples, so their latency overlaps this
+        // half-block's work
+#pragma unroll
+        for (int u = 0; u < HU; ++u) cnext[u] = cp[W + HU + u];
+#pragma unroll
+        for (int u = 0; u < HU; ++u) ring[H * HU + u] = part_of<NORM>(rp[W + u] - cv[u]);
+        keys<H>(out);
+    }
+    template <int H>
+    __device__ __forceinline__ void half_clamped(uint32_t (&out)[HU])
+    {
+        float cv[HU];
+#pragma unroll
+        for (int u = 0; u < HU; ++u) cv[u] = cnext[u];
+#pragma unroll
+        for (int u = 0; u < HU; ++u) cnext[u] = col(d + x + W + HU + u);
+#pragma unroll
+        for (int u = 0; u < HU; ++u) ring[H * HU + u] = part_of<NORM>(row(x + W + u) - cv[u]);
+        keys<H>(out);
     }
 };
 
-// Margin (cells) an interior tile keeps beyond its last cell: the walker may
-// compute up to HU - 1 cells past the end of the requested range.
-constexpr int WALK_SLACK = 32;
+// Run-time (m, tau): no ring (its length is not known to the compiler), so
+// every component's difference is formed anew, HU cells at a time and four
+// components' samples loaded together.
+template <int NORM>
+struct Walker<NORM, 0, 0> {
+    static constexpr int HU = 8;
+    static constexpr int KU = 4;  // components whose loads are in flight together
+    const float* y;
+    uint32_t d, x, last;
+    int m, tau;
 
-// Calls fb(keys, valid) for the cells x = x0 .. x0+count-1 of the lane's
-// diagonal, in order, one half-block of HU keys at a time; only the first
-// `valid` keys of a call are cells of the range (valid = HU except at the
-// end).  Every lane must own cells up to x0 + count - 1 + WALK_SLACK.
-template <int NORM, int M, int TAU, class FB>
-__device__ __forceinline__ void walk(const float* y, int d, int x0, int count, FB&& fb)
-{
-    using WK = Walker<NORM, M, TAU>;
-    constexpr int HU = WK::HU;
-    static_assert(2 * HU - 1 <= WALK_SLACK, "walker slack (the last half-block prefetches one more)");
-    WK wk;
-    wk.start(y, d, x0);
-    int rem = count;
-    while (rem >= 2 * HU) {
-        uint32_t k[HU];
-        wk.template half<0>(k);
-        fb(k, HU);
-        wk.template half<1>(k);
-        fb(k, HU);
-        rem -= 2 * HU;
+    __device__ __forceinline__ void start(const SeriesScalars& sd, int d_, int x0)
+    {
+        y = sd.y;
+        d = (uint32_t)d_;
+        x = (uint32_t)x0;
+        last = (uint32_t)sd.n - 1u;
+        m = sd.m;
+        tau = sd.tau;
     }
-    if (rem > 0) {
-        uint32_t k[HU];
-        wk.template half<0>(k);
-        fb(k, min(rem, HU));
-        rem -= HU;
-        if (rem > 0) {
-            wk.template half<1>(k);
-            fb(k, rem);
+    template <bool CLAMP>
+    __device__ __forceinline__ void block(uint32_t (&out)[HU])
+    {
+        float acc[HU];
+#pragma unroll 1
+        for (int k = 0; k < m; k += KU) {
+            float c[KU][HU];
+#pragma unroll
+            for (int j = 0; j < KU; ++j) {
+                if (k + j < m) {
+                    const uint32_t off = x + (uint32_t)((m - 1 - k - j) * tau);
+                    const gf32* cp = (const gf32*)y + (d + off);
+#pragma unroll
+                    for (int u = 0; u < HU; ++u)
+                        c[j][u] = CLAMP ? ((const gf32*)y)[min(d + off + u, last)] : cp[u];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < KU; ++j) {
+                if (k + j < m) {
+                    const uint32_t off = x + (uint32_t)((m - 1 - k - j) * tau);
+                    const cf32* rp = (const cf32*)y + off;
+#pragma unroll
+                    for (int u = 0; u < HU; ++u) {
+                        const float r = CLAMP ? ((const cf32*)y)[min(off + u, last)] : rp[u];
+                        const float p = part_of<NORM>(r - c[j][u]);
+                        acc[u] = k + j == 0 ? p : fold<NORM>(acc[u], p);
+                    }
+                }
+            }
         }
+#pragma unroll
+        for (int u = 0; u < HU; ++u) out[u] = __float_as_uint(acc[u]);
+        x += HU;
     }
-}
+    template <int H>
+    __device__ __forceinline__ void half(uint32_t (&out)[HU]) { block<false>(out); }
+    template <int H>
+    __device__ __forceinline__ void half_clamped(uint32_t (&out)[HU]) { block<true>(out); }
+};
+
+// The walker of a kernel's embedding class (m = 1 takes any tau).
+template <int NORM, int MC, int TC>
+using WalkerOf = Walker<NORM, MC, MC == 1 ? 1 : TC>;
 
 // Number of keys per call of a walk callback.
-template <int NORM, int M, int TAU>
-constexpr int walk_block() { return Walker<NORM, M, TAU>::HU; }
+template <int NORM, int MC, int TC>
+constexpr int walk_block() { return WalkerOf<NORM, MC, TC>::HU; }
 
-// End of the part of a tile the walker can take: the whole tile when every
-// lane's diagonal covers [t0, t1 + WALK_SLACK] (interior tiles), else the
-// longest prefix [t0, tw) whose cells and slack every lane of the band owns,
-// in whole pairs of half-blocks (so that state a body carries from block to
-// block is exact at tw); the cells after tw take the per-cell path.  A band
-// with fewer than 64 diagonals has no walker part.
-template <int HU>
-__device__ __forceinline__ int walk_end(const TileGeo& g)
+// Calls whole(keys) or edge(keys, x) for the cells x0 .. x1 - 1 of the lane's
+// diagonal, in order, one half-block of HU keys at a time.  whole: every lane
+// of the band owns every cell of the half-block, and all lie before x1.
+// edge: cells from x on, where lanes may be past their diagonal (x + u >=
+// g.len) and cells past x1 (the last half-block); such keys mean nothing.
+// Edge blocks cost a clamp per load and a mask per cell.  A path that formed
+// the last cells one by one waited for its loads at every step: with it the
+// three passes over one N = 1e3 series took 13.6, 23.4 and 25.1 us, with edge
+// blocks 10.1, 17.6 and 17.4 us, and one N = 20011 series with a run-time
+// embedding (m = 4, all cells one by one) 1.65 ms instead of 0.62 ms.
+template <int NORM, int MC, int TC, class FW, class FE>
+__device__ __forceinline__ void walk(const SeriesScalars& sd, const TileGeo& g, int x0, int x1, FW&& whole, FE&& edge)
 {
-    if (g.t1 + TILE_W + WALK_SLACK <= g.len0) return g.t1;
-    const int safe = g.len0 - TILE_W - WALK_SLACK;
-    if (safe <= g.t0) return g.t0;
-    return g.t0 + ((safe - g.t0) / (2 * HU)) * (2 * HU);
+    using WK = WalkerOf<NORM, MC, TC>;
+    constexpr int HU = WK::HU;
+    WK wk;
+    wk.start(sd, g.d, x0);
+    int x = x0;
+    // whole half-blocks in pairs, as long as the band's shortest diagonal
+    // holds them and the samples loaded one half-block ahead
+    const int xw = min(x1, g.len0 - (TILE_W - 1) - HU);
+    while (x + 2 * HU <= xw) {
+        uint32_t k[HU];
+        wk.template half<0>(k);
+        whole(k);
+        wk.template half<1>(k);
+        whole(k);
+        x += 2 * HU;
+    }
+    while (x < x1) {
+        uint32_t k[HU];
+        wk.template half_clamped<0>(k);
+        edge(k, x);
+        x += HU;
+        if (x < x1) {
+            wk.template half_clamped<1>(k);
+            edge(k, x);
+            x += HU;
+        }
+    }
 }
 
 // ------------------------------------------------------------------ zero / checks
@@ -442,31 +527,25 @@ template <int NORM, int MC, int TC, class Body>
 __device__ __forceinline__ void select_tile(const SeriesScalars& sd, uint32_t tile_id, int lane, Body& body)
 {
     const TileGeo g = tile_geo(sd, tile_id, lane);
-    constexpr bool kFast = MC > 0 && (MC == 1 || TC > 0);
-    int tx = g.t0;  // cells before tx are counted by the walker
-    if constexpr (kFast) {
-        constexpr int TW = MC == 1 ? 1 : TC;
-        constexpr int HU = walk_block<NORM, MC, TW>();
-        const int tw = walk_end<HU>(g);
-        if (tw > g.t0) {
-            // every lane's diagonal covers [t0, tw + WALK_SLACK]
-            walk<NORM, MC, TW>(sd.y, g.d, g.t0, tw - g.t0, [&](const uint32_t(&k)[HU], int valid) {
-                uint32_t lk[HU];
+    constexpr int HU = walk_block<NORM, MC, TC>();
+    const int lim = min(g.len, g.t1);
+    walk<NORM, MC, TC>(
+        sd, g, g.t0, g.t1,
+        [&](const uint32_t(&k)[HU]) {
+            uint32_t lk[HU];
 #pragma unroll
-                for (int u = 0; u < HU; ++u) lk[u] = body.look(k[u]);
+            for (int u = 0; u < HU; ++u) lk[u] = body.look(k[u]);
 #pragma unroll
-                for (int u = 0; u < HU; ++u)
-                    if (u < valid) body.count(k[u], lk[u]);
-            });
-            tx = tw;
-        }
-    }
-    for (int x = tx; x < g.t1; ++x) {
-        if (x < g.len) {
-            const uint32_t u = __float_as_uint(pair_key<NORM, MC, TC>(sd.y, x, x + g.d, sd.m, sd.tau));
-            body.count(u, body.look(u));
-        }
-    }
+            for (int u = 0; u < HU; ++u) body.count(k[u], lk[u]);
+        },
+        [&](const uint32_t(&k)[HU], int x) {
+            uint32_t lk[HU];
+#pragma unroll
+            for (int u = 0; u < HU; ++u) lk[u] = body.look(k[u]);
+#pragma unroll
+            for (int u = 0; u < HU; ++u)
+                if (x + u < lim) body.count(k[u], lk[u]);
+        });
 }
 
 #ifndef RQA_P1_COPIES
@@ -1256,60 +1335,54 @@ struct SweepBody {
     __device__ __forceinline__ void tile_impl(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
         const TileGeo g = tile_geo(sd, tile_id, lane);
-        constexpr bool kFast = (LMC == 1 || LMC == 2) && MC > 0 && (MC == 1 || TC > 0);
-        constexpr int TW = MC == 1 ? 1 : TC;
-        int tx = g.t0;  // cells before tx are counted by the walker
-        // lmin = 2: ranks of the cells before and at the next one counted
-        uint32_t rm1 = 0, r0 = 0;
-        if constexpr (LMC == 2) {
-            rm1 = rho_at<MULTI>(sd, g, g.t0 - 1);
-            r0 = rho_at<MULTI>(sd, g, g.t0);
-        }
-        if constexpr (kFast) {
-            constexpr int HU = walk_block<NORM, MC, TW>();
-            const int tw = walk_end<HU>(g);
-            if (tw > g.t0) {
-                // every lane's diagonal covers [t0 - 1, tw + WALK_SLACK]
-                const RhoCtx c = rc;
-                if constexpr (LMC == 1) {
-                    walk<NORM, MC, TW>(sd.y, g.d, g.t0, tw - g.t0, [&](const uint32_t(&k)[HU], int valid) {
-                        uint32_t r[HU];
-#pragma unroll
-                        for (int u = 0; u < HU; ++u) r[u] = rho_of<MULTI>(k[u], c);
-#pragma unroll
-                        for (int u = 0; u < HU; ++u)
-                            if (u < valid) emit(r[u], r[u], lane);
-                    });
-                } else {
-                    walk<NORM, MC, TW>(sd.y, g.d, g.t0 + 1, tw - g.t0, [&](const uint32_t(&k)[HU], int valid) {
-                        uint32_t r[HU];
-#pragma unroll
-                        for (int u = 0; u < HU; ++u) r[u] = rho_of<MULTI>(k[u], c);
-#pragma unroll
-                        for (int u = 0; u < HU; ++u) {
-                            if (u < valid) {
-                                emit(r0, max(r0, min(rm1, r[u])), lane);
-                                rm1 = r0;
-                                r0 = r[u];
-                            }
-                        }
-                    });
-                }
-                tx = tw;
-            }
-        }
+        constexpr int HU = walk_block<NORM, MC, TC>();
+        const RhoCtx c = rc;
         if constexpr (LMC == 1) {
-            for (int x = tx; x < g.t1; ++x) {
-                const uint32_t r = rho_at<MULTI>(sd, g, x);
-                emit(r, r, lane);
-            }
+            walk<NORM, MC, TC>(
+                sd, g, g.t0, g.t1,
+                [&](const uint32_t(&k)[HU]) {
+                    uint32_t r[HU];
+#pragma unroll
+                    for (int u = 0; u < HU; ++u) r[u] = rho_of<MULTI>(k[u], c);
+#pragma unroll
+                    for (int u = 0; u < HU; ++u) emit(r[u], r[u], lane);
+                },
+                [&](const uint32_t(&k)[HU], int x) {
+#pragma unroll
+                    for (int u = 0; u < HU; ++u) {
+                        const uint32_t r = x + u < g.len ? rho_of<MULTI>(k[u], c) : rc.Kp;
+                        if (x + u < g.t1) emit(r, r, lane);
+                    }
+                });
         } else if constexpr (LMC == 2) {
-            for (int x = tx; x < g.t1; ++x) {
-                const uint32_t rp1 = rho_at<MULTI>(sd, g, x + 1);
-                emit(r0, max(r0, min(rm1, rp1)), lane);
-                rm1 = r0;
-                r0 = rp1;
-            }
+            // ranks of the cells before and at the next one counted; the walk
+            // runs one cell ahead
+            uint32_t rm1 = rho_at<MULTI>(sd, g, g.t0 - 1);
+            uint32_t r0 = rho_at<MULTI>(sd, g, g.t0);
+            walk<NORM, MC, TC>(
+                sd, g, g.t0 + 1, g.t1 + 1,
+                [&](const uint32_t(&k)[HU]) {
+                    uint32_t r[HU];
+#pragma unroll
+                    for (int u = 0; u < HU; ++u) r[u] = rho_of<MULTI>(k[u], c);
+#pragma unroll
+                    for (int u = 0; u < HU; ++u) {
+                        emit(r0, max(r0, min(rm1, r[u])), lane);
+                        rm1 = r0;
+                        r0 = r[u];
+                    }
+                },
+                [&](const uint32_t(&k)[HU], int x) {
+#pragma unroll
+                    for (int u = 0; u < HU; ++u) {
+                        const uint32_t r = x + u < g.len ? rho_of<MULTI>(k[u], c) : rc.Kp;
+                        if (x + u <= g.t1) {
+                            emit(r0, max(r0, min(rm1, r)), lane);
+                            rm1 = r0;
+                            r0 = r;
+                        }
+                    }
+                });
         } else {
             // general lmin <= LMIN_MAX: rings of the last lmin ranks and of the
             // last lmin window maxima; output lags the newest rank by h = lmin-1.
@@ -1481,111 +1554,85 @@ struct RangeBody {
     __device__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
         const TileGeo g = tile_geo(sd, tile_id, lane);
-        constexpr bool kFast = (LMC == 1 || LMC == 2) && MC > 0 && (MC == 1 || TC > 0);
-        constexpr int TW = MC == 1 ? 1 : TC;
-        int tx = g.t0;  // cells before tx are counted by the walker
-        // lmin = 2: keys and codes of the cells before and at the next one counted
-        uint32_t km1 = 0, k0 = 0, rm1 = 0, r0 = 0;
-        if constexpr (LMC == 2) {
-            km1 = key_at(sd, g, g.t0 - 1);
-            k0 = key_at(sd, g, g.t0);
-            rm1 = code_at(km1);
-            r0 = code_at(k0);
-        }
-        if constexpr (kFast) {
-            constexpr int HU = walk_block<NORM, MC, TW>();
-            const int tw = walk_end<HU>(g);
-            if (tw > g.t0) {
-                // every lane's diagonal covers [t0 - 1, tw + WALK_SLACK]
-                CodeCtx c = rc;
-                c.sh = in_vgpr(rc.sh);
-                if constexpr (LMC == 1) {
-                    walk<NORM, MC, TW>(sd.y, g.d, g.t0, tw - g.t0, [&](const uint32_t(&k)[HU], int valid) {
-                        uint32_t r[HU];
-                        uint32_t acc = 0;
-#pragma unroll
-                        for (int u = 0; u < HU; ++u) {
-                            r[u] = code_of(k[u], c);
-                            if (u < valid) acc |= r[u];
-                        }
-                        if (__ballot(acc & 1u)) {   // rare: an odd code in the block
-#pragma unroll
-                            for (int u = 0; u < HU; ++u)
-                                if (u < valid && __ballot(r[u] & 1u)) fine_key(r[u], k[u]);
-                        }
-                    });
-                } else {
-                    // the walk runs one cell ahead: block keys are the right
-                    // neighbours of the cells counted in the block
-                    walk<NORM, MC, TW>(sd.y, g.d, g.t0 + 1, tw - g.t0, [&](const uint32_t(&k)[HU], int valid) {
-                        uint32_t r[HU];
-                        // a line code is one of the codes of its cell and the two
-                        // neighbours, so an odd code among those of the block and the
-                        // two before it covers every odd key code and line code
-                        uint32_t acc = rm1 | r0;
-#pragma unroll
-                        for (int u = 0; u < HU; ++u) {
-                            r[u] = code_of(k[u], c);
-                            acc |= r[u];
-                        }
-#pragma unroll
-                        for (int u = 0; u < HU; ++u) {
-                            if (u < valid) {
-                                const uint32_t cr = u == 0 ? r0 : r[u - 1];
-                                const uint32_t left = u == 0 ? rm1 : (u == 1 ? r0 : r[u - 2]);
-                                emit(max(cr, min(left, r[u])));
-                            }
-                        }
-                        if (__ballot(acc & 1u)) {
-                            // rare: some key or line value of the block has an odd
-                            // code; walk the block again to place them exactly
-#pragma unroll
-                            for (int u = 0; u < HU; ++u) {
-                                if (u < valid) {
-                                    const uint32_t cr = u == 0 ? r0 : r[u - 1];
-                                    const uint32_t left = u == 0 ? rm1 : (u == 1 ? r0 : r[u - 2]);
-                                    const uint32_t lam = max(cr, min(left, r[u]));
-                                    if (__ballot((cr | lam) & 1u)) {
-                                        const uint32_t ck = u == 0 ? k0 : k[u - 1];
-                                        const uint32_t lk = u == 0 ? km1 : (u == 1 ? k0 : k[u - 2]);
-                                        fine_key(cr, ck);
-                                        fine_line(lam, max(ck, min(lk, k[u])));
-                                    }
-                                }
-                            }
-                        }
-                        // state for the next block (the walk covers whole blocks
-                        // only, so after it: the keys and codes at tw - 1 and tw)
-                        km1 = k[HU - 2];
-                        k0 = k[HU - 1];
-                        rm1 = r[HU - 2];
-                        r0 = r[HU - 1];
-                    });
-                }
-                tx = tw;
-            }
-        }
+        constexpr int HU = walk_block<NORM, MC, TC>();
+        CodeCtx c = rc;
+        c.sh = in_vgpr(rc.sh);
         if constexpr (LMC == 1) {
-            for (int x = tx; x < g.t1; ++x) {
-                const uint32_t k = key_at(sd, g, x);
-                const uint32_t r = code_at(k);
-                if (__ballot(r & 1u)) fine_key(r, k);
-            }
-        } else if constexpr (LMC == 2) {
-            for (int x = tx; x < g.t1; ++x) {
-                const uint32_t kp1 = key_at(sd, g, x + 1);
-                const uint32_t rp1 = code_at(kp1);
-                const uint32_t lam = max(r0, min(rm1, rp1));
-                emit(lam);
-                if (__ballot((r0 | lam) & 1u)) {
-                    fine_key(r0, k0);
-                    fine_line(lam, max(k0, min(km1, kp1)));
+            auto block = [&](auto masked, const uint32_t(&k)[HU], int x) {
+                uint32_t r[HU];
+                uint32_t acc = 0;
+#pragma unroll
+                for (int u = 0; u < HU; ++u) {
+                    r[u] = code_of(k[u], c);
+                    if constexpr (masked)
+                        if (x + u >= min(g.len, g.t1)) r[u] = spare;
+                    acc |= r[u];
                 }
-                km1 = k0;
-                k0 = kp1;
-                rm1 = r0;
-                r0 = rp1;
-            }
+                if (__ballot(acc & 1u)) {   // rare: an odd code in the block
+#pragma unroll
+                    for (int u = 0; u < HU; ++u)
+                        if (__ballot(r[u] & 1u)) fine_key(r[u], k[u]);
+                }
+            };
+            walk<NORM, MC, TC>(
+                sd, g, g.t0, g.t1, [&](const uint32_t(&k)[HU]) { block(std::false_type{}, k, 0); },
+                [&](const uint32_t(&k)[HU], int x) { block(std::true_type{}, k, x); });
+        } else if constexpr (LMC == 2) {
+            // keys and codes of the cells before and at the next one counted;
+            // the walk runs one cell ahead: block keys are the right
+            // neighbours of the cells counted in the block
+            uint32_t km1 = key_at(sd, g, g.t0 - 1), k0 = key_at(sd, g, g.t0);
+            uint32_t rm1 = code_at(km1), r0 = code_at(k0);
+            auto block = [&](auto masked, uint32_t(&k)[HU], int x) {
+                uint32_t r[HU];
+                // a line code is one of the codes of its cell and the two
+                // neighbours, so an odd code among those of the block and the
+                // two before it covers every odd key code and line code
+                uint32_t acc = rm1 | r0;
+#pragma unroll
+                for (int u = 0; u < HU; ++u) {
+                    r[u] = code_of(k[u], c);
+                    if constexpr (masked) {
+                        if (x + u >= g.len) {
+                            r[u] = spare;
+                            k[u] = 0xFFFFFFFFu;
+                        }
+                    }
+                    acc |= r[u];
+                }
+#pragma unroll
+                for (int u = 0; u < HU; ++u) {
+                    if (masked && x + u > g.t1) break;
+                    const uint32_t cr = u == 0 ? r0 : r[u - 1];
+                    const uint32_t left = u == 0 ? rm1 : (u == 1 ? r0 : r[u - 2]);
+                    emit(max(cr, min(left, r[u])));
+                }
+                if (__ballot(acc & 1u)) {
+                    // rare: some key or line value of the block has an odd
+                    // code; walk the block again to place them exactly
+#pragma unroll
+                    for (int u = 0; u < HU; ++u) {
+                        if (masked && x + u > g.t1) break;
+                        const uint32_t cr = u == 0 ? r0 : r[u - 1];
+                        const uint32_t left = u == 0 ? rm1 : (u == 1 ? r0 : r[u - 2]);
+                        const uint32_t lam = max(cr, min(left, r[u]));
+                        if (__ballot((cr | lam) & 1u)) {
+                            const uint32_t ck = u == 0 ? k0 : k[u - 1];
+                            const uint32_t lk = u == 0 ? km1 : (u == 1 ? k0 : k[u - 2]);
+                            fine_key(cr, ck);
+                            fine_line(lam, max(ck, min(lk, k[u])));
+                        }
+                    }
+                }
+                // state for the next block
+                km1 = k[HU - 2];
+                k0 = k[HU - 1];
+                rm1 = r[HU - 2];
+                r0 = r[HU - 1];
+            };
+            walk<NORM, MC, TC>(
+                sd, g, g.t0 + 1, g.t1 + 1, [&](uint32_t(&k)[HU]) { block(std::false_type{}, k, 0); },
+                [&](uint32_t(&k)[HU], int x) { block(std::true_type{}, k, x); });
         } else {
             // general lmin <= LMIN_MAX: rings of the last lmin keys and of the
             // last lmin window maxima (keys; ranks follow); the counted cell lags
@@ -2031,37 +2078,27 @@ struct HistBody {
         top = nx = ((Kp + 1) << 24) | t0;
         at(so0) = top;
         pm = 0;
-        constexpr bool kFast = MC > 0 && (MC == 1 || TC > 0);
-        int tx = g.t0;  // cells before tx are taken by the walker
-        if constexpr (kFast) {
-            constexpr int TW = MC == 1 ? 1 : TC;
-            constexpr int HU = walk_block<NORM, MC, TW>();
-            const int tw = walk_end<HU>(g);
-            if (tw > g.t0) {
-                // every lane's diagonal covers [t0, tw + WALK_SLACK]
-                const RhoCtx c = rc;
-                uint32_t t = t0;
-                walk<NORM, MC, TW>(sd.y, g.d, g.t0, tw - g.t0, [&](const uint32_t(&k)[HU], int valid) {
-                    uint32_t rk[HU];
+        constexpr int HU = walk_block<NORM, MC, TC>();
+        const RhoCtx c = rc;
+        uint32_t t = t0;
+        walk<NORM, MC, TC>(
+            sd, g, g.t0, g.t1,
+            [&](const uint32_t(&k)[HU]) {
+                uint32_t rk[HU];
 #pragma unroll
-                    for (int u = 0; u < HU; ++u) rk[u] = rank<MULTI>(k[u], c);
+                for (int u = 0; u < HU; ++u) rk[u] = rank<MULTI>(k[u], c);
 #pragma unroll
-                    for (int u = 0; u < HU; ++u)
-                        if (u < valid) cell(rk[u], t + (uint32_t)u);
-                    t += HU;
-                });
-                tx = tw;
-            }
-        }
-        {
-            for (int x = tx; x < g.t1; ++x) {
-                uint32_t r = Kp;
-                if (x < g.len)
-                    r = min(rho_of<MULTI>(__float_as_uint(pair_key<NORM, MC, TC>(sd.y, x, x + g.d, sd.m, sd.tau)), rc),
-                            Kp);
-                cell(r, (uint32_t)x);
-            }
-        }
+                for (int u = 0; u < HU; ++u) cell(rk[u], t + (uint32_t)u);
+                t += HU;
+            },
+            [&](const uint32_t(&k)[HU], int x) {
+                uint32_t rk[HU];
+#pragma unroll
+                for (int u = 0; u < HU; ++u) rk[u] = x + u < g.len ? min(rank<MULTI>(k[u], c), Kp) : Kp;
+#pragma unroll
+                for (int u = 0; u < HU; ++u)
+                    if (x + u < g.t1) cell(rk[u], (uint32_t)(x + u));
+            });
         // trailing runs: below the last cell's rank empty, then one per stack entry
         const uint32_t e = (uint32_t)g.t1;
         #pragma unroll 1
