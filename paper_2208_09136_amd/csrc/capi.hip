@@ -352,8 +352,6 @@ struct Job {
     size_t hist_series_stride = 0;   // 0: K * hist_len (rows of consecutive series back to back)
 };
 
-rqa_status ensure_acts(rqa_ctx* c, uint32_t B, MlpActs& a);
-
 // Pass-2 slots (targets counted per launch) that fit the LDS next to the
 // bucket table; false if not even one does.
 bool pass2_slots(const rqa_ctx* c, uint32_t K, uint32_t* G)
@@ -607,9 +605,7 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         if (job.sel == 3) {
             HIP_TRY(launch_window_fixed(sm, all, c->win_lo, c->win_hi));
         } else if (job.sel == 1) {
-            MlpActs acts;
-            if ((st = ensure_acts(c, S, acts))) return st;
-            HIP_TRY(mlp_forward(sm, c->mlp, (const float*)(pool + o_feat), (int)S, acts, (float*)(pool + o_pred)));
+            HIP_TRY(mlp_forward(sm, c->mlp, (const float*)(pool + o_feat), (int)S, (float*)(pool + o_pred)));
             HIP_TRY(launch_window_from_offsets(sm, all, (const float*)(pool + o_pred), (const float*)(pool + o_delta)));
         } else {
             HIP_TRY(launch_window_from_sample(sm, all, (const uint32_t*)(pool + o_smp), nullptr, c->sample_z));
@@ -1835,7 +1831,7 @@ rqa_status ensure_mlp(rqa_ctx* c)
         (void)hipGetLastError();
         return fail(RQA_ERR_NOMEM, "hipMalloc of the network failed");
     }
-    if (hipMalloc(&c->mlp_partial, sizeof(float) * 4096) != hipSuccess) {
+    if (hipMalloc(&c->mlp_partial, sizeof(float) * mlp_loss_partials(65536)) != hipSuccess) {
         c->mlp_partial = nullptr;
         (void)hipGetLastError();
         return fail(RQA_ERR_NOMEM, "hipMalloc of the loss buffer failed");
@@ -1850,7 +1846,7 @@ rqa_status ensure_acts(rqa_ctx* c, uint32_t B, MlpActs& a)
         if (c->mlp_acts) (void)hipFree(c->mlp_acts);
         c->mlp_acts = nullptr;
         c->mlp_cap = 0;
-        const size_t per = 5 * MLP_H + 2 * MLP_OUT + MLP_H;  // Z1 A1 Z2 A2 dZ2 dZ1 + Y dY
+        const size_t per = 4 * MLP_H + MLP_OUT;  // A1 A2 dZ2 dZ1 dY
         if (hipMalloc(&c->mlp_acts, sizeof(float) * per * B) != hipSuccess) {
             c->mlp_acts = nullptr;
             (void)hipGetLastError();
@@ -1860,13 +1856,10 @@ rqa_status ensure_acts(rqa_ctx* c, uint32_t B, MlpActs& a)
     }
     float* p = c->mlp_acts;
     const size_t cap = c->mlp_cap;
-    a.Z1 = p; p += cap * MLP_H;
     a.A1 = p; p += cap * MLP_H;
-    a.Z2 = p; p += cap * MLP_H;
     a.A2 = p; p += cap * MLP_H;
     a.dZ2 = p; p += cap * MLP_H;
     a.dZ1 = p; p += cap * MLP_H;
-    a.Y = p; p += cap * MLP_OUT;
     a.dY = p;
     return RQA_OK;
 }
@@ -1880,21 +1873,24 @@ rqa_status check_model(rqa_ctx* c, uint32_t B)
     return RQA_OK;
 }
 
-// forward + backward into the gradient buffer; loss summed on the host
-rqa_status mlp_grad(rqa_ctx* c, const float* x, const float* t, uint32_t B, double* loss)
+// Forward + backward into the gradient buffer, and the loss, summed on the
+// host; grad_out (or NULL) receives the gradient in the same round trip.
+rqa_status mlp_grad(rqa_ctx* c, const float* x, const float* t, uint32_t B, float* grad_out, double* loss)
 {
+    if ((uint64_t)B * MLP_OUT > 4096ull * 256) return fail(RQA_ERR_INVALID_ARG, "batch too large for the loss buffer");
     MlpActs a;
     rqa_status st = ensure_acts(c, B, a);
     if (st) return st;
+    const int np = mlp_loss_partials((int)B);
+    if ((st = ensure_host(c, sizeof(float) * ((size_t)np + MLP_PARAMS)))) return st;
+    float* part = (float*)c->host;
     float* params = c->mlp;
     float* grad = c->mlp + MLP_PARAMS;
-    HIP_TRY(mlp_forward(c->stream, params, x, (int)B, a, a.Y));
-    int np = 0;
-    HIP_TRY(mlp_backward(c->stream, params, x, t, (int)B, a, grad, c->mlp_partial, &np));
-    if (np > 4096) return fail(RQA_ERR_INVALID_ARG, "batch too large for the loss buffer");
-    float part[4096];
+    HIP_TRY(mlp_gradients(c->stream, params, x, t, (int)B, a, grad, c->mlp_partial));
     HIP_TRY(hipMemcpyAsync(part, c->mlp_partial, sizeof(float) * np, hipMemcpyDeviceToHost, c->stream));
+    if (grad_out) HIP_TRY(hipMemcpyAsync(part + np, grad, sizeof(float) * MLP_PARAMS, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
+    if (grad_out) std::memcpy(grad_out, part + np, sizeof(float) * MLP_PARAMS);
     double sum = 0.0;
     for (int i = 0; i < np; ++i) sum += part[i];
     if (loss) *loss = sum;
@@ -1967,9 +1963,7 @@ rqa_status rqa_mlp_forward(rqa_ctx* c, const float* x_dev, uint32_t B, float* y_
     rqa_status st = check_model(c, B);
     if (st) return st;
     if (!x_dev || !y_dev) return fail(RQA_ERR_INVALID_ARG, "a device pointer is NULL");
-    MlpActs a;
-    if ((st = ensure_acts(c, B, a))) return st;
-    HIP_TRY(mlp_forward(c->stream, c->mlp, x_dev, (int)B, a, y_dev));
+    HIP_TRY(mlp_forward(c->stream, c->mlp, x_dev, (int)B, y_dev));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return RQA_OK;
 }
@@ -1980,10 +1974,7 @@ rqa_status rqa_mlp_gradients(rqa_ctx* c, const float* x_dev, const float* t_dev,
     rqa_status st = check_model(c, B);
     if (st) return st;
     if (!x_dev || !t_dev || !grad_out) return fail(RQA_ERR_INVALID_ARG, "a pointer is NULL");
-    if ((st = mlp_grad(c, x_dev, t_dev, B, loss_out))) return st;
-    HIP_TRY(hipMemcpyAsync(grad_out, c->mlp + MLP_PARAMS, sizeof(float) * MLP_PARAMS, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    return RQA_OK;
+    return mlp_grad(c, x_dev, t_dev, B, grad_out, loss_out);
 }
 
 rqa_status rqa_mlp_train_step(rqa_ctx* c, const float* x_dev, const float* t_dev, uint32_t B, float lr,
@@ -1993,7 +1984,7 @@ rqa_status rqa_mlp_train_step(rqa_ctx* c, const float* x_dev, const float* t_dev
     if (st) return st;
     if (!x_dev || !t_dev) return fail(RQA_ERR_INVALID_ARG, "a device pointer is NULL");
     if (!(lr > 0.f) || !std::isfinite(lr)) return fail(RQA_ERR_INVALID_ARG, "learning rate must be positive");
-    if ((st = mlp_grad(c, x_dev, t_dev, B, loss_out))) return st;
+    if ((st = mlp_grad(c, x_dev, t_dev, B, nullptr, loss_out))) return st;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     c->adam_t += 1;
     const float c1 = (float)(1.0 - std::pow((double)b1, (double)c->adam_t));

@@ -20,15 +20,18 @@ struct MlpOffsets {
     int b3 = W3 + MLP_H * MLP_OUT;
 };
 
-// Activations of one batch (device buffers of B rows).
+// What the weight gradients of one batch need (device buffers of B rows).
 struct MlpActs {
-    float *Z1, *A1, *Z2, *A2, *Y;  // pre-activations, activations, output
-    float *dY, *dZ2, *dZ1;         // gradients w.r.t. output and pre-activations
+    float *A1, *A2;         // activations of the hidden layers
+    float *dY, *dZ2, *dZ1;  // gradients w.r.t. output and pre-activations
 };
 
-hipError_t mlp_forward(hipStream_t st, const float* params, const float* X, int B, MlpActs& a, float* Y);
-hipError_t mlp_backward(hipStream_t st, const float* params, const float* X, const float* T, int B, MlpActs& a,
-                        float* grad, float* loss_partial, int* n_partial);
+hipError_t mlp_forward(hipStream_t st, const float* params, const float* X, int B, float* Y);
+// Gradient of the mean squared error into grad (MLP_PARAMS floats); the loss
+// is the sum of mlp_loss_partials(B) floats.
+int mlp_loss_partials(int B);
+hipError_t mlp_gradients(hipStream_t st, const float* params, const float* X, const float* T, int B, const MlpActs& a,
+                         float* grad, float* loss_partial);
 hipError_t mlp_adam(hipStream_t st, float* params, const float* grad, float* m, float* v, float lr, float b1,
                     float b2, float eps, float c1, float c2);
 
