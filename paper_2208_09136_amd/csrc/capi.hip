@@ -251,6 +251,10 @@ uint32_t chunk_for(const rqa_ctx* c, uint32_t S, uint64_t nv0, const rqa_params&
     return DEFAULT_CHUNK;
 }
 
+// Largest number of series whose descriptors, targets and results the kernels
+// access in pinned host memory.
+constexpr uint32_t DIRECT_MAX_S = 16;
+
 rqa_status ensure_pool(rqa_ctx* c, size_t bytes)
 {
     if (c->pool_bytes >= bytes) return RQA_OK;
@@ -485,14 +489,15 @@ rqa_status run_job(rqa_ctx* c, Job& job)
     const bool lines_out = (job.mode & MODE_SWEEP) != 0;
     const size_t res_words = result_words(K, lines_out);
     const size_t o_res = carve(sizeof(uint64_t) * S * res_words);
-    const size_t o_tick = carve(sizeof(uint32_t) * NUM_TICKETS);
-    // the working state is cleared with the tickets and histograms; the
-    // targets are placed into it on the device
+    const size_t o_nf = carve(sizeof(uint32_t) * S * NF_PARTS);
     const size_t o_work = carve(sizeof(SeriesWork) * S);
-    const size_t o_h1 = carve(sizeof(uint64_t) * S * SEL_N1);
-    const size_t o_h2 = carve(sizeof(uint64_t) * S * K * SEL_N2);
-    const size_t o_h3 = carve(sizeof(uint64_t) * S * K * SEL_N3);
     const bool window = (job.mode & MODE_SELECT) && job.sel != 0;
+    const bool radix = (job.mode & MODE_SELECT) && !window;
+    // tickets and histograms are cleared every call
+    const size_t o_tick = carve(sizeof(uint32_t) * NUM_TICKETS);
+    const size_t o_h1 = radix ? carve(sizeof(uint64_t) * S * SEL_N1) : 0;
+    const size_t o_h2 = radix ? carve(sizeof(uint64_t) * S * K * SEL_N2) : 0;
+    const size_t o_h3 = radix && !fused ? carve(sizeof(uint64_t) * S * K * SEL_N3) : 0;
     const size_t o_wbins = window ? carve(sizeof(uint64_t) * S * WIN_BINS) : 0;
     const size_t hist_words = hist ? (size_t)S * job.hist_len * (job.hist_kp + 1) : 0;
     const size_t o_dh = hist ? carve(sizeof(uint64_t) * hist_words) : 0;
@@ -504,9 +509,9 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         hist_tiles += (size_t)groups[gi].nchunks * CT;
     }
     const size_t run_words = hist ? hist_tiles * (job.hist_kp + 1) * TILE_W : 0;
+    const size_t zero_end = off;
     const size_t o_pre = hist ? carve(sizeof(uint16_t) * run_words) : 0;
     const size_t o_suf = hist ? carve(sizeof(uint16_t) * run_words) : 0;
-    const size_t zero_end = off;  // tickets and histograms are cleared every call
     // histogram rows: every entry written by the finishing kernel
     const size_t o_hout = hist ? carve(sizeof(uint64_t) * (size_t)S * K * job.hist_len) : 0;
     const size_t o_T1 = carve((size_t)S * SEL_N1);
@@ -541,6 +546,8 @@ rqa_status run_job(rqa_ctx* c, Job& job)
     DevBufs all;
     all.sd = (SeriesDesc*)(pool + o_sd);
     all.work = (SeriesWork*)(pool + o_work);
+    all.nf = (uint32_t*)(pool + o_nf);
+    all.nparts = std::min<uint32_t>((maxn + 1023) / 1024, NF_PARTS);
     all.tickets = (uint32_t*)(pool + o_tick);
     all.h1 = (uint64_t*)(pool + o_h1);
     all.h2 = (uint64_t*)(pool + o_h2);
@@ -593,18 +600,33 @@ rqa_status run_job(rqa_ctx* c, Job& job)
 
     Timer tm(c);
     hipStream_t sm = c->stream;
+    // on an early return the kernels already launched may still read the
+    // staging, which the next call overwrites
+    struct Drain {
+        hipStream_t s;
+        bool armed;
+        ~Drain() { if (armed) (void)hipStreamSynchronize(s); }
+    } drain{sm, true};
     HIP_TRY(tm.begin(PH_OTHER));
-    HIP_TRY(hipMemcpyAsync(all.sd, h_sd, hs_sd, hipMemcpyHostToDevice, sm));
-    HIP_TRY(hipMemcpyAsync(pool + o_tgt, h_tgt, hs_tgt, hipMemcpyHostToDevice, sm));
-    HIP_TRY(launch_zero(sm, pool + o_tick, zero_end - o_tick));
-    HIP_TRY(launch_check_finite(sm, all, maxn, (const uint64_t*)(pool + o_tgt), as_rank));
+    // A few series: kernels read descriptors and targets from the pinned
+    // staging and write the results there, over the bus, instead of waiting for
+    // three copies of about 10 us each.
+    const bool direct = !c->use_static && S <= DIRECT_MAX_S;
+    const SeriesDesc* src_sd = direct ? h_sd : all.sd;
+    const uint64_t* src_tgt = direct ? h_tgt : (const uint64_t*)(pool + o_tgt);
+    uint64_t* res = direct ? h_res : (uint64_t*)(pool + o_res);
+    if (!direct) {
+        HIP_TRY(hipMemcpyAsync(all.sd, h_sd, hs_sd, hipMemcpyHostToDevice, sm));
+        HIP_TRY(hipMemcpyAsync(pool + o_tgt, h_tgt, hs_tgt, hipMemcpyHostToDevice, sm));
+    }
+    HIP_TRY(launch_setup(sm, all, src_sd, src_tgt, as_rank, pool + o_tick, zero_end - o_tick));
     if (sketch)
         HIP_TRY(launch_sketch(sm, all, (float*)(pool + o_feat), keep_sample ? (uint32_t*)(pool + o_smp) : nullptr));
     if (window) {
-        HIP_TRY(hipMemcpyAsync(pool + o_delta, h_delta, sizeof(float) * MLP_OUT, hipMemcpyHostToDevice, sm));
         if (job.sel == 3) {
             HIP_TRY(launch_window_fixed(sm, all, c->win_lo, c->win_hi));
         } else if (job.sel == 1) {
+            HIP_TRY(hipMemcpyAsync(pool + o_delta, h_delta, sizeof(float) * MLP_OUT, hipMemcpyHostToDevice, sm));
             HIP_TRY(mlp_forward(sm, c->mlp, (const float*)(pool + o_feat), (int)S, (float*)(pool + o_pred)));
             HIP_TRY(launch_window_from_offsets(sm, all, (const float*)(pool + o_pred), (const float*)(pool + o_delta)));
         } else {
@@ -719,7 +741,7 @@ rqa_status run_job(rqa_ctx* c, Job& job)
             HIP_TRY(join());
             HIP_TRY(tm.end());
             HIP_TRY(tm.begin(PH_OTHER));
-            HIP_TRY(launch_select_scan(sm, all, pass));
+            HIP_TRY(launch_select_scan(sm, all, pass, fused));
             HIP_TRY(tm.end());
         }
     }
@@ -754,10 +776,11 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         HIP_TRY(tm.end());
     }
     if ((job.mode & MODE_SWEEP) || fused) {
-        HIP_TRY(tm.begin(PH_OTHER));
-        if (fused) HIP_TRY(launch_range_prep(sm, all, window));
-        else HIP_TRY(launch_sweep_prep(sm, all));
-        HIP_TRY(tm.end());
+        if (!fused) {
+            HIP_TRY(tm.begin(PH_OTHER));
+            HIP_TRY(launch_sweep_prep(sm, all));
+            HIP_TRY(tm.end());
+        }
         HIP_TRY(tm.begin(PH_SWEEP));
         HIP_TRY(fork());
         for (size_t gi = 0; gi < groups.size(); ++gi) {
@@ -776,12 +799,12 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         HIP_TRY(tm.end());
         if (fused) {
             HIP_TRY(tm.begin(PH_OTHER));
-            HIP_TRY(launch_range_scan(sm, all));
+            HIP_TRY(launch_range_scan(sm, all, res));
             HIP_TRY(tm.end());
         }
     }
-    HIP_TRY(launch_pack_results(sm, all, lines_out, (uint64_t*)(pool + o_res)));
-    HIP_TRY(hipMemcpyAsync(h_res, pool + o_res, hs_res, hipMemcpyDeviceToHost, sm));
+    if (!fused) HIP_TRY(launch_pack_results(sm, all, lines_out, res));
+    if (!direct) HIP_TRY(hipMemcpyAsync(h_res, res, hs_res, hipMemcpyDeviceToHost, sm));
     if (hs_feat) HIP_TRY(hipMemcpyAsync(h_feat, pool + o_feat, hs_feat, hipMemcpyDeviceToHost, sm));
     if (hs_smp) HIP_TRY(hipMemcpyAsync(h_smp, pool + o_smp, hs_smp, hipMemcpyDeviceToHost, sm));
     if (hist) {
@@ -794,6 +817,7 @@ rqa_status run_job(rqa_ctx* c, Job& job)
                                    sizeof(uint64_t) * rows, hipMemcpyDeviceToHost, sm));
     }
     HIP_TRY(hipStreamSynchronize(sm));
+    drain.armed = false;
     tm.collect();
 
     // results, back in caller order
@@ -815,13 +839,16 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         const uint32_t s = order[i];
         // packed results of device series i (layout at k_pack_results)
         const uint64_t* w = h_res + (size_t)i * res_words;
-        const uint32_t status = (uint32_t)w[0], nonfinite = (uint32_t)(w[0] >> 32);
+        uint32_t status = (uint32_t)w[0];
+        const uint32_t nonfinite = (uint32_t)(w[0] >> 32);
         const uint32_t scale = (uint32_t)w[1], range_ok = (uint32_t)(w[1] >> 32);
         const uint64_t* w_eps = w + 3;
         const uint64_t* w_k = w_eps + K;
         const uint64_t* w_count = w_k + K;
         const uint64_t* w_dcount = w_count + K;
         const uint64_t* w_hitmap = w_dcount + K;
+        if (fused)
+            for (uint32_t r = 0; r < K; ++r) status |= (uint32_t)(w_hitmap[r] >> 32);
         if (nonfinite) return fail(RQA_ERR_NONFINITE, "series %u holds a NaN or infinite sample", s);
         if (status & ~8u) return fail(RQA_ERR_DEVICE, "selection of series %u is inconsistent (code %u)", s, status);
         if (job.mode & MODE_SKETCH) {

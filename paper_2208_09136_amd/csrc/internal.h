@@ -160,6 +160,8 @@ struct DevBufs {
     uint64_t* fineK;    // range sweep: [S][fine_stride] sub-value counts of keys
     uint64_t* fineL;    //              and of line values
     uint32_t fine_stride;
+    uint32_t* nf;       // [S][NF_PARTS] parts of a series with a NaN or infinite sample
+    uint32_t nparts;    // parts in use
     uint32_t* tickets;  // work-queue counters, one per launch
     uint32_t S, K;
     uint32_t nchunks;   // over all series
@@ -167,12 +169,16 @@ struct DevBufs {
 };
 
 constexpr int NUM_TICKETS = 256;
+constexpr uint32_t NF_PARTS = 64;
 
 // Kernel launchers (kernels.hip).  Each returns the hipError_t of the launch.
 hipError_t launch_zero(hipStream_t st, void* p, size_t bytes);
-// Flags non-finite samples and places the targets tgt[S][K] (ranks when
-// as_rank, else threshold bit patterns) into the zeroed working state.
-hipError_t launch_check_finite(hipStream_t st, const DevBufs& b, uint32_t maxn, const uint64_t* tgt, bool as_rank);
+// Set-up of a call: descriptors src[S] (device or pinned host memory) to b.sd,
+// working state cleared and targets tgt[S][K] placed in it (ranks when as_rank,
+// else threshold bit patterns), non-finite samples looked for, zero_bytes (a
+// multiple of 16) cleared at zero.
+hipError_t launch_setup(hipStream_t st, const DevBufs& b, const SeriesDesc* src, const uint64_t* tgt, bool as_rank,
+                        void* zero, size_t zero_bytes);
 // Results the host reads, result_words(K, lines) words per series (layout at
 // k_pack_results).
 __host__ __device__ __forceinline__ size_t result_words(uint32_t K, bool lines) { return 3 + (size_t)(lines ? 7 : 5) * K; }
@@ -180,17 +186,16 @@ hipError_t launch_pack_results(hipStream_t st, const DevBufs& b, bool lines, uin
 hipError_t launch_select_pass(hipStream_t st, const DevBufs& b, int pass, int variant,
                               uint32_t grid, uint32_t block, uint32_t groups, uint32_t group_slots,
                               uint32_t ticket_base);
-hipError_t launch_select_scan(hipStream_t st, const DevBufs& b, int pass);
+// Scan after pass 1, 2 or 3; after pass 2 with fused, the range sweep's set-up.
+hipError_t launch_select_scan(hipStream_t st, const DevBufs& b, int pass, bool fused);
 hipError_t launch_sweep_prep(hipStream_t st, const DevBufs& b);
 // ranges = false: sweep at given thresholds (rank table from k_sweep_prep);
-// ranges = true: range sweep (rank table from k_range_prep)
+// ranges = true: range sweep (code table from the scan before it)
 hipError_t launch_sweep(hipStream_t st, const DevBufs& b, int variant, bool ranges, uint32_t grid,
                         uint32_t block, uint32_t ticket);
-// Range sweep set-up after the counting passes: from the plain selection
-// state after scan 2 (window = false) or from the window state after window
-// scan 1 (window = true); and the final scan giving eps, C and D.
-hipError_t launch_range_prep(hipStream_t st, const DevBufs& b, bool window);
-hipError_t launch_range_scan(hipStream_t st, const DevBufs& b);
+// After the range sweep: eps, C and D into the host's result words (device or
+// pinned host memory).
+hipError_t launch_range_scan(hipStream_t st, const DevBufs& b, uint64_t* out);
 // Full line-length histogram at given thresholds (after k_sweep_prep) over
 // the (band, segment) tiles: difference counts dglob[S][hist_len][Kp + 1]
 // (two's complement in uint64; cleared by the caller) of the lines inside a
@@ -223,6 +228,7 @@ hipError_t launch_window_from_sample(hipStream_t st, const DevBufs& b, const uin
                                      float z);
 hipError_t launch_window_pass(hipStream_t st, const DevBufs& b, const WinBufs& w, int pass, int variant, uint32_t grid,
                               uint32_t block, uint32_t ticket);
+// Scan after window pass 1 (without w.fine: and the range sweep's set-up) or 2.
 hipError_t launch_window_scan(hipStream_t st, const DevBufs& b, const WinBufs& w, int pass);
 size_t window_lds_bytes(int pass);
 int window_blocks_per_cu(int pass, int variant, uint32_t block);

@@ -384,40 +384,68 @@ hipError_t launch_zero(hipStream_t st, void* p, size_t bytes)
     return hipGetLastError();
 }
 
-// Per series: flags a NaN or infinite sample, and (block x = 0) places the
-// call's targets into the zeroed working state: tgt[s * K + r] is target r's
-// rank (selection) or threshold bit pattern (given thresholds).
-__global__ void k_check_finite(const SeriesDesc* __restrict__ sds, SeriesWork* __restrict__ works,
-                               const uint64_t* __restrict__ tgt, uint32_t K, uint32_t as_rank)
+// First kernel of a call, one launch for what took two copies and two
+// launches: block (0, s) brings series s's descriptor to the device (src and
+// dst differ where the host's pinned copy is read directly), clears its working
+// state and places its targets tgt[s * K + r] (ranks, or threshold bit
+// patterns); blocks x < nparts look for NaN or infinite samples (nf[s][x]); and
+// all blocks share the clearing of the call's counters.
+__global__ void __launch_bounds__(256)
+k_setup(const SeriesDesc* __restrict__ src, SeriesDesc* __restrict__ dst, SeriesWork* __restrict__ works,
+        const uint64_t* __restrict__ tgt, uint32_t K, uint32_t as_rank, uint4* __restrict__ zero, size_t nzero,
+        uint32_t* __restrict__ nf, uint32_t nparts)
 {
-    const SeriesDesc& sd = sds[blockIdx.y];
-    SeriesWork& w = works[blockIdx.y];
-    if (blockIdx.x == 0 && tgt) {
+    const uint32_t s = blockIdx.y;
+    const float* y = src[s].y;
+    const uint32_t n = src[s].n;
+    if (blockIdx.x == 0) {
+        SeriesWork& w = works[s];
+        for (uint32_t i = threadIdx.x; i < sizeof(SeriesWork) / 4; i += blockDim.x) ((uint32_t*)&w)[i] = 0u;
+        if (dst != src)
+            for (uint32_t i = threadIdx.x; i < sizeof(SeriesDesc) / 4; i += blockDim.x)
+                ((uint32_t*)&dst[s])[i] = ((const uint32_t*)&src[s])[i];
+        __syncthreads();
         for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) {
-            const uint64_t v = tgt[(size_t)blockIdx.y * K + r];
+            const uint64_t v = tgt[(size_t)s * K + r];
             if (as_rank) w.k[r] = v;
             else w.eps_bits[r] = (uint32_t)v;
         }
     }
-    bool bad = false;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < sd.n; i += gridDim.x * blockDim.x) {
-        const uint32_t u = __float_as_uint(sd.y[i]);
-        bad |= (u & 0x7F800000u) == 0x7F800000u;
+    const size_t b = (size_t)s * gridDim.x + blockIdx.x, nb = (size_t)gridDim.x * gridDim.y;
+    for (size_t i = b * blockDim.x + threadIdx.x; i < nzero; i += nb * blockDim.x) zero[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (blockIdx.x < nparts) {  // uniform over the block
+        bool bad = false;
+        for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += nparts * blockDim.x)
+            bad |= (__float_as_uint(y[i]) & 0x7F800000u) == 0x7F800000u;
+        const int any = __syncthreads_or(bad);
+        if (threadIdx.x == 0) nf[s * NF_PARTS + blockIdx.x] = any ? 1u : 0u;
     }
-    if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(&w.nonfinite, 1u);
 }
 
-hipError_t launch_check_finite(hipStream_t st, const DevBufs& b, uint32_t maxn, const uint64_t* tgt, bool as_rank)
+hipError_t launch_setup(hipStream_t st, const DevBufs& b, const SeriesDesc* src, const uint64_t* tgt, bool as_rank,
+                        void* zero, size_t zero_bytes)
 {
-    uint32_t gx = std::min<uint32_t>((maxn + 255) / 256, 1024);
-    hipLaunchKernelGGL(k_check_finite, dim3(gx, b.S), dim3(256), 0, st, b.sd, b.work, tgt, b.K, as_rank ? 1u : 0u);
+    // four 16-byte stores per thread, at most 4096 workgroups over all series
+    const size_t share = (zero_bytes / 16 + 1023) / 1024;
+    const uint32_t gx = (uint32_t)std::max<size_t>(b.nparts, std::min<size_t>((share + b.S - 1) / b.S, (4096 + b.S - 1) / b.S));
+    hipLaunchKernelGGL(k_setup, dim3(gx, b.S), dim3(256), 0, st, src, b.sd, b.work, tgt, b.K, as_rank ? 1u : 0u,
+                       (uint4*)zero, zero_bytes / 16, b.nf, b.nparts);
     return hipGetLastError();
+}
+
+// Whether a part of series s holds a NaN or infinite sample; called by a whole
+// block of at least NF_PARTS threads, which gets the answer on every thread.
+__device__ __forceinline__ bool block_nonfinite(const uint32_t* __restrict__ nf, uint32_t nparts, uint32_t s)
+{
+    return __syncthreads_or(threadIdx.x < nparts && nf[s * NF_PARTS + threadIdx.x] != 0u) != 0;
 }
 
 // The results the host reads, packed per series into result_words(K, lines)
 // 64-bit words: [0] status | nonfinite << 32, [1] scale | range_ok << 32,
 // [2] Kp, then K words each of eps_bits, k, count, dcount, win_hit | dmap
-// << 32, and with lines (threshold sweep) Kp words each of hrho and hlam.
+// << 32 (the range scan, which writes the words itself: win_hit | its own
+// status << 32), and with lines (threshold sweep) Kp words each of hrho and
+// hlam.
 __global__ void k_pack_results(const SeriesWork* __restrict__ works, uint32_t K, uint32_t lines, uint64_t* __restrict__ out)
 {
     const SeriesWork& w = works[blockIdx.x];
@@ -888,22 +916,6 @@ __device__ __forceinline__ uint64_t block_sum(uint64_t v)
     return tot;
 }
 
-// Inclusive prefix sums of n (multiple of blockDim.x) u64 values into LDS.
-__device__ void block_cumsum(const uint64_t* __restrict__ src, uint64_t* cum, uint32_t n)
-{
-    const uint32_t per = n / blockDim.x;
-    const uint32_t base = threadIdx.x * per;
-    uint64_t s = 0;
-    for (uint32_t i = 0; i < per; ++i) {
-        s += src[base + i];
-        cum[base + i] = s;
-    }
-    uint64_t tot;
-    const uint64_t off = block_excl_scan(s, &tot);
-    for (uint32_t i = 0; i < per; ++i) cum[base + i] += off;
-    __syncthreads();
-}
-
 // A u64 moved between lanes by a DPP control (row_mask and bank_mask all
 // rows and banks).
 template <int CTRL>
@@ -1058,16 +1070,30 @@ __device__ uint32_t block_sort_unique(const uint32_t* v, const uint32_t* keep, u
 }
 
 // After pass 1: locate each target's bucket, assign pass-2 slots, fill T1.
-__global__ void __launch_bounds__(256) k_scan1(const SeriesDesc* __restrict__ sds, SeriesWork* __restrict__ works,
-                                               uint8_t* __restrict__ T1, const uint64_t* __restrict__ h1)
+// Four buckets per thread: with 256 threads of 16 buckets each the kernel took
+// 12 us, most of it waiting for each thread's 16 loads.
+__global__ void __launch_bounds__(SEL_N1 / 4) k_scan1(const SeriesDesc* __restrict__ sds, SeriesWork* __restrict__ works,
+                                                      uint8_t* __restrict__ T1, const uint64_t* __restrict__ h1,
+                                                      const uint32_t* __restrict__ nf, uint32_t nparts)
 {
     __shared__ uint64_t cum[SEL_N1];
     __shared__ uint32_t s_pre[RQA_MAX_K], uniq[RQA_MAX_K], s_pos[RQA_MAX_K], s_flag[RQA_MAX_K];
     const uint32_t s = blockIdx.x;
     const uint32_t K = sds[s].K;
     SeriesWork& w = works[s];
-    block_cumsum(h1 + (size_t)s * SEL_N1, cum, SEL_N1);
-    for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) {
+    const uint64_t* h = h1 + (size_t)s * SEL_N1 + 4 * threadIdx.x;
+    const uint64_t v0 = h[0], v1 = v0 + h[1], v2 = v1 + h[2], v3 = v2 + h[3];
+    ((uint32_t*)(T1 + (size_t)s * SEL_N1))[threadIdx.x] = NO_SLOT * 0x01010101u;
+    const bool bad = block_nonfinite(nf, nparts, s);
+    uint64_t tot;
+    const uint64_t off = block_excl_scan(v3, &tot);
+    cum[4 * threadIdx.x] = off + v0;
+    cum[4 * threadIdx.x + 1] = off + v1;
+    cum[4 * threadIdx.x + 2] = off + v2;
+    cum[4 * threadIdx.x + 3] = off + v3;
+    __syncthreads();
+    const uint32_t r = threadIdx.x;
+    if (r < K) {
         const uint64_t k = w.k[r];
         const uint32_t b = first_reaching(cum, SEL_N1, k);
         if (cum[b] < k) atomicOr(&w.status, 1u);
@@ -1075,38 +1101,14 @@ __global__ void __launch_bounds__(256) k_scan1(const SeriesDesc* __restrict__ sd
         w.below[r] = b ? cum[b - 1] : 0;
         s_pre[r] = b;
     }
-    uint8_t* t1 = T1 + (size_t)s * SEL_N1;
-    for (uint32_t i = threadIdx.x; i < SEL_N1; i += blockDim.x) t1[i] = NO_SLOT;
     __syncthreads();
     const uint32_t nu = block_sort_unique(s_pre, nullptr, K, uniq, s_pos, s_flag);
-    for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) w.slot[r] = s_pos[r];
-    for (uint32_t u = threadIdx.x; u < nu; u += blockDim.x) t1[uniq[u]] = (uint8_t)u;
-    if (threadIdx.x == 0) w.nslots2 = nu;
-}
-
-// After pass 2: resolve SEL_B2 more bits per target, assign pass-3 slots,
-// fill T2 (per pass-2 slot and sub-bucket).
-__global__ void __launch_bounds__(256) k_scan2(const SeriesDesc* __restrict__ sds, SeriesWork* __restrict__ works,
-                                               uint8_t* __restrict__ T2, const uint64_t* __restrict__ h2all)
-{
-    __shared__ uint32_t s_pre[RQA_MAX_K], uniq[RQA_MAX_K], s_pos[RQA_MAX_K], s_flag[RQA_MAX_K];
-    const uint32_t s = blockIdx.x;
-    const uint32_t K = sds[s].K;
-    SeriesWork& w = works[s];
-    uint8_t* t2 = T2 + (size_t)s * K * SEL_N2;
-    const uint32_t n2 = w.nslots2;
-    const uint64_t* h2 = h2all + (size_t)s * K * SEL_N2;
-    (void)h2;
-    for (uint32_t i = threadIdx.x; i < n2 * SEL_N2; i += blockDim.x) t2[i] = NO_SLOT;
-    // below / prefix of every target come from k_scan2_find
-    for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) s_pre[r] = w.prefix[r];
-    __syncthreads();
-    const uint32_t nu = block_sort_unique(s_pre, nullptr, K, uniq, s_pos, s_flag);
-    for (uint32_t r = threadIdx.x; r < K; r += blockDim.x)
-        t2[w.slot[r] * SEL_N2 + (s_pre[r] & (SEL_N2 - 1))] = (uint8_t)s_pos[r];
-    __syncthreads();
-    for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) w.slot[r] = s_pos[r];
-    if (threadIdx.x == 0) w.nslots3 = nu;
+    if (r < K) w.slot[r] = s_pos[r];
+    if (r < nu) T1[(size_t)s * SEL_N1 + uniq[r]] = (uint8_t)r;
+    if (r == 0) {
+        w.nslots2 = nu;
+        w.nonfinite = bad ? 1u : 0u;
+    }
 }
 
 // First bin of a target's histogram row whose prefix reaches want: one
@@ -1133,25 +1135,6 @@ __device__ void target_bin(const uint64_t* __restrict__ h, uint32_t n, uint64_t 
     }
 }
 
-// Pass-2 bins of every target (workgroup per series and target), before k_scan2.
-__global__ void __launch_bounds__(256) k_scan2_find(const SeriesDesc* __restrict__ sds,
-                                                    SeriesWork* __restrict__ works, const uint64_t* __restrict__ h2all)
-{
-    __shared__ uint64_t pre[257];
-    __shared__ uint32_t s_c;
-    __shared__ uint64_t s_run;
-    const uint32_t s = blockIdx.x, r = blockIdx.y;
-    const uint32_t K = sds[s].K;
-    if (r >= K) return;
-    SeriesWork& w = works[s];
-    const uint64_t* h = h2all + (size_t)s * K * SEL_N2 + (size_t)w.slot[r] * SEL_N2;
-    target_bin(h, SEL_N2, w.k[r] - w.below[r], w, 2u, pre, &s_c, &s_run);
-    if (threadIdx.x == 0) {
-        w.below[r] += s_run;
-        w.prefix[r] = (w.prefix[r] << SEL_B2) | s_c;
-    }
-}
-
 // After pass 3: the last SEL_B3 bits give the threshold; count = #{key <= eps}.
 // Workgroup per series and target.
 __global__ void __launch_bounds__(256) k_scan3(const SeriesDesc* __restrict__ sds, SeriesWork* __restrict__ works,
@@ -1170,16 +1153,6 @@ __global__ void __launch_bounds__(256) k_scan3(const SeriesDesc* __restrict__ sd
         w.eps_bits[r] = (w.prefix[r] << SEL_B3) | s_c;
         w.count[r] = w.below[r] + s_run + h[s_c];
     }
-}
-
-hipError_t launch_select_scan(hipStream_t st, const DevBufs& b, int pass)
-{
-    if (pass == 1) hipLaunchKernelGGL(k_scan1, dim3(b.S), dim3(256), 0, st, b.sd, b.work, b.T1, b.h1);
-    else if (pass == 2) {
-        hipLaunchKernelGGL(k_scan2_find, dim3(b.S, b.K), dim3(256), 0, st, b.sd, b.work, b.h2);
-        hipLaunchKernelGGL(k_scan2, dim3(b.S), dim3(256), 0, st, b.sd, b.work, b.T2, b.h2);
-    } else hipLaunchKernelGGL(k_scan3, dim3(b.S, b.K), dim3(256), 0, st, b.sd, b.work, b.h3);
-    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ sweep
@@ -1886,7 +1859,8 @@ __device__ void build_rank_table(SeriesWork& w, const uint32_t* es, uint32_t kp,
 // Sweep at given thresholds: per series the distinct sorted thresholds, the
 // caller->distinct map and the rank table.
 __global__ void __launch_bounds__(PREP_THREADS) k_sweep_prep(const SeriesDesc* __restrict__ sds,
-                                                    SeriesWork* __restrict__ works, uint2* __restrict__ rtab)
+                                                    SeriesWork* __restrict__ works, uint2* __restrict__ rtab,
+                                                    const uint32_t* __restrict__ nf, uint32_t nparts)
 {
     __shared__ uint32_t s_eps[RQA_MAX_K], es[RQA_MAX_K], s_pos[RQA_MAX_K], s_flag[RQA_MAX_K];
     __shared__ uint32_t s_shift;
@@ -1894,7 +1868,8 @@ __global__ void __launch_bounds__(PREP_THREADS) k_sweep_prep(const SeriesDesc* _
     const uint32_t K = sds[s].K;
     SeriesWork& w = works[s];
     for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) s_eps[r] = w.eps_bits[r];
-    __syncthreads();
+    const bool bad = block_nonfinite(nf, nparts, s);
+    if (threadIdx.x == 0) w.nonfinite = bad ? 1u : 0u;
     const uint32_t kp = block_sort_unique(s_eps, nullptr, K, es, s_pos, s_flag);
     for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) w.dmap[r] = s_pos[r];
     build_rank_table(w, es, kp, rtab + (size_t)s * RHO_TABLE, &s_shift);
@@ -1902,7 +1877,7 @@ __global__ void __launch_bounds__(PREP_THREADS) k_sweep_prep(const SeriesDesc* _
 
 hipError_t launch_sweep_prep(hipStream_t st, const DevBufs& b)
 {
-    hipLaunchKernelGGL(k_sweep_prep, dim3(b.S), dim3(PREP_THREADS), 0, st, b.sd, b.work, b.rtab);
+    hipLaunchKernelGGL(k_sweep_prep, dim3(b.S), dim3(PREP_THREADS), 0, st, b.sd, b.work, b.rtab, b.nf, b.nparts);
     return hipGetLastError();
 }
 
@@ -2321,73 +2296,66 @@ __device__ void build_code_table(SeriesWork& w, const uint32_t* glo, const uint6
     for (uint32_t i = threadIdx.x; i < RANK_MAX + 2; i += blockDim.x) { w.hrho[i] = 0; w.hlam[i] = 0; }
     const uint32_t a0 = glo[0] >> sh;
     const uint32_t aL = a0 ? a0 - 1u : 0u;
-    for (uint32_t word = threadIdx.x; word < CODE_TABLE / 4; word += blockDim.x) {
-        uint32_t packed = 0, g = 0, prev = 0xFFFFFFFFu;
+    // 32 buckets per thread and step: one search, then a walk along the groups
+    for (uint32_t i0 = 32u * threadIdx.x; i0 < CODE_TABLE; i0 += 32u * blockDim.x) {
+        uint32_t g = 0, prev = 0;
+        uint64_t gl = 0, ge = 0;  // group g: its start and end (no key reaches group ng)
+        uint32_t out[8];
 #pragma unroll
-        for (uint32_t i = 0; i < 4; ++i) {
-            const uint32_t a = aL + ((4u * word + i - aL) & (CODE_TABLE - 1u));
-            const uint64_t lo = (uint64_t)a << sh, hi = (uint64_t)(a + 1u) << sh;
-            if (a != prev + 1u || i == 0) {
-                // first group that ends above the bucket's start
-                uint32_t b = 0, e = ng;
-                while (b < e) {
-                    const uint32_t mid = (b + e) >> 1;
-                    if (gend[mid] <= lo) b = mid + 1; else e = mid;
+        for (uint32_t v = 0; v < 8; ++v) {
+            uint32_t packed = 0;
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) {
+                const uint32_t a = aL + ((i0 + 4u * v + i - aL) & (CODE_TABLE - 1u));
+                const uint64_t lo = (uint64_t)a << sh, hi = (uint64_t)(a + 1u) << sh;
+                if (v + i == 0 || a != prev + 1u) {
+                    // first group that ends above the bucket's start
+                    uint32_t b = 0, e = ng;
+                    while (b < e) {
+                        const uint32_t mid = (b + e) >> 1;
+                        if (gend[mid] <= lo) b = mid + 1; else e = mid;
+                    }
+                    g = b;
+                    gl = g < ng ? glo[g] : ~0ull;
+                    ge = g < ng ? gend[g] : ~0ull;
+                } else {
+                    while (ge <= lo) {
+                        ++g;
+                        gl = g < ng ? glo[g] : ~0ull;
+                        ge = g < ng ? gend[g] : ~0ull;
+                    }
                 }
-                g = b;
-            } else {
-                while (g < ng && gend[g] <= lo) ++g;
+                prev = a;
+                packed |= (2u * g + (gl < hi ? 1u : 0u)) << (8u * i);
             }
-            prev = a;
-            const uint32_t code = 2u * g + (g < ng && (uint64_t)glo[g] < hi ? 1u : 0u);
-            packed |= code << (8u * i);
+            out[v] = packed;
         }
-        tab[word] = packed;
+        uint4* dst = (uint4*)tab + i0 / 16u;
+        dst[0] = make_uint4(out[0], out[1], out[2], out[3]);
+        dst[1] = make_uint4(out[4], out[5], out[6], out[7]);
     }
 }
 
-// Range sweep set-up.  Every target's key lies in a candidate range of
-// 2^bits bit patterns starting at a_r, with rbase_r keys below it: after
-// plain scan 2 (a_r = 21-bit prefix << SEL_B3, rbase = keys below the
-// prefix) or after window scan 1 (a_r = fine-bin start, rbase = keys below
-// the fine bin; a series with a target outside its window is left out).
-// Distinct ranges are sorted, adjacent ones merge into groups, and the code
-// table is built over the groups; the fine counters of the ranges are cleared.
-__global__ void __launch_bounds__(PREP_THREADS) k_range_prep(const SeriesDesc* __restrict__ sds,
-                                                    SeriesWork* __restrict__ works, uint2* __restrict__ rtab,
-                                                    uint64_t* __restrict__ fineK, uint64_t* __restrict__ fineL,
-                                                    uint32_t fine_stride, uint32_t window)
+// Range sweep set-up, the last part of the scan that locates the targets (its
+// own launch cost about 7 us more).  Every target's key lies in a candidate
+// range of 2^bits bit patterns starting at s_addr[r] (LDS), with w.rbase[r]
+// keys below it; ok: the series takes part (no NaN or infinite sample, and no
+// target outside its window).  Distinct ranges are sorted, adjacent ones merge
+// into groups, and the code table is built over the groups; the fine counters
+// of the ranges are cleared.  Called by a whole block of at least RQA_MAX_K
+// threads, after a barrier behind the writes of s_addr.
+__device__ void range_prep(SeriesWork& w, uint32_t s, uint32_t K, uint32_t bits, bool ok, const uint32_t* s_addr,
+                           uint2* __restrict__ rtab, uint64_t* __restrict__ fineK, uint64_t* __restrict__ fineL,
+                           uint32_t fine_stride)
 {
     __shared__ uint64_t s_gend[RQA_MAX_K];
     __shared__ uint32_t sub[RQA_MAX_K];
-    // the per-target inputs and the group arrays in LDS, worked on by one
-    // thread per target or range (serially, each step would wait on a round
-    // trip to memory or LDS)
-    __shared__ uint32_t s_addr[RQA_MAX_K], s_tsub[RQA_MAX_K], s_tgroup[RQA_MAX_K];
+    // the group arrays in LDS, worked on by one thread per target or range
+    // (serially, each step would wait on a round trip to memory or LDS)
+    __shared__ uint32_t s_tsub[RQA_MAX_K], s_tgroup[RQA_MAX_K];
     __shared__ uint32_t s_flag[RQA_MAX_K], s_gid[RQA_MAX_K];
     __shared__ uint32_t s_glo[RQA_MAX_K + 1], s_goff[RQA_MAX_K + 1];
-    __shared__ uint32_t s_shift, s_miss;
-    const uint32_t s = blockIdx.x;
-    const uint32_t K = sds[s].K;
-    SeriesWork& w = works[s];
-    const uint32_t bits = window ? w.win_shift : (uint32_t)SEL_B3;
-    if (threadIdx.x == 0) s_miss = 0u;
-    __syncthreads();
-    // each target's range start and base count, loaded in parallel
-    for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) {
-        if (window) {
-            if (!w.win_hit[r]) atomicOr(&s_miss, 1u);
-            s_addr[r] = w.win_lo + (w.win_fbin[r] << bits);
-            w.rbase[r] = w.win_base[r];
-        } else {
-            s_addr[r] = w.prefix[r] << SEL_B3;
-            w.rbase[r] = w.below[r];
-        }
-    }
-    __syncthreads();
-    // series with a NaN or infinite sample end in an error; keep them out
-    // (the same value on every thread)
-    const bool ok = w.nonfinite == 0u && (!window || (w.win_ok != 0u && s_miss == 0u));
+    __shared__ uint32_t s_shift;
     uint32_t ns = 0, ng = 0;
     if (ok) {
         ns = block_sort_unique(s_addr, nullptr, K, sub, s_tsub, s_flag);
@@ -2438,21 +2406,102 @@ __global__ void __launch_bounds__(PREP_THREADS) k_range_prep(const SeriesDesc* _
         w.g_lo[g] = s_glo[g];
         w.g_off[g] = s_goff[g];
     }
-    // clear the fine counters of the ranges
+    // clear the fine counters of the ranges (two per 16-byte store: a range
+    // holds at least four)
     const uint32_t nfine = ns << bits;
-    uint64_t* fk = fineK + (size_t)s * fine_stride;
-    uint64_t* fl = fineL + (size_t)s * fine_stride;
-    for (uint32_t i = threadIdx.x; i < nfine; i += blockDim.x) {
-        fk[i] = 0;
-        fl[i] = 0;
+    uint4* fk = (uint4*)(fineK + (size_t)s * fine_stride);
+    uint4* fl = (uint4*)(fineL + (size_t)s * fine_stride);
+    for (uint32_t i = threadIdx.x; i < nfine / 2; i += blockDim.x) {
+        fk[i] = make_uint4(0u, 0u, 0u, 0u);
+        fl[i] = make_uint4(0u, 0u, 0u, 0u);
     }
     build_code_table(w, s_glo, s_gend, ng, (uint32_t*)(rtab + (size_t)s * RHO_TABLE), &s_shift);
 }
 
-hipError_t launch_range_prep(hipStream_t st, const DevBufs& b, bool window)
+// After pass 2: resolve SEL_B2 more bits per target, a wave per target (each
+// lane sums eight of the row's SEL_N2 bins).  FUSED: the targets' 21-bit
+// prefixes are the range sweep's candidate ranges; else pass 3 follows: assign
+// its slots and fill T2 (per pass-2 slot and sub-bucket).
+template <bool FUSED>
+__global__ void __launch_bounds__(PREP_THREADS) k_scan2(const SeriesDesc* __restrict__ sds, SeriesWork* __restrict__ works,
+                                                        uint8_t* __restrict__ T2, const uint64_t* __restrict__ h2all,
+                                                        uint2* __restrict__ rtab, uint64_t* __restrict__ fineK,
+                                                        uint64_t* __restrict__ fineL, uint32_t fine_stride)
 {
-    hipLaunchKernelGGL(k_range_prep, dim3(b.S), dim3(PREP_THREADS), 0, st, b.sd, b.work, b.rtab, b.fineK, b.fineL,
-                       b.fine_stride, window ? 1u : 0u);
+    static_assert(SEL_N2 == 64 * 8, "a wave takes a row of pass-2 bins, eight per lane");
+    __shared__ uint32_t s_pre[RQA_MAX_K], uniq[RQA_MAX_K], s_pos[RQA_MAX_K], s_flag[RQA_MAX_K];
+    const uint32_t s = blockIdx.x;
+    const uint32_t K = sds[s].K;
+    SeriesWork& w = works[s];
+    const uint64_t* h2 = h2all + (size_t)s * K * SEL_N2;
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint32_t r = threadIdx.x >> 6; r < K; r += blockDim.x >> 6) {
+        const uint64_t* h = h2 + (size_t)w.slot[r] * SEL_N2 + 8 * lane;
+        const uint64_t below = w.below[r], want = w.k[r] - below;
+        uint64_t v[8], x = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            v[i] = h[i];
+            x += v[i];
+        }
+        const uint64_t mine = x;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint64_t y = __shfl_up(x, off);
+            if (lane >= (uint32_t)off) x += y;
+        }
+        const unsigned long long hit = __ballot(x >= want);
+        // counts that do not reach the target (inconsistent) give the last bin
+        const uint32_t at = hit ? (uint32_t)__ffsll(hit) - 1u : 63u;
+        if (lane == at) {
+            uint64_t run = x - mine;
+            uint32_t c = 8 * lane + 7;
+            if (hit) {
+                bool found = false;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (!found && run + v[i] >= want) {
+                        found = true;
+                        c = 8 * lane + i;
+                    }
+                    if (!found) run += v[i];
+                }
+            } else {
+                run = x;
+                atomicOr(&w.status, 2u);
+            }
+            const uint32_t prefix = (w.prefix[r] << SEL_B2) | c;
+            w.below[r] = below + run;
+            w.prefix[r] = prefix;
+            s_pre[r] = FUSED ? prefix << SEL_B3 : prefix;
+            if (FUSED) w.rbase[r] = below + run;
+        }
+    }
+    if constexpr (FUSED) {
+        __syncthreads();
+        range_prep(w, s, K, SEL_B3, w.nonfinite == 0u, s_pre, rtab, fineK, fineL, fine_stride);
+    } else {
+        uint8_t* t2 = T2 + (size_t)s * K * SEL_N2;
+        const uint32_t n2 = w.nslots2;
+        for (uint32_t i = threadIdx.x; i < n2 * SEL_N2; i += blockDim.x) t2[i] = NO_SLOT;
+        __syncthreads();
+        const uint32_t nu = block_sort_unique(s_pre, nullptr, K, uniq, s_pos, s_flag);
+        for (uint32_t r = threadIdx.x; r < K; r += blockDim.x)
+            t2[w.slot[r] * SEL_N2 + (s_pre[r] & (SEL_N2 - 1))] = (uint8_t)s_pos[r];
+        __syncthreads();
+        for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) w.slot[r] = s_pos[r];
+        if (threadIdx.x == 0) w.nslots3 = nu;
+    }
+}
+
+hipError_t launch_select_scan(hipStream_t st, const DevBufs& b, int pass, bool fused)
+{
+    if (pass == 1)
+        hipLaunchKernelGGL(k_scan1, dim3(b.S), dim3(SEL_N1 / 4), 0, st, b.sd, b.work, b.T1, b.h1, b.nf, b.nparts);
+    else if (pass == 2)
+        hipLaunchKernelGGL((fused ? k_scan2<true> : k_scan2<false>), dim3(b.S), dim3(PREP_THREADS), 0, st, b.sd, b.work, b.T2,
+                           b.h2, b.rtab, b.fineK, b.fineL, b.fine_stride);
+    else hipLaunchKernelGGL(k_scan3, dim3(b.S, b.K), dim3(256), 0, st, b.sd, b.work, b.h3);
     return hipGetLastError();
 }
 
@@ -2481,19 +2530,35 @@ constexpr uint32_t RANGE_SCAN_THREADS = 128;
 // After the range sweep: per target, the fine counters of its range resolve
 // the last bits of eps (rank k - rbase inside the range); C = rbase + the
 // keys of the range up to eps; D = line values of rank below the target's
-// group (line ranks 0 .. 2 g) + those from the group start up to eps.
-__global__ void __launch_bounds__(RANGE_SCAN_THREADS) k_range_scan(const SeriesDesc* __restrict__ sds,
-                                                    SeriesWork* __restrict__ works,
+// group (line ranks 0 .. 2 g) + those from the group start up to eps.  Writes
+// the host's result words itself (layout at k_pack_results), so that no
+// launch and, where out is pinned host memory, no copy follows.
+__global__ void __launch_bounds__(RANGE_SCAN_THREADS) k_range_scan(const SeriesWork* __restrict__ works,
                                                     const uint64_t* __restrict__ fineK,
-                                                    const uint64_t* __restrict__ fineL, uint32_t fine_stride)
+                                                    const uint64_t* __restrict__ fineL, uint32_t fine_stride,
+                                                    uint32_t K, uint64_t* __restrict__ out)
 {
     // workgroup (series, target)
     __shared__ uint64_t pre[RANGE_SCAN_THREADS + 1];
-    __shared__ uint32_t s_c;
+    __shared__ uint32_t s_c, s_bad;
     __shared__ uint64_t s_run;
     const uint32_t s = blockIdx.x, r = blockIdx.y;
-    SeriesWork& w = works[s];
-    if (r >= sds[s].K || !w.range_ok) return;  // uniform over the workgroup
+    if (threadIdx.x == 0) s_bad = 0u;  // chunk_prefix below synchronises
+    const SeriesWork& w = works[s];
+    uint64_t* o = out + (size_t)s * result_words(K, false);
+    if (r == 0 && threadIdx.x == 0) {
+        o[0] = (uint64_t)w.status | ((uint64_t)w.nonfinite << 32);
+        o[1] = (uint64_t)w.scale | ((uint64_t)w.range_ok << 32);
+        o[2] = w.Kp;
+    }
+    if (!w.range_ok) {  // uniform over the workgroup
+        if (threadIdx.x == 0) {
+            o[3 + r] = o[3 + 2 * K + r] = o[3 + 3 * K + r] = 0;
+            o[3 + K + r] = w.k[r];
+            o[3 + 4 * K + r] = w.win_hit[r];
+        }
+        return;
+    }
     const uint32_t bits = w.range_bits, width = 1u << bits;
     const uint64_t* fk = fineK + (size_t)s * fine_stride;
     const uint64_t* fl = fineL + (size_t)s * fine_stride;
@@ -2517,7 +2582,7 @@ __global__ void __launch_bounds__(RANGE_SCAN_THREADS) k_range_scan(const SeriesD
         } else if (threadIdx.x == 0) {
             s_c = width - 1;
             s_run = pre[blockDim.x];
-            atomicOr(&w.status, 32u);
+            s_bad = 32u;
         }
     }
     __syncthreads();
@@ -2525,15 +2590,18 @@ __global__ void __launch_bounds__(RANGE_SCAN_THREADS) k_range_scan(const SeriesD
     part += strided_sum(fl, fj, fj + c + 1);
     const uint64_t cl = block_sum(part);
     if (threadIdx.x == 0) {
-        w.eps_bits[r] = w.sub_lo[j] + c;
-        w.count[r] = w.rbase[r] + s_run + fk[fj + c];
-        w.dcount[r] = cl;
+        o[3 + r] = w.sub_lo[j] + c;
+        o[3 + K + r] = w.k[r];
+        o[3 + 2 * K + r] = w.rbase[r] + s_run + fk[fj + c];
+        o[3 + 3 * K + r] = cl;
+        o[3 + 4 * K + r] = (uint64_t)w.win_hit[r] | ((uint64_t)s_bad << 32);
     }
 }
 
-hipError_t launch_range_scan(hipStream_t st, const DevBufs& b)
+hipError_t launch_range_scan(hipStream_t st, const DevBufs& b, uint64_t* out)
 {
-    hipLaunchKernelGGL(k_range_scan, dim3(b.S, b.K), dim3(RANGE_SCAN_THREADS), 0, st, b.sd, b.work, b.fineK, b.fineL, b.fine_stride);
+    hipLaunchKernelGGL(k_range_scan, dim3(b.S, b.K), dim3(RANGE_SCAN_THREADS), 0, st, b.work, b.fineK, b.fineL, b.fine_stride,
+                       b.K, out);
     return hipGetLastError();
 }
 
@@ -2822,20 +2890,21 @@ int window_blocks_per_cu(int pass, int variant, uint32_t block)
 }
 
 // After window pass 1: per target, hit if its rank falls inside the window;
-// its fine bin and the count below that bin; pass-2 slots and table.
+// its fine bin and the count below that bin; then the range sweep's set-up
+// (fused), or pass-2 slots and table.
 __global__ void __launch_bounds__(1024) k_window_scan1(const SeriesDesc* __restrict__ sds, SeriesWork* __restrict__ works,
                                                        uint64_t* __restrict__ bins, uint8_t* __restrict__ table,
-                                                       uint64_t* __restrict__ fine, uint32_t clear_fine)
+                                                       uint64_t* __restrict__ fine, uint32_t fused,
+                                                       uint2* __restrict__ rtab, uint64_t* __restrict__ fineK,
+                                                       uint64_t* __restrict__ fineL, uint32_t fine_stride)
 {
     // up to 1024 threads (each then sums 39 of the 39,936 fine bins)
     __shared__ uint64_t pre[1025];
     __shared__ uint32_t uniq[RQA_MAX_K], s_pos[RQA_MAX_K], s_flag[RQA_MAX_K];
-    __shared__ uint32_t s_hit[RQA_MAX_K], s_fbin[RQA_MAX_K];
+    __shared__ uint32_t s_hit[RQA_MAX_K], s_fbin[RQA_MAX_K], s_addr[RQA_MAX_K];
     const uint32_t s = blockIdx.x;
     const uint32_t K = sds[s].K;
     SeriesWork& w = works[s];
-    uint8_t* tb = table + (size_t)s * WIN_BINS;
-    for (uint32_t i = threadIdx.x; i < WIN_BINS; i += blockDim.x) tb[i] = NO_SLOT;
     const bool ok = w.win_ok != 0;
     const uint64_t below = w.win_below;
     const uint64_t* cb = bins + (size_t)s * WIN_BINS;
@@ -2856,8 +2925,22 @@ __global__ void __launch_bounds__(1024) k_window_scan1(const SeriesDesc* __restr
                 w.win_fbin[r] = fb;
                 w.win_base[r] = below + before;
             }
+            if (fused) {
+                w.rbase[r] = below + before;
+                s_addr[r] = w.win_lo + (fb << w.win_shift);
+            }
         }
     }
+    if (fused) {  // uniform over the launch
+        __syncthreads();
+        const bool miss = __syncthreads_or(threadIdx.x < K && s_hit[threadIdx.x] == 0u);
+        // series with a NaN or infinite sample end in an error; a series with
+        // a target outside its window is selected again
+        range_prep(w, s, K, w.win_shift, w.nonfinite == 0u && ok && !miss, s_addr, rtab, fineK, fineL, fine_stride);
+        return;
+    }
+    uint8_t* tb = table + (size_t)s * WIN_BINS;
+    for (uint32_t i = threadIdx.x; i < WIN_BINS; i += blockDim.x) tb[i] = NO_SLOT;
     __syncthreads();
     const uint32_t nu = block_sort_unique(s_fbin, s_hit, K, uniq, s_pos, s_flag);
     for (uint32_t r = threadIdx.x; r < K; r += blockDim.x)
@@ -2866,12 +2949,10 @@ __global__ void __launch_bounds__(1024) k_window_scan1(const SeriesDesc* __restr
     for (uint32_t u = threadIdx.x; u < nu; u += blockDim.x) tb[uniq[u]] = (uint8_t)u;
     if (threadIdx.x == 0) w.win_nslots = nu;
     // clear the sub-bins window pass 2 will count into
-    if (clear_fine) {
-        const uint32_t nsub = 1u << w.win_shift;
-        uint64_t* f = fine + (size_t)s * K * (1u << WIN_MAX_SHIFT);
-        for (uint32_t u = 0; u < nu; ++u)
-            for (uint32_t i = threadIdx.x; i < nsub; i += blockDim.x) f[(size_t)u * (1u << WIN_MAX_SHIFT) + i] = 0;
-    }
+    const uint32_t nsub = 1u << w.win_shift;
+    uint64_t* f = fine + (size_t)s * K * (1u << WIN_MAX_SHIFT);
+    for (uint32_t u = 0; u < nu; ++u)
+        for (uint32_t i = threadIdx.x; i < nsub; i += blockDim.x) f[(size_t)u * (1u << WIN_MAX_SHIFT) + i] = 0;
 }
 
 // After window pass 2: the sub-bin of each hit target gives its threshold;
@@ -2906,13 +2987,11 @@ __global__ void __launch_bounds__(256) k_window_scan2(const SeriesDesc* __restri
 
 hipError_t launch_window_scan(hipStream_t st, const DevBufs& b, const WinBufs& w, int pass)
 {
-    // scan 1 clears the fine counters of window pass 2 unless the range sweep
-    // (which clears its own) follows
     if (pass == 1)
         // few series: 1024 threads share each series' bins; many: 256, so
         // that several series' workgroups share a CU
         hipLaunchKernelGGL(k_window_scan1, dim3(b.S), dim3(b.S <= 128 ? 1024 : 256), 0, st, b.sd, b.work, w.bins, w.table, w.fine,
-                           w.fine ? 1u : 0u);
+                           w.fine ? 0u : 1u, b.rtab, b.fineK, b.fineL, b.fine_stride);
     else hipLaunchKernelGGL(k_window_scan2, dim3(b.S, b.K), dim3(256), 0, st, b.sd, b.work, w.fine);
     return hipGetLastError();
 }
@@ -2935,7 +3014,8 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t s)
 // clamped to SKETCH_BINS quarter-binade bins.
 constexpr uint32_t SKETCH_THREADS = 1024;
 __global__ void __launch_bounds__(SKETCH_THREADS) k_sketch(const SeriesDesc* __restrict__ sds, SeriesWork* __restrict__ works,
-                                                float* __restrict__ features, uint32_t* __restrict__ sample_sorted)
+                                                float* __restrict__ features, uint32_t* __restrict__ sample_sorted,
+                                                const uint32_t* __restrict__ nf, uint32_t nparts)
 {
     __shared__ uint32_t keys[SKETCH_P];
     __shared__ uint32_t keys2[SKETCH_P];
@@ -2945,6 +3025,8 @@ __global__ void __launch_bounds__(SKETCH_THREADS) k_sketch(const SeriesDesc* __r
     const uint64_t M = sd.M;
     const uint64_t L0 = (uint64_t)sd.nv - sd.w;
     for (uint32_t i = threadIdx.x; i < SKETCH_BINS; i += blockDim.x) hist[i] = 0u;
+    const bool bad = block_nonfinite(nf, nparts, s);
+    if (threadIdx.x == 0) works[s].nonfinite = bad ? 1u : 0u;
     for (uint32_t q = threadIdx.x; q < (uint32_t)SKETCH_P; q += blockDim.x) {
         const uint64_t p = splitmix64(sd.seed, q) % M;
         // diagonal offset dl: the largest with C(dl) = dl*L0 - dl(dl-1)/2 <= p
@@ -3036,7 +3118,8 @@ __global__ void __launch_bounds__(SKETCH_THREADS) k_sketch(const SeriesDesc* __r
 hipError_t launch_sketch(hipStream_t st, const DevBufs& b, float* features, uint32_t* sample_sorted)
 {
     // 1024 threads: four sample keys per thread through the 78 bitonic stages
-    hipLaunchKernelGGL(k_sketch, dim3(b.S), dim3(SKETCH_THREADS), 0, st, b.sd, b.work, features, sample_sorted);
+    hipLaunchKernelGGL(k_sketch, dim3(b.S), dim3(SKETCH_THREADS), 0, st, b.sd, b.work, features, sample_sorted, b.nf,
+                       b.nparts);
     return hipGetLastError();
 }
 
