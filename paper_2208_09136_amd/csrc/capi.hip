@@ -498,6 +498,15 @@ rqa_status run_job(rqa_ctx* c, Job& job)
     const size_t o_h1 = radix ? carve(sizeof(uint64_t) * S * SEL_N1) : 0;
     const size_t o_h2 = radix ? carve(sizeof(uint64_t) * S * K * SEL_N2) : 0;
     const size_t o_h3 = radix && !fused ? carve(sizeof(uint64_t) * S * K * SEL_N3) : 0;
+    // range sweep: fine counters of keys and line values; after a window only
+    // the ranges in use are cleared, by the scan that finds them
+    const uint32_t fine_stride = fused ? K << (window ? WIN_MAX_SHIFT : (uint32_t)SEL_B3) : 0;
+    size_t o_fineK = 0, o_fineL = 0;
+    auto carve_fine = [&] {
+        o_fineK = carve(sizeof(uint64_t) * S * fine_stride);
+        o_fineL = carve(sizeof(uint64_t) * S * fine_stride);
+    };
+    if (fused && !window) carve_fine();
     const size_t o_wbins = window ? carve(sizeof(uint64_t) * S * WIN_BINS) : 0;
     const size_t hist_words = hist ? (size_t)S * job.hist_len * (job.hist_kp + 1) : 0;
     const size_t o_dh = hist ? carve(sizeof(uint64_t) * hist_words) : 0;
@@ -510,6 +519,7 @@ rqa_status run_job(rqa_ctx* c, Job& job)
     }
     const size_t run_words = hist ? hist_tiles * (job.hist_kp + 1) * TILE_W : 0;
     const size_t zero_end = off;
+    if (fused && window) carve_fine();
     const size_t o_pre = hist ? carve(sizeof(uint16_t) * run_words) : 0;
     const size_t o_suf = hist ? carve(sizeof(uint16_t) * run_words) : 0;
     // histogram rows: every entry written by the finishing kernel
@@ -523,10 +533,6 @@ rqa_status run_job(rqa_ctx* c, Job& job)
     const size_t o_smp = keep_sample ? carve(sizeof(uint32_t) * S * SKETCH_P) : 0;
     const size_t o_wtab = window ? carve((size_t)S * WIN_BINS) : 0;
     const size_t o_wfine = window && !fused ? carve(sizeof(uint64_t) * S * K * (1u << WIN_MAX_SHIFT)) : 0;
-    // range sweep: fine counters of keys and line values, cleared by the set-up kernel
-    const uint32_t fine_stride = fused ? K << (window ? WIN_MAX_SHIFT : (uint32_t)SEL_B3) : 0;
-    const size_t o_fineK = fused ? carve(sizeof(uint64_t) * S * fine_stride) : 0;
-    const size_t o_fineL = fused ? carve(sizeof(uint64_t) * S * fine_stride) : 0;
     const size_t o_pred = window ? carve(sizeof(float) * S * MLP_OUT) : 0;
     const size_t o_delta = window ? carve(sizeof(float) * MLP_OUT) : 0;
     if (window && window_lds_bytes(1) > c->max_lds)

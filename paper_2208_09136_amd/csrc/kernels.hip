@@ -1041,29 +1041,39 @@ __device__ __forceinline__ uint32_t first_reaching(const uint64_t* cum, uint32_t
 // The distinct values of v[0..n) in ascending order, written to out[] (which
 // must not overlap v), over the entries with keep[i] != 0 (all entries when
 // keep is null); pos[i] = the position of v[i] among them, for kept entries.
-// flag is LDS scratch of n words.  One entry per thread, in parallel (a
-// serial sort on one thread waits on an LDS round trip per step), so n is at
-// most RQA_MAX_K and every caller runs at least that many threads.  Called by
-// the whole block; synchronises it.  Returns the number of distinct values.
-static_assert(RQA_MAX_K <= 256, "the set-up kernels give every target a thread of 256");
-__device__ uint32_t block_sort_unique(const uint32_t* v, const uint32_t* keep, uint32_t n, uint32_t* out,
-                                      uint32_t* pos, uint32_t* flag)
+// All threads share the n^2 comparisons (thread t: entry t mod 128 with its
+// share of the others): with a thread per entry, each comparison waited for an
+// LDS round trip, 4 us at n = 20 and 13 us at n = 100.  n is at most RQA_MAX_K.
+// Called by the whole block (a multiple of 128 threads), after a barrier behind
+// the writes of v and keep; synchronises it.  Returns the number of distinct
+// values.
+static_assert(RQA_MAX_K <= 128, "an entry per thread of 128");
+__device__ uint32_t block_sort_unique(const uint32_t* v, const uint32_t* keep, uint32_t n, uint32_t* out, uint32_t* pos)
 {
-    const uint32_t i = threadIdx.x;
+    __shared__ uint32_t s_out[128], s_below[128];  // not the first of its value (or not kept); distinct values below
+    const uint32_t i = threadIdx.x & 127u, part = threadIdx.x >> 7, parts = blockDim.x >> 7;
     const bool mine = i < n && (keep == nullptr || keep[i] != 0u);
     const uint32_t x = mine ? v[i] : 0u;
+    if (part == 0) {
+        s_out[i] = mine ? 0u : 1u;
+        s_below[i] = 0u;
+    }
+    __syncthreads();
     // the first kept entry of each value stands for it
-    bool first = mine;
-    if (mine)
-        for (uint32_t j = 0; j < i; ++j)
-            if ((keep == nullptr || keep[j] != 0u) && v[j] == x) first = false;
-    if (i < n) flag[i] = first ? 1u : 0u;
+    bool dup = false;
+#pragma unroll 4
+    for (uint32_t j = part; j < n; j += parts) dup |= j < i && v[j] == x && (keep == nullptr || keep[j] != 0u);
+    if (mine && dup) s_out[i] = 1u;
+    __syncthreads();
+    uint32_t below = 0;
+#pragma unroll 4
+    for (uint32_t j = part; j < n; j += parts) below += s_out[j] == 0u && v[j] < x ? 1u : 0u;
+    if (mine && below) atomicAdd(&s_below[i], below);
+    const bool first = part == 0 && s_out[i] == 0u;
     const uint32_t nu = (uint32_t)__syncthreads_count(first);
-    if (mine) {
-        uint32_t p = 0;
-        for (uint32_t j = 0; j < n; ++j) p += (flag[j] != 0u && v[j] < x) ? 1u : 0u;
-        pos[i] = p;
-        if (first) out[p] = x;
+    if (part == 0 && mine) {
+        pos[i] = s_below[i];
+        if (first) out[s_below[i]] = x;
     }
     __syncthreads();
     return nu;
@@ -1077,7 +1087,7 @@ __global__ void __launch_bounds__(SEL_N1 / 4) k_scan1(const SeriesDesc* __restri
                                                       const uint32_t* __restrict__ nf, uint32_t nparts)
 {
     __shared__ uint64_t cum[SEL_N1];
-    __shared__ uint32_t s_pre[RQA_MAX_K], uniq[RQA_MAX_K], s_pos[RQA_MAX_K], s_flag[RQA_MAX_K];
+    __shared__ uint32_t s_pre[RQA_MAX_K], uniq[RQA_MAX_K], s_pos[RQA_MAX_K];
     const uint32_t s = blockIdx.x;
     const uint32_t K = sds[s].K;
     SeriesWork& w = works[s];
@@ -1102,7 +1112,7 @@ __global__ void __launch_bounds__(SEL_N1 / 4) k_scan1(const SeriesDesc* __restri
         s_pre[r] = b;
     }
     __syncthreads();
-    const uint32_t nu = block_sort_unique(s_pre, nullptr, K, uniq, s_pos, s_flag);
+    const uint32_t nu = block_sort_unique(s_pre, nullptr, K, uniq, s_pos);
     if (r < K) w.slot[r] = s_pos[r];
     if (r < nu) T1[(size_t)s * SEL_N1 + uniq[r]] = (uint8_t)r;
     if (r == 0) {
@@ -1862,7 +1872,7 @@ __global__ void __launch_bounds__(PREP_THREADS) k_sweep_prep(const SeriesDesc* _
                                                     SeriesWork* __restrict__ works, uint2* __restrict__ rtab,
                                                     const uint32_t* __restrict__ nf, uint32_t nparts)
 {
-    __shared__ uint32_t s_eps[RQA_MAX_K], es[RQA_MAX_K], s_pos[RQA_MAX_K], s_flag[RQA_MAX_K];
+    __shared__ uint32_t s_eps[RQA_MAX_K], es[RQA_MAX_K], s_pos[RQA_MAX_K];
     __shared__ uint32_t s_shift;
     const uint32_t s = blockIdx.x;
     const uint32_t K = sds[s].K;
@@ -1870,7 +1880,7 @@ __global__ void __launch_bounds__(PREP_THREADS) k_sweep_prep(const SeriesDesc* _
     for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) s_eps[r] = w.eps_bits[r];
     const bool bad = block_nonfinite(nf, nparts, s);
     if (threadIdx.x == 0) w.nonfinite = bad ? 1u : 0u;
-    const uint32_t kp = block_sort_unique(s_eps, nullptr, K, es, s_pos, s_flag);
+    const uint32_t kp = block_sort_unique(s_eps, nullptr, K, es, s_pos);
     for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) w.dmap[r] = s_pos[r];
     build_rank_table(w, es, kp, rtab + (size_t)s * RHO_TABLE, &s_shift);
 }
@@ -2274,65 +2284,67 @@ int hist_blocks_per_cu(int select_variant, uint32_t Kp, uint32_t block)
 // the end gend[], ascending and disjoint, in LDS; see CodeCtx): the smallest
 // shift for which the buckets of all groups and one on either side fit
 // CODE_TABLE; bucket a (mod CODE_TABLE) at byte a.  Called by a whole block.
-__device__ void build_code_table(SeriesWork& w, const uint32_t* glo, const uint64_t* gend, uint32_t ng, uint32_t* tab,
-                                 uint32_t* s_shift)
+// A thread takes 32 buckets at a time: one search for the first group that ends
+// at or above them tells whether all have one code, which all but the few that
+// hold a group's start or end do; those are filled bucket by bucket (every
+// bucket searched for or walked to took 9 us of the one workgroup's time).
+__device__ void build_code_table(SeriesWork& w, const uint32_t* glo, const uint64_t* gend, uint32_t ng, uint32_t* tab)
 {
+    __shared__ uint32_t s_first[RQA_MAX_K], s_last[RQA_MAX_K];  // groups' first and last buckets
     const uint32_t last = (uint32_t)min(gend[ng - 1] - 1ull, (uint64_t)0x7F800000u);  // keys never exceed +inf
+    uint32_t sh = 0;
+    // 32 more than the buckets in use: the table starts at a multiple of 32
+    while ((last >> sh) - (glo[0] >> sh) + 3u + 32u > CODE_TABLE) ++sh;
+    const uint32_t a0 = glo[0] >> sh;
     if (threadIdx.x == 0) {
-        uint32_t sh = 0;
-        while ((last >> sh) - (glo[0] >> sh) + 3u > CODE_TABLE) ++sh;
-        *s_shift = sh;
         // clamp bounds in the buckets next to the groups: a key of such a
         // bucket has an even code, also where a group shares its bucket with
         // keys outside
-        const uint32_t a0 = glo[0] >> sh, a1 = last >> sh;
         w.emin = a0 ? (a0 << sh) - 1u : 0u;
-        w.emax = (uint32_t)min((uint64_t)(a1 + 1u) << sh, (uint64_t)0x7F800000u);
+        w.emax = (uint32_t)min((uint64_t)((last >> sh) + 1u) << sh, (uint64_t)0x7F800000u);
         w.shift = sh;
         w.Kp = 2u * ng;
     }
-    __syncthreads();
-    const uint32_t sh = *s_shift;
+    if (threadIdx.x < ng) {
+        s_first[threadIdx.x] = glo[threadIdx.x] >> sh;
+        s_last[threadIdx.x] = (uint32_t)((gend[threadIdx.x] - 1ull) >> sh);
+    }
     for (uint32_t i = threadIdx.x; i < RANK_MAX + 2; i += blockDim.x) { w.hrho[i] = 0; w.hlam[i] = 0; }
-    const uint32_t a0 = glo[0] >> sh;
-    const uint32_t aL = a0 ? a0 - 1u : 0u;
-    // 32 buckets per thread and step: one search, then a walk along the groups
+    __syncthreads();
+    const uint32_t base = (a0 ? a0 - 1u : 0u) & ~31u;
     for (uint32_t i0 = 32u * threadIdx.x; i0 < CODE_TABLE; i0 += 32u * blockDim.x) {
-        uint32_t g = 0, prev = 0;
-        uint64_t gl = 0, ge = 0;  // group g: its start and end (no key reaches group ng)
-        uint32_t out[8];
+        const uint32_t a = base + ((i0 - base) & (CODE_TABLE - 1u));
+        uint32_t g = 0, e = ng;  // first group whose last bucket is a or above
+        while (g < e) {
+            const uint32_t mid = (g + e) >> 1;
+            if (s_last[mid] < a) g = mid + 1; else e = mid;
+        }
+        uint32_t b0 = g < ng ? s_first[g] : 0xFFFFFFFFu, b1 = g < ng ? s_last[g] : 0xFFFFFFFFu;
+        uint32_t v[8];
+        if (b0 > a + 31u || (b0 <= a && b1 >= a + 31u)) {
+            const uint32_t c = (2u * g + (b0 <= a ? 1u : 0u)) * 0x01010101u;
 #pragma unroll
-        for (uint32_t v = 0; v < 8; ++v) {
-            uint32_t packed = 0;
+            for (uint32_t q = 0; q < 8; ++q) v[q] = c;
+        } else {
 #pragma unroll
-            for (uint32_t i = 0; i < 4; ++i) {
-                const uint32_t a = aL + ((i0 + 4u * v + i - aL) & (CODE_TABLE - 1u));
-                const uint64_t lo = (uint64_t)a << sh, hi = (uint64_t)(a + 1u) << sh;
-                if (v + i == 0 || a != prev + 1u) {
-                    // first group that ends above the bucket's start
-                    uint32_t b = 0, e = ng;
-                    while (b < e) {
-                        const uint32_t mid = (b + e) >> 1;
-                        if (gend[mid] <= lo) b = mid + 1; else e = mid;
-                    }
-                    g = b;
-                    gl = g < ng ? glo[g] : ~0ull;
-                    ge = g < ng ? gend[g] : ~0ull;
-                } else {
-                    while (ge <= lo) {
+            for (uint32_t q = 0; q < 8; ++q) {
+                uint32_t packed = 0;
+#pragma unroll
+                for (uint32_t i = 0; i < 4; ++i) {
+                    const uint32_t at = a + 4u * q + i;
+                    while (b1 < at) {
                         ++g;
-                        gl = g < ng ? glo[g] : ~0ull;
-                        ge = g < ng ? gend[g] : ~0ull;
+                        b0 = g < ng ? s_first[g] : 0xFFFFFFFFu;
+                        b1 = g < ng ? s_last[g] : 0xFFFFFFFFu;
                     }
+                    packed |= (2u * g + (b0 <= at ? 1u : 0u)) << (8u * i);
                 }
-                prev = a;
-                packed |= (2u * g + (gl < hi ? 1u : 0u)) << (8u * i);
+                v[q] = packed;
             }
-            out[v] = packed;
         }
         uint4* dst = (uint4*)tab + i0 / 16u;
-        dst[0] = make_uint4(out[0], out[1], out[2], out[3]);
-        dst[1] = make_uint4(out[4], out[5], out[6], out[7]);
+        dst[0] = make_uint4(v[0], v[1], v[2], v[3]);
+        dst[1] = make_uint4(v[4], v[5], v[6], v[7]);
     }
 }
 
@@ -2341,38 +2353,39 @@ __device__ void build_code_table(SeriesWork& w, const uint32_t* glo, const uint6
 // range of 2^bits bit patterns starting at s_addr[r] (LDS), with w.rbase[r]
 // keys below it; ok: the series takes part (no NaN or infinite sample, and no
 // target outside its window).  Distinct ranges are sorted, adjacent ones merge
-// into groups, and the code table is built over the groups; the fine counters
-// of the ranges are cleared.  Called by a whole block of at least RQA_MAX_K
+// into groups, and the code table is built over the groups; clear: the fine
+// counters of the ranges are cleared.  Called by a whole block of at least RQA_MAX_K
 // threads, after a barrier behind the writes of s_addr.
 __device__ void range_prep(SeriesWork& w, uint32_t s, uint32_t K, uint32_t bits, bool ok, const uint32_t* s_addr,
                            uint2* __restrict__ rtab, uint64_t* __restrict__ fineK, uint64_t* __restrict__ fineL,
-                           uint32_t fine_stride)
+                           uint32_t fine_stride, bool clear)
 {
     __shared__ uint64_t s_gend[RQA_MAX_K];
     __shared__ uint32_t sub[RQA_MAX_K];
     // the group arrays in LDS, worked on by one thread per target or range
     // (serially, each step would wait on a round trip to memory or LDS)
     __shared__ uint32_t s_tsub[RQA_MAX_K], s_tgroup[RQA_MAX_K];
-    __shared__ uint32_t s_flag[RQA_MAX_K], s_gid[RQA_MAX_K];
+    __shared__ uint32_t s_starts[2], s_gid[RQA_MAX_K];
     __shared__ uint32_t s_glo[RQA_MAX_K + 1], s_goff[RQA_MAX_K + 1];
-    __shared__ uint32_t s_shift;
     uint32_t ns = 0, ng = 0;
     if (ok) {
-        ns = block_sort_unique(s_addr, nullptr, K, sub, s_tsub, s_flag);
+        ns = block_sort_unique(s_addr, nullptr, K, sub, s_tsub);
         // groups of adjacent ranges: a range starts a group unless it follows
         // the one before it directly
         const uint64_t width = 1ull << bits;
         const uint32_t j = threadIdx.x;
         const bool start = j < ns && (j == 0 || (uint64_t)sub[j] != (uint64_t)sub[j - 1] + width);
-        if (j < ns) s_flag[j] = start ? 1u : 0u;
+        // group of a range: the starts up to it (two waves hold all ranges)
+        const uint64_t starts = __ballot(start);
+        if (j < 128 && (j & 63u) == 0) s_starts[j >> 6] = (uint32_t)__popcll(starts);
         ng = (uint32_t)__syncthreads_count(start);
         if (j < ns) {
-            uint32_t gi = 0;  // starts after the first one, up to j
-            for (uint32_t i = 1; i <= j; ++i) gi += s_flag[i];
-            s_gid[j] = gi;
+            const uint32_t before = (j < 64 ? 0u : s_starts[0]) +
+                                    (uint32_t)__popcll(starts & (~0ull >> (63u - (j & 63u)))) - 1u;
+            s_gid[j] = before;
             if (start) {
-                s_glo[gi] = sub[j];
-                s_goff[gi] = j << bits;
+                s_glo[before] = sub[j];
+                s_goff[before] = j << bits;
             }
         }
         __syncthreads();
@@ -2406,16 +2419,18 @@ __device__ void range_prep(SeriesWork& w, uint32_t s, uint32_t K, uint32_t bits,
         w.g_lo[g] = s_glo[g];
         w.g_off[g] = s_goff[g];
     }
-    // clear the fine counters of the ranges (two per 16-byte store: a range
-    // holds at least four)
-    const uint32_t nfine = ns << bits;
-    uint4* fk = (uint4*)(fineK + (size_t)s * fine_stride);
-    uint4* fl = (uint4*)(fineL + (size_t)s * fine_stride);
-    for (uint32_t i = threadIdx.x; i < nfine / 2; i += blockDim.x) {
-        fk[i] = make_uint4(0u, 0u, 0u, 0u);
-        fl[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (clear) {
+        // clear the fine counters of the ranges (two per 16-byte store: a
+        // range holds at least four)
+        const uint32_t nfine = ns << bits;
+        uint4* fk = (uint4*)(fineK + (size_t)s * fine_stride);
+        uint4* fl = (uint4*)(fineL + (size_t)s * fine_stride);
+        for (uint32_t i = threadIdx.x; i < nfine / 2; i += blockDim.x) {
+            fk[i] = make_uint4(0u, 0u, 0u, 0u);
+            fl[i] = make_uint4(0u, 0u, 0u, 0u);
+        }
     }
-    build_code_table(w, s_glo, s_gend, ng, (uint32_t*)(rtab + (size_t)s * RHO_TABLE), &s_shift);
+    build_code_table(w, s_glo, s_gend, ng, (uint32_t*)(rtab + (size_t)s * RHO_TABLE));
 }
 
 // After pass 2: resolve SEL_B2 more bits per target, a wave per target (each
@@ -2429,7 +2444,7 @@ __global__ void __launch_bounds__(PREP_THREADS) k_scan2(const SeriesDesc* __rest
                                                         uint64_t* __restrict__ fineL, uint32_t fine_stride)
 {
     static_assert(SEL_N2 == 64 * 8, "a wave takes a row of pass-2 bins, eight per lane");
-    __shared__ uint32_t s_pre[RQA_MAX_K], uniq[RQA_MAX_K], s_pos[RQA_MAX_K], s_flag[RQA_MAX_K];
+    __shared__ uint32_t s_pre[RQA_MAX_K], uniq[RQA_MAX_K], s_pos[RQA_MAX_K];
     const uint32_t s = blockIdx.x;
     const uint32_t K = sds[s].K;
     SeriesWork& w = works[s];
@@ -2479,13 +2494,14 @@ __global__ void __launch_bounds__(PREP_THREADS) k_scan2(const SeriesDesc* __rest
     }
     if constexpr (FUSED) {
         __syncthreads();
-        range_prep(w, s, K, SEL_B3, w.nonfinite == 0u, s_pre, rtab, fineK, fineL, fine_stride);
+        // the set-up kernel cleared the fine counters
+        range_prep(w, s, K, SEL_B3, w.nonfinite == 0u, s_pre, rtab, fineK, fineL, fine_stride, false);
     } else {
         uint8_t* t2 = T2 + (size_t)s * K * SEL_N2;
         const uint32_t n2 = w.nslots2;
         for (uint32_t i = threadIdx.x; i < n2 * SEL_N2; i += blockDim.x) t2[i] = NO_SLOT;
         __syncthreads();
-        const uint32_t nu = block_sort_unique(s_pre, nullptr, K, uniq, s_pos, s_flag);
+        const uint32_t nu = block_sort_unique(s_pre, nullptr, K, uniq, s_pos);
         for (uint32_t r = threadIdx.x; r < K; r += blockDim.x)
             t2[w.slot[r] * SEL_N2 + (s_pre[r] & (SEL_N2 - 1))] = (uint8_t)s_pos[r];
         __syncthreads();
@@ -2900,7 +2916,7 @@ __global__ void __launch_bounds__(1024) k_window_scan1(const SeriesDesc* __restr
 {
     // up to 1024 threads (each then sums 39 of the 39,936 fine bins)
     __shared__ uint64_t pre[1025];
-    __shared__ uint32_t uniq[RQA_MAX_K], s_pos[RQA_MAX_K], s_flag[RQA_MAX_K];
+    __shared__ uint32_t uniq[RQA_MAX_K], s_pos[RQA_MAX_K];
     __shared__ uint32_t s_hit[RQA_MAX_K], s_fbin[RQA_MAX_K], s_addr[RQA_MAX_K];
     const uint32_t s = blockIdx.x;
     const uint32_t K = sds[s].K;
@@ -2936,13 +2952,13 @@ __global__ void __launch_bounds__(1024) k_window_scan1(const SeriesDesc* __restr
         const bool miss = __syncthreads_or(threadIdx.x < K && s_hit[threadIdx.x] == 0u);
         // series with a NaN or infinite sample end in an error; a series with
         // a target outside its window is selected again
-        range_prep(w, s, K, w.win_shift, w.nonfinite == 0u && ok && !miss, s_addr, rtab, fineK, fineL, fine_stride);
+        range_prep(w, s, K, w.win_shift, w.nonfinite == 0u && ok && !miss, s_addr, rtab, fineK, fineL, fine_stride, true);
         return;
     }
     uint8_t* tb = table + (size_t)s * WIN_BINS;
     for (uint32_t i = threadIdx.x; i < WIN_BINS; i += blockDim.x) tb[i] = NO_SLOT;
     __syncthreads();
-    const uint32_t nu = block_sort_unique(s_fbin, s_hit, K, uniq, s_pos, s_flag);
+    const uint32_t nu = block_sort_unique(s_fbin, s_hit, K, uniq, s_pos);
     for (uint32_t r = threadIdx.x; r < K; r += blockDim.x)
         w.win_slot[r] = s_hit[r] ? s_pos[r] : (uint32_t)NO_SLOT;
     __syncthreads();
