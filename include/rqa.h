@@ -231,8 +231,8 @@ rqa_status rqa_set_timing(rqa_ctx *ctx, int enable);
 /* Kernel launch shape overrides for later calls on this context: segment
  * length along a diagonal (a multiple of 64, at most 65536) and tiles per
  * work chunk (at most 4096).  0 selects automatic: the autotuned table of the
- * context where it has the size bucket, otherwise about 16 segments per
- * series (64..1024) and 8 tiles per chunk.  Shapes never change results. */
+ * context where it has the size bucket, otherwise segments (64..1024) and
+ * chunks by the work of the whole call.  Shapes never change results. */
 rqa_status rqa_set_shape(rqa_ctx *ctx, uint32_t segment, uint32_t chunk_tiles);
 
 /* Launch-shape autotuner (batched persistent launch of the workload

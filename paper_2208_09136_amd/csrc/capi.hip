@@ -208,23 +208,35 @@ TuneKey tune_key(uint64_t nv, const rqa_params& p, uint32_t K)
     return {log2_floor(nv), variant_of(p.norm, p.m, p.tau, p.lmin), K <= 32 ? 0 : 1};
 }
 
-// Default segment length when nothing is tuned: about 16 segments per series,
-// a power of two between 64 and 1024.
-uint32_t default_segment(uint64_t L0)
+// Default segment length when nothing is tuned, from the work of the whole call
+// (pairs over all series) per wave of one 8-wave workgroup on every CU: a call
+// with up to 512 steps for each gives each one tile, so that no CU waits for a
+// second round of short tiles; a larger one about six, of 256 to 1024 steps.
+// Measured (us per call, K = 20, m = 1 unless said): one N = 1e4 series
+// (381 steps) T = 128 / 256 / 512 / 1024: 233 / 181 / 175 / 231; twenty
+// N = 3000 (686): 128 / 256 / 512: 339 / 289 / 326; N = 30,000 (3433): 128 /
+// 512 / 1024: 549 / 510 / 547; the 600-series ensemble (87,000): 128 / 512 /
+// 960: 6663 / 6331 / 5796.  From the walker's unit on (the two half-blocks of
+// its ring and 64: 320 for m = 3, tau = 5, 192 for tau = 3, 64 else) a multiple
+// of it, so that no segment ends with a part of a half-block, which takes the
+// walker's edge path (two N = 1e5 series, tau = 5: 512 / 640: 5337 / 4787).
+uint32_t default_segment(uint64_t pairs, int num_cu, const rqa_params& p)
 {
-    uint64_t t = 64;
-    while (t * 2 <= L0 / 16 && t < 1024) t *= 2;
-    return (uint32_t)t;
+    const uint64_t steps = pairs / TILE_W / ((uint64_t)num_cu * 8);
+    const uint64_t t = steps <= 512 ? std::max<uint64_t>(steps, 64) : std::min<uint64_t>(std::max<uint64_t>(steps / 6, 256), 1024);
+    const int cls = select_variant_of(p.norm, p.m, p.tau) % NUM_MCLASS;
+    const uint64_t unit = cls == 3 ? 320 : cls == 2 ? 192 : 64;
+    return (uint32_t)(t >= unit ? t / unit * unit : t / 64 * 64);
 }
 
 constexpr uint32_t DEFAULT_CHUNK = 8;
 
-uint32_t segment_for(const rqa_ctx* c, uint64_t nv, const rqa_params& p, uint32_t K)
+uint32_t segment_for(const rqa_ctx* c, uint64_t nv, const rqa_params& p, uint32_t K, uint64_t pairs)
 {
     if (c->seg) return c->seg;
     auto it = c->tune.find(tune_key(nv, p, K));
     if (it != c->tune.end()) return it->second.seg;
-    return default_segment(nv - p.theiler);
+    return default_segment(pairs, c->num_cu, p);
 }
 
 // The threshold sweep runs 1024-thread workgroups when its LDS (rank table,
@@ -248,7 +260,7 @@ uint32_t chunk_for(const rqa_ctx* c, uint32_t S, uint64_t nv0, const rqa_params&
     const TuneKey key = S == 1 ? tune_key(nv0, p0, K) : TuneKey{-1, 0, K <= 32 ? 0 : 1};
     auto it = c->tune.find(key);
     if (it != c->tune.end()) return it->second.chunk;
-    return DEFAULT_CHUNK;
+    return 0;  // automatic
 }
 
 // Largest number of series whose descriptors, targets and results the kernels
@@ -382,10 +394,13 @@ rqa_status run_job(rqa_ctx* c, Job& job)
             }
         if (!hist_block) return fail(RQA_ERR_UNSUPPORTED, "the histogram pass does not fit in LDS");
     }
-    uint32_t CT;
+    uint32_t CT;  // tiles per chunk; automatic: the fewest
+    bool auto_chunks;
     {
         const Series& z0 = job.series[0];
         CT = hist ? hist_block / TILE_W : chunk_for(c, S, z0.n - (uint64_t)(z0.p.m - 1) * z0.p.tau, z0.p, K);
+        auto_chunks = CT == 0;
+        if (auto_chunks) CT = DEFAULT_CHUNK;
         // the wide threshold sweep needs a tile per wave of its 1024-thread workgroups
         if ((job.mode & MODE_SWEEP) && !((job.mode & MODE_SELECT) && (job.mode & MODE_LINES)) && wide_sweep(c, K))
             CT = std::max<uint32_t>(CT, 1024 / TILE_W);
@@ -416,6 +431,8 @@ rqa_status run_job(rqa_ctx* c, Job& job)
     struct Group { uint32_t begin, end; int sel, swp; uint32_t nchunks; };
     const bool fused = (job.mode & MODE_SELECT) && (job.mode & MODE_LINES);
     std::vector<Group> groups;
+    uint64_t pairs = 0;
+    for (uint64_t m : job.M) pairs += m;
     uint32_t maxn = 0;
     for (uint32_t i = 0; i < S; ++i) {
         const uint32_t s = order[i];
@@ -428,7 +445,7 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         const uint64_t nv = z.n - (uint64_t)(z.p.m - 1) * z.p.tau;
         const uint64_t L0 = nv - z.p.theiler;
         SeriesDesc& d = sd[i];
-        const uint32_t T = hist ? hist_segment_for(c, L0) : segment_for(c, nv, z.p, K);
+        const uint32_t T = hist ? hist_segment_for(c, L0) : segment_for(c, nv, z.p, K, pairs);
         d.y = job.base + z.offset;
         d.n = (uint32_t)z.n;
         d.nv = (uint32_t)nv;
@@ -462,20 +479,20 @@ rqa_status run_job(rqa_ctx* c, Job& job)
             if (fits && select_blocks_per_cu(2, g.sel, 512, select_lds_bytes(2, K, G)) == 1)
                 CT = std::max<uint32_t>(CT, 1024 / TILE_W);
     }
-    // The window pass flushes WIN_BINS fine bins (nearly all non-zero) each
-    // time a workgroup moves to another series: give windowed jobs chunks
-    // large enough that a workgroup sees about eight of them in all.
-    if ((job.mode & MODE_SELECT) && job.sel != 0) {
-        uint64_t tiles = 0;
-        for (uint32_t i = 0; i < S; ++i) tiles += sd[i].ntiles;
-        const uint64_t wgs = (uint64_t)c->num_cu * 2;
-        const uint64_t want = tiles / (wgs * 8);
-        CT = (uint32_t)std::max<uint64_t>(CT, std::min<uint64_t>(want, 1024));
-    }
+    // a tile for each wave of the window pass's workgroups
+    if ((job.mode & MODE_SELECT) && job.sel != 0) CT = std::max<uint32_t>(CT, WIN_BLOCK / TILE_W);
+    // Automatic chunks: up to 8192 steps along the diagonals each (fewer
+    // where a workgroup would not see four), so that short segments go many to
+    // a chunk: the ensemble with 64 to 1024 steps per segment took 6.97 ms with
+    // eight tiles per chunk, 5.98 with 8192 steps and 6.3 with 32,768.
+    uint64_t steps = 0;
+    for (uint32_t i = 0; i < S; ++i) steps += (uint64_t)sd[i].ntiles * sd[i].T;
+    const uint64_t chunk_steps = std::min<uint64_t>(8192, steps / ((uint64_t)c->num_cu * 3 * 4));
     for (Group& g : groups) {
         for (uint32_t i = g.begin; i < g.end; ++i) {
             SeriesDesc& d = sd[i];
-            d.nchunks = (d.ntiles + CT - 1) / CT;
+            d.ctiles = auto_chunks ? (uint32_t)std::max<uint64_t>(CT, chunk_steps / d.T) : CT;
+            d.nchunks = (d.ntiles + d.ctiles - 1) / d.ctiles;
             d.chunk_begin = g.nchunks;  // chunk numbering restarts in every group
             g.nchunks += d.nchunks;
         }
@@ -1250,7 +1267,7 @@ rqa_status tune_job(rqa_ctx* c, Job& job, uint32_t* seg_out, uint32_t* chunk_out
         c->chunk_tiles = DEFAULT_CHUNK;
         // one untimed run first: a GPU that has been idle raises its clocks
         // during the first candidates, which would favour the later ones
-        c->seg = default_segment(L0);
+        c->seg = 512;
         {
             double warm;
             if ((st = time_job(c, sub, 1, &warm))) break;

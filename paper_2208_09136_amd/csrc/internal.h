@@ -77,6 +77,7 @@ struct SeriesDesc {
     uint32_t ntiles;       // (band, segment) tiles
     uint32_t chunk_begin;  // first global chunk index of this series
     uint32_t nchunks;      // chunks of this series
+    uint32_t ctiles;       // tiles per chunk
     uint32_t variant;      // kernel variant (norm/m/lmin class), host bookkeeping
     uint64_t seed;         // sketch sampling stream
     float f_logn, f_m;     // sketch features log2(n)/16 and m/4
