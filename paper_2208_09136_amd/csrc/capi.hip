@@ -223,7 +223,9 @@ TuneKey tune_key(uint64_t nv, const rqa_params& p, uint32_t K)
 uint32_t default_segment(uint64_t pairs, int num_cu, const rqa_params& p)
 {
     const uint64_t steps = pairs / TILE_W / ((uint64_t)num_cu * 8);
-    const uint64_t t = steps <= 512 ? std::max<uint64_t>(steps, 64) : std::min<uint64_t>(std::max<uint64_t>(steps / 6, 256), 1024);
+    // an eighth more than its share, or a few workgroups would not find a CU
+    if (steps <= 512) return (uint32_t)((steps * 9 / 8 + 63) / 64 * 64 + (steps ? 0 : 64));
+    const uint64_t t = std::min<uint64_t>(std::max<uint64_t>(steps / 6, 256), 1024);
     const int cls = select_variant_of(p.norm, p.m, p.tau) % NUM_MCLASS;
     const uint64_t unit = cls == 3 ? 320 : cls == 2 ? 192 : 64;
     return (uint32_t)(t >= unit ? t / unit * unit : t / 64 * 64);
@@ -238,11 +240,6 @@ uint32_t segment_for(const rqa_ctx* c, uint64_t nv, const rqa_params& p, uint32_
     if (it != c->tune.end()) return it->second.seg;
     return default_segment(pairs, c->num_cu, p);
 }
-
-// The threshold sweep runs 1024-thread workgroups when its LDS (rank table,
-// per-lane histograms of K + 1 rows) admits only one workgroup per CU: at
-// K = 99 on two N = 1e5 series 6.1 -> 4.5 ms.
-bool wide_sweep(const rqa_ctx* c, uint32_t K) { return sweep_lds_bytes(K, false) * 2 > c->max_lds; }
 
 // Segment of the histogram pass: the caller's override (at most
 // HIST_MAX_SEG_HOST), else about 96 segments on the longest diagonal
@@ -350,6 +347,7 @@ struct Job {
     int sel = 0;                     // selection: 0 plain radix, 1 network window, 2 sample window, 3 given window
     std::vector<uint64_t> k;         // S*K, selection targets
     std::vector<uint32_t> eps_bits;  // S*K, sweep-only thresholds
+    std::vector<uint64_t> c_known;   // S*K, sweep-only: #{key <= eps} where it is known (else counted)
     // results
     std::vector<float> eps;
     std::vector<uint64_t> kout, count_sel, count;
@@ -384,6 +382,8 @@ rqa_status run_job(rqa_ctx* c, Job& job)
     const uint32_t S = (uint32_t)job.series.size();
     const uint32_t K = job.K;
     const bool hist = (job.mode & MODE_HIST) != 0;
+    // the threshold sweep counts C unless the selection before it has
+    const bool rho = !(job.mode & MODE_SELECT) && job.c_known.empty();
     // histogram pass: the largest workgroup whose stacks fit in LDS, one tile per wave and chunk
     uint32_t hist_block = 0;
     if (hist) {
@@ -401,9 +401,6 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         CT = hist ? hist_block / TILE_W : chunk_for(c, S, z0.n - (uint64_t)(z0.p.m - 1) * z0.p.tau, z0.p, K);
         auto_chunks = CT == 0;
         if (auto_chunks) CT = DEFAULT_CHUNK;
-        // the wide threshold sweep needs a tile per wave of its 1024-thread workgroups
-        if ((job.mode & MODE_SWEEP) && !((job.mode & MODE_SELECT) && (job.mode & MODE_LINES)) && wide_sweep(c, K))
-            CT = std::max<uint32_t>(CT, 1024 / TILE_W);
     }
 
     // descriptors, ordered by kernel variant so each launch sees a contiguous range
@@ -809,14 +806,14 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         for (size_t gi = 0; gi < groups.size(); ++gi) {
             const Group& g = groups[gi];
             DevBufs v = view(g);
-            const uint32_t block = (!fused && wide_sweep(c, K)) ? 1024 : 512;
-            const size_t lds = sweep_lds_bytes(fused ? 2 * K + 1 : K, fused);
-            const int per_cu = sweep_blocks_per_cu(g.swp, fused, block, lds);
+            const uint32_t block = 512;
+            const size_t lds = sweep_lds_bytes(fused ? 2 * K + 1 : K, fused, rho);
+            const int per_cu = sweep_blocks_per_cu(g.swp, fused, rho, block, lds);
             const uint32_t grid = c->grid ? c->grid
                                           : std::max<uint32_t>(1, std::min<uint32_t>(g.nchunks, (uint32_t)(c->num_cu * per_cu)));
             const int t = take(1);
             if (t < 0) return fail(RQA_ERR_UNSUPPORTED, "too many kernel launches in one call");
-            HIP_TRY(launch_sweep(gstream(gi), v, g.swp, fused, grid, block, (uint32_t)t));
+            HIP_TRY(launch_sweep(gstream(gi), v, g.swp, fused, rho, grid, block, (uint32_t)t));
         }
         HIP_TRY(join());
         HIP_TRY(tm.end());
@@ -908,7 +905,7 @@ rqa_status run_job(rqa_ctx* c, Job& job)
             double sum = 0.0;
             for (uint32_t r = 0; r < K; ++r) {
                 const uint32_t j = (uint32_t)(w_hitmap[r] >> 32);
-                const uint64_t cnt = C[j];
+                const uint64_t cnt = rho ? C[j] : (job.mode & MODE_SELECT) ? w_count[r] : job.c_known[(size_t)s * K + r];
                 const double det = cnt ? (double)D[j] / (double)cnt : NAN;
                 job.count[(size_t)s * K + r] = cnt;
                 job.rr[(size_t)s * K + r] = (double)cnt / (double)job.M[s];
@@ -1093,13 +1090,13 @@ void finish_lines(Job& job)
 // threshold sweep.  The range sweep's cost grows with K (line-rank histograms
 // of 2K + 1 rows in LDS, which keep three workgroups per CU up to K = 76, and
 // more keys inside candidate ranges take its fine-counter path), the
-// threshold sweep's hardly does.  Measured on MI355X (two N = 1e5 series,
-// targets 1..K %, range sweep / complete selection, ms per step): plain
-// selection 12.7 / 13.6 at K = 56, 13.4 / 13.8 at 64, 14.1 / 14.1 at 72,
-// 17.5 / 14.5 at 80; with the sample window, whose candidate ranges are
-// wider, 8.9 / 9.5 at K = 36, 9.4 / 9.6 at 40, 10.5 / 9.8 at 48.
+// threshold sweep's hardly does.  Measured on MI355X (two N = 60,000 series,
+// targets 1..K %, range sweep / complete selection, ms per call): plain
+// selection 4.29 / 4.36 at K = 48, 4.86 / 4.41 at 56, and one N = 1e4 series
+// 0.263 / 0.295 at K = 36, 0.324 / 0.303 at 48; with the sample window, whose
+// candidate ranges are wider, 2.95 / 3.10 at K = 40, 3.53 / 3.14 at 48.
 #ifndef RQA_FUSED_MAX_K_PLAIN
-#define RQA_FUSED_MAX_K_PLAIN 64
+#define RQA_FUSED_MAX_K_PLAIN 44
 #endif
 #ifndef RQA_FUSED_MAX_K_WINDOW
 #define RQA_FUSED_MAX_K_WINDOW 40
@@ -1109,7 +1106,7 @@ constexpr uint32_t FUSED_MAX_K_WINDOW = RQA_FUSED_MAX_K_WINDOW;
 
 bool use_fused(const rqa_ctx* c, uint32_t K, int sel)
 {
-    return K <= (sel == 0 ? FUSED_MAX_K_PLAIN : FUSED_MAX_K_WINDOW) && sweep_lds_bytes(2 * K + 1, true) <= c->max_lds;
+    return K <= (sel == 0 ? FUSED_MAX_K_PLAIN : FUSED_MAX_K_WINDOW) && sweep_lds_bytes(2 * K + 1, true, false) <= c->max_lds;
 }
 
 rqa_status select_and_sweep(rqa_ctx* c, Job& job)
@@ -1145,6 +1142,7 @@ rqa_status select_and_sweep(rqa_ctx* c, Job& job)
     sw.series = job.series;
     sw.eps_bits.resize(job.eps.size());
     std::memcpy(sw.eps_bits.data(), job.eps.data(), sizeof(uint32_t) * job.eps.size());
+    sw.c_known = job.count_sel;
     if ((st = run_job(c, sw))) return st;
     c->stat_passes += 1;
     job.count = sw.count;

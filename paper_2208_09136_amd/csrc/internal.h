@@ -192,7 +192,8 @@ hipError_t launch_select_scan(hipStream_t st, const DevBufs& b, int pass, bool f
 hipError_t launch_sweep_prep(hipStream_t st, const DevBufs& b);
 // ranges = false: sweep at given thresholds (rank table from k_sweep_prep);
 // ranges = true: range sweep (code table from the scan before it)
-hipError_t launch_sweep(hipStream_t st, const DevBufs& b, int variant, bool ranges, uint32_t grid,
+// rho (given thresholds): count C too, not only the line values
+hipError_t launch_sweep(hipStream_t st, const DevBufs& b, int variant, bool ranges, bool rho, uint32_t grid,
                         uint32_t block, uint32_t ticket);
 // After the range sweep: eps, C and D into the host's result words (device or
 // pinned host memory).
@@ -248,15 +249,14 @@ constexpr int NUM_SWEEP_VARIANTS = NUM_SELECT_VARIANTS * 3;
 int select_variant_of(uint32_t norm, uint32_t m, uint32_t tau);
 int variant_of(uint32_t norm, uint32_t m, uint32_t tau, uint32_t lmin);
 
-// Dynamic LDS bytes of each kernel for a K and group size.  The sweep holds
-// rows + 1 histogram rows per lane: rows = K for given thresholds, 2K + 1 for
-// the range sweep.
+// Dynamic LDS bytes of each kernel for a K and group size.  Histogram rows of
+// the sweeps: K for given thresholds, 2K + 1 for the range sweep.
 size_t select_lds_bytes(int pass, uint32_t K, uint32_t group_slots);
-size_t sweep_lds_bytes(uint32_t rows, bool ranges);
+size_t sweep_lds_bytes(uint32_t rows, bool ranges, bool rho);
 
 // Occupancy helpers (kernels.hip): max resident workgroups per CU.
 int select_blocks_per_cu(int pass, int variant, uint32_t block, size_t lds);
-int sweep_blocks_per_cu(int variant, bool ranges, uint32_t block, size_t lds);
+int sweep_blocks_per_cu(int variant, bool ranges, bool rho, uint32_t block, size_t lds);
 hipError_t set_kernel_lds_limits(size_t max_dyn_lds);
 
 // VALU issue-rate probe (probe.hip): kind 0 v_add_f32, 1 v_add_u32,

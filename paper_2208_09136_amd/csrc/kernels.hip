@@ -550,11 +550,19 @@ __device__ __forceinline__ void chunk_loop(const SeriesDesc* __restrict__ sds, u
     if (cur != 0xFFFFFFFFu) body.flush(cur);
 }
 
-// Adds 1 to slot base[idx] for every active lane, one atomic per distinct idx
-// among the active lanes.
+// Adds 1 to slot base[idx] for every active lane: an atomic per lane where few
+// are active, else (ties) one per distinct idx.  An atomic per distinct idx in
+// every case took some 20 instructions for each of the one or two lanes that
+// usually hit (K = 99: window pass 2 over a hundred N = 1e4 series 2.57 -> 1.72
+// ms, pass 3 over two N = 60,000 series 1.65 -> 1.38 ms).
 __device__ __forceinline__ void wave_add(unsigned long long* base, uint32_t idx, bool active)
 {
     uint64_t mask = __ballot(active);
+    if (!mask) return;
+    if (__popcll(mask) <= 8) {
+        if (active) atomicAdd(base + idx, 1ull);
+        return;
+    }
     while (mask) {
         const int leader = __ffsll((unsigned long long)mask) - 1;
         const uint32_t li = __builtin_amdgcn_readlane(idx, leader);
@@ -1271,6 +1279,17 @@ __device__ __forceinline__ uint32_t code_of(uint32_t u, const CodeCtx& c)
     return *(const __attribute__((address_space(3))) uint8_t*)(size_t)off;
 }
 
+// Sum of a histogram row of cols (a power of two, at least 32) columns; at most
+// 2^32 - 1, as all cells counted between two flushes.  Thread j starts at column
+// j, so that neighbouring threads' rows are read from different banks.
+__device__ __forceinline__ uint32_t row_sum(const uint32_t* row, uint32_t j, uint32_t cols)
+{
+    uint32_t sum = 0;
+#pragma unroll 16
+    for (uint32_t l = 0; l < cols; ++l) sum += row[(j + l) & (cols - 1u)];
+    return sum;
+}
+
 // Line rank lambda_t: the smallest threshold index at which cell t lies on a
 // diagonal line of length >= lmin, i.e. the minimum over windows of lmin
 // consecutive cells containing t of the window's largest rho (cells outside
@@ -1279,15 +1298,34 @@ __device__ __forceinline__ uint32_t code_of(uint32_t u, const CodeCtx& c)
 // of the cell's line value: the same expression over keys, i.e. the smallest
 // threshold at which the cell lies on such a line (Eq. 4 and the line
 // definition after it).
-template <int NORM, int MC, int TC, int LMC>
+// RHO: count the cells' ranks too (C at every threshold); without it only the
+// line ranks, where the selection has counted C already: a third of the LDS
+// traffic, and room for another workgroup.
+// LDS: rank table, thresholds, then the histograms of rows + 1 rows (the last
+// collects cells that recur at no threshold) with a column per lane, or 32
+// columns (lanes L and L + 32 share one) where 64 would cost a CU its second or
+// third workgroup of 512 threads.
+__host__ __device__ __forceinline__ size_t rank_sweep_lds(uint32_t rows, bool rho, uint32_t cols)
+{
+    return RHO_TABLE * sizeof(uint2) + RANK_MAX * 4 + (rho ? 2 : 1) * (size_t)(rows + 1) * cols * 4;
+}
+__host__ __device__ __forceinline__ uint32_t rank_sweep_cols(uint32_t rows, bool rho)
+{
+    const uint32_t f64 = lds_blocks_fit(rank_sweep_lds(rows, rho, 64) + 16), f32 = lds_blocks_fit(rank_sweep_lds(rows, rho, 32) + 16);
+    return f64 < 3 && f32 > f64 ? 32u : 64u;
+}
+
+template <int NORM, int MC, int TC, int LMC, bool RHO>
 struct SweepBody {
     uint2* stab;          // LDS [RHO_TABLE]
     uint32_t* ses;        // LDS [RANK_MAX]
-    uint32_t* brho;       // LDS [Kcap+1][64]: row Kp collects cells that recur at no threshold
-    uint32_t* blam;       // LDS [Kcap+1][64]
+    uint32_t* brho;       // LDS [Kcap+1][cols]: row Kp collects cells that recur at no threshold
+    uint32_t* blam;       // LDS [Kcap+1][cols]
     const uint2* rtab;    // global [S][RHO_TABLE]
     SeriesWork* works;
     uint32_t Kcap;
+    uint32_t cols, csh;   // histogram columns, log2 of a row's bytes
+    uint32_t lcol;        // this lane's column byte offset
     RhoCtx rc;
     uint32_t lmin;
     bool multi;
@@ -1298,7 +1336,10 @@ struct SweepBody {
         const SeriesWork& w = works[s];
         for (uint32_t i = threadIdx.x; i < RHO_TABLE; i += blockDim.x) stab[i] = rtab[(size_t)s * RHO_TABLE + i];
         for (uint32_t i = threadIdx.x; i < RANK_MAX; i += blockDim.x) ses[i] = w.esorted[i];
-        for (uint32_t i = threadIdx.x; i < (Kcap + 1) * TILE_W; i += blockDim.x) { brho[i] = 0u; blam[i] = 0u; }
+        for (uint32_t i = threadIdx.x; i < (Kcap + 1) * cols; i += blockDim.x) {
+            if constexpr (RHO) brho[i] = 0u;
+            blam[i] = 0u;
+        }
         rc.table = stab;
         rc.es = ses;
         rc.emin = __uint_as_float(uniform(w.emin));
@@ -1311,20 +1352,18 @@ struct SweepBody {
     {
         SeriesWork& w = works[s];
         const uint32_t Kp = rc.Kp;
-        for (uint32_t j = threadIdx.x; j < 2 * Kp; j += blockDim.x) {
-            const uint32_t* row = (j < Kp) ? brho + j * TILE_W : blam + (j - Kp) * TILE_W;
-            uint64_t sum = 0;
-            for (int l = 0; l < TILE_W; ++l) sum += row[l];
-            if (sum) atomicAdd((unsigned long long*)((j < Kp) ? &w.hrho[j] : &w.hlam[j - Kp]),
-                               (unsigned long long)sum);
+        for (uint32_t j = threadIdx.x; j < (RHO ? 2 : 1) * Kp; j += blockDim.x) {
+            const uint32_t sum = row_sum(j < Kp ? blam + j * cols : brho + (j - Kp) * cols, j, cols);
+            if (sum)
+                atomicAdd((unsigned long long*)(j < Kp ? &w.hlam[j] : &w.hrho[j - Kp]), (unsigned long long)sum);
         }
     }
     // rho, lam <= Kp: the row Kp absorbs cells that recur at no threshold, so
-    // the counting is branch-free and every lane hits its own bank.
-    __device__ __forceinline__ void emit(uint32_t rho, uint32_t lam, int lane) const
+    // the counting is branch-free
+    __device__ __forceinline__ void emit(uint32_t rho, uint32_t lam, int) const
     {
-        atomicAdd(&brho[rho * TILE_W + lane], 1u);
-        atomicAdd(&blam[lam * TILE_W + lane], 1u);
+        if constexpr (RHO) atomicAdd((uint32_t*)((unsigned char*)brho + ((rho << csh) + lcol)), 1u);
+        atomicAdd((uint32_t*)((unsigned char*)blam + ((lam << csh) + lcol)), 1u);
     }
     template <bool MULTI>
     __device__ __forceinline__ uint32_t rho_at(const SeriesScalars& sd, const TileGeo& g, int x) const
@@ -1492,20 +1531,14 @@ struct RangeBody {
         dk = (unsigned long long*)(fineK + (size_t)s * fine_stride);
         dl = (unsigned long long*)(fineL + (size_t)s * fine_stride);
     }
-    // one wave per row (a thread per row would read every column of its row
-    // from the same bank as its neighbours)
     __device__ void flush(uint32_t s)
     {
         if (!active || LMC == 1) return;
         SeriesWork& w = works[s];
-        const uint32_t lane = threadIdx.x & 63u;
-        for (uint32_t j = threadIdx.x >> 6; j < spare; j += blockDim.x >> 6) {
-            uint32_t v = (j & 1u) == 0u && lane < cols ? blam[j * cols + lane] : 0u;
-            uint64_t sum = v;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-            sum += hx[j];
-            if (lane == 0 && sum) atomicAdd((unsigned long long*)&w.hlam[j], (unsigned long long)sum);
+        for (uint32_t j = threadIdx.x; j < spare; j += blockDim.x) {
+            uint64_t sum = hx[j];
+            if ((j & 1u) == 0u) sum += row_sum(blam + j * cols, j, cols);
+            if (sum) atomicAdd((unsigned long long*)&w.hlam[j], (unsigned long long)sum);
         }
     }
     // row of a line code, this lane's column: one shift-and-add for the byte offset
@@ -1681,29 +1714,32 @@ struct RangeBody {
     }
 };
 
-// LDS of the sweeps: rank table, thresholds, per-lane histograms with a spare
-// row (two for given thresholds, one for the range sweep, which also holds
-// the group arrays), then the work-queue word.
-__host__ __device__ __forceinline__ size_t sweep_lds_bytes_dev(uint32_t rows, bool ranges)
+// LDS of the sweeps; the work-queue word follows.
+__host__ __device__ __forceinline__ size_t sweep_lds_bytes_dev(uint32_t rows, bool ranges, bool rho)
 {
-    if (ranges)
-        return range_lds_layout(rows, range_cols(rows));
-    return RHO_TABLE * sizeof(uint2) + RANK_MAX * 4 + 2 * (size_t)(rows + 1) * TILE_W * 4;
+    return ranges ? range_lds_layout(rows, range_cols(rows)) : rank_sweep_lds(rows, rho, rank_sweep_cols(rows, rho));
 }
 
-// Launched with 512 threads, or 1024 where its LDS admits one workgroup per
-// CU (large K), so that more waves share the one copy of the tables.
-template <int NORM, int MC, int TC, int LMC>
-__global__ void __launch_bounds__(1024)
+// 512 threads and 80 registers, so that three workgroups fit where the LDS
+// admits them.  K = 99 (RR 1 .. 99 %), a hundred N = 1e4 series: 2.24 ms
+// counting both ranks in one 1024-thread workgroup per CU, 1.66 ms counting
+// line ranks in three; two N = 60,000 series 1.54 -> 1.12 ms (1.20 with 83
+// registers, two workgroups).  Both ranks at 100 given thresholds, N = 1e4
+// (two workgroups of 32 columns): 45 us, as one of 64 columns and 1024 threads.
+template <int NORM, int MC, int TC, int LMC, bool RHO>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6)))
 k_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
         uint32_t* __restrict__ ticket, SeriesWork* __restrict__ works, const uint2* __restrict__ rtab, uint32_t Kcap)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    SweepBody<NORM, MC, TC, LMC> body;
+    SweepBody<NORM, MC, TC, LMC, RHO> body;
+    body.cols = rank_sweep_cols(Kcap, RHO);
+    body.csh = body.cols == 64 ? 8u : 7u;
+    body.lcol = ((uint32_t)threadIdx.x & (body.cols - 1)) * 4u;
     body.stab = (uint2*)smem;
     body.ses = (uint32_t*)(smem + RHO_TABLE * sizeof(uint2));
-    body.brho = body.ses + RANK_MAX;
-    body.blam = body.brho + (size_t)(Kcap + 1) * TILE_W;
+    body.blam = body.ses + RANK_MAX;
+    body.brho = body.blam + (size_t)(Kcap + 1) * body.cols;  // RHO only
     body.rtab = rtab;
     body.works = works;
     body.Kcap = Kcap;
@@ -1711,7 +1747,7 @@ k_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
     // the generic line class reads lmin from the descriptors: launches group
     // series of one lmin
     body.lmin = LMC == 0 ? sds[0].lmin : (uint32_t)LMC;
-    chunk_loop(sds, S, nchunks, ticket, body, (uint32_t*)(smem + sweep_lds_bytes_dev(Kcap, false)));
+    chunk_loop(sds, S, nchunks, ticket, body, (uint32_t*)(smem + sweep_lds_bytes_dev(Kcap, false, RHO)));
 }
 
 // Six waves per SIMD (three workgroups of 512 per CU, which the LDS allows up
@@ -1754,10 +1790,10 @@ k_range_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
             for (uint32_t s = 0; s < S; ++s) atomicOr(&works[s].status, 64u);
         return;
     }
-    chunk_loop(sds, S, nchunks, ticket, body, (uint32_t*)(smem + sweep_lds_bytes_dev(rows, true)));
+    chunk_loop(sds, S, nchunks, ticket, body, (uint32_t*)(smem + sweep_lds_bytes_dev(rows, true, false)));
 }
 
-size_t sweep_lds_bytes(uint32_t rows, bool ranges) { return sweep_lds_bytes_dev(rows, ranges) + 16; }
+size_t sweep_lds_bytes(uint32_t rows, bool ranges, bool rho) { return sweep_lds_bytes_dev(rows, ranges, rho) + 16; }
 
 using SweepFn = void (*)(const SeriesDesc*, uint32_t, uint32_t, uint32_t*, SeriesWork*, const uint2*,
                          uint32_t);
@@ -1765,11 +1801,11 @@ using RangeFn = void (*)(const SeriesDesc*, uint32_t, uint32_t, uint32_t*, Serie
                          uint32_t, uint64_t*, uint64_t*, uint32_t);
 
 template <int NORM, int MC, int TC>
-static SweepFn sweep_fn_l(int lc)
+static SweepFn sweep_fn_l(int lc, bool rho)
 {
-    if (lc == 1) return k_sweep<NORM, MC, TC, 1>;
-    if (lc == 2) return k_sweep<NORM, MC, TC, 2>;
-    return k_sweep<NORM, MC, TC, 0>;
+    if (lc == 1) return rho ? k_sweep<NORM, MC, TC, 1, true> : k_sweep<NORM, MC, TC, 1, false>;
+    if (lc == 2) return rho ? k_sweep<NORM, MC, TC, 2, true> : k_sweep<NORM, MC, TC, 2, false>;
+    return rho ? k_sweep<NORM, MC, TC, 0, true> : k_sweep<NORM, MC, TC, 0, false>;
 }
 
 template <int NORM, int MC, int TC>
@@ -1781,13 +1817,13 @@ static RangeFn range_fn_l(int lc)
 }
 
 template <int NORM>
-static SweepFn sweep_fn_n(int mclass, int lc)
+static SweepFn sweep_fn_n(int mclass, int lc, bool rho)
 {
     switch (mclass) {
-    case 1: return sweep_fn_l<NORM, 1, 0>(lc);
-    case 2: return sweep_fn_l<NORM, 3, 3>(lc);
-    case 3: return sweep_fn_l<NORM, 3, 5>(lc);
-    default: return sweep_fn_l<NORM, 0, 0>(lc);
+    case 1: return sweep_fn_l<NORM, 1, 0>(lc, rho);
+    case 2: return sweep_fn_l<NORM, 3, 3>(lc, rho);
+    case 3: return sweep_fn_l<NORM, 3, 5>(lc, rho);
+    default: return sweep_fn_l<NORM, 0, 0>(lc, rho);
     }
 }
 
@@ -1802,11 +1838,11 @@ static RangeFn range_fn_n(int mclass, int lc)
     }
 }
 
-static SweepFn sweep_fn(int variant)
+static SweepFn sweep_fn(int variant, bool rho)
 {
     const int lc = variant % 3, sv = variant / 3;
     const int norm = sv / NUM_MCLASS, mc = sv % NUM_MCLASS;
-    return norm == RQA_NORM_MAX ? sweep_fn_n<RQA_NORM_MAX>(mc, lc) : sweep_fn_n<RQA_NORM_EUCLIDEAN>(mc, lc);
+    return norm == RQA_NORM_MAX ? sweep_fn_n<RQA_NORM_MAX>(mc, lc, rho) : sweep_fn_n<RQA_NORM_EUCLIDEAN>(mc, lc, rho);
 }
 
 static RangeFn range_fn(int variant)
@@ -1818,23 +1854,23 @@ static RangeFn range_fn(int variant)
 
 static uint32_t sweep_rows(uint32_t K, bool ranges) { return ranges ? 2 * K + 1 : K; }
 
-hipError_t launch_sweep(hipStream_t st, const DevBufs& b, int variant, bool ranges, uint32_t grid, uint32_t block,
-                        uint32_t ticket)
+hipError_t launch_sweep(hipStream_t st, const DevBufs& b, int variant, bool ranges, bool rho, uint32_t grid,
+                        uint32_t block, uint32_t ticket)
 {
     const uint32_t rows = sweep_rows(b.K, ranges);
     if (ranges)
-        hipLaunchKernelGGL(range_fn(variant), dim3(grid), dim3(block), sweep_lds_bytes(rows, true), st, b.sd, b.S,
+        hipLaunchKernelGGL(range_fn(variant), dim3(grid), dim3(block), sweep_lds_bytes(rows, true, false), st, b.sd, b.S,
                            b.nchunks, b.tickets + ticket, b.work, b.rtab, rows, b.fineK, b.fineL,
                            b.fine_stride);
     else
-        hipLaunchKernelGGL(sweep_fn(variant), dim3(grid), dim3(block), sweep_lds_bytes(rows, false), st, b.sd, b.S,
+        hipLaunchKernelGGL(sweep_fn(variant, rho), dim3(grid), dim3(block), sweep_lds_bytes(rows, false, rho), st, b.sd, b.S,
                            b.nchunks, b.tickets + ticket, b.work, b.rtab, rows);
     return hipGetLastError();
 }
 
-int sweep_blocks_per_cu(int variant, bool ranges, uint32_t block, size_t lds)
+int sweep_blocks_per_cu(int variant, bool ranges, bool rho, uint32_t block, size_t lds)
 {
-    return blocks_per_cu(ranges ? (const void*)range_fn(variant) : (const void*)sweep_fn(variant), block, lds);
+    return blocks_per_cu(ranges ? (const void*)range_fn(variant) : (const void*)sweep_fn(variant, rho), block, lds);
 }
 
 // Threads of the sweeps' set-up kernels: each looks up a few table buckets
@@ -3176,7 +3212,8 @@ hipError_t set_kernel_lds_limits(size_t max_dyn_lds)
         for (int p = 1; p <= 3; ++p) set((const void*)select_fn_pass(p, v));
         for (int p = 1; p <= 2; ++p) set((const void*)window_fn(p, v));
         for (int l = 0; l < 3; ++l) {
-            set((const void*)sweep_fn(v * 3 + l));
+            set((const void*)sweep_fn(v * 3 + l, false));
+            set((const void*)sweep_fn(v * 3 + l, true));
             set((const void*)range_fn(v * 3 + l));
         }
         set((const void*)hist_fn(v));
