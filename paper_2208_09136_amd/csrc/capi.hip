@@ -242,13 +242,17 @@ uint32_t segment_for(const rqa_ctx* c, uint64_t nv, const rqa_params& p, uint32_
 }
 
 // Segment of the histogram pass: the caller's override (at most
-// HIST_MAX_SEG_HOST), else about 96 segments on the longest diagonal
-// (256 .. 4096).
-uint32_t hist_segment_for(const rqa_ctx* c, uint64_t L0)
+// HIST_MAX_SEG_HOST), else what spreads the call's pairs over eight waves per
+// CU, but at least 64 and at most 448 cells (four N = 2e4 series with 256 / 448
+// / 640: 1.45 / 1.38 / 1.39 ms); beyond, about 48 segments on the longest
+// diagonal, up to 4096 (the runs at segment borders take 4 bytes per segment,
+// diagonal and threshold).
+uint32_t hist_segment_for(const rqa_ctx* c, uint64_t L0, uint64_t pairs)
 {
     if (c->seg) return std::min<uint32_t>(c->seg, HIST_MAX_SEG_HOST);
-    const uint64_t t = (L0 + 95) / 96;
-    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>((t + TILE_W - 1) / TILE_W * TILE_W, 256), 4096);
+    const auto round = [](uint64_t t) { return (t + TILE_W - 1) / TILE_W * TILE_W; };
+    const uint64_t share = round(pairs / TILE_W / ((uint64_t)c->num_cu * 8));
+    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>({round((L0 + 47) / 48), std::min<uint64_t>(share, 448), TILE_W}), 4096);
 }
 
 uint32_t chunk_for(const rqa_ctx* c, uint32_t S, uint64_t nv0, const rqa_params& p0, uint32_t K)
@@ -384,13 +388,21 @@ rqa_status run_job(rqa_ctx* c, Job& job)
     const bool hist = (job.mode & MODE_HIST) != 0;
     // the threshold sweep counts C unless the selection before it has
     const bool rho = !(job.mode & MODE_SELECT) && job.c_known.empty();
-    // histogram pass: the largest workgroup whose stacks fit in LDS, one tile per wave and chunk
+    // histogram pass: one tile per wave and chunk, and the largest workgroup whose
+    // stacks fit in LDS and which leaves chunks for all CUs
     uint32_t hist_block = 0;
     if (hist) {
+        uint64_t pairs = 0, L0 = 0;
+        for (const Series& z : job.series) {
+            const uint64_t a = z.n - (uint64_t)(z.p.m - 1) * z.p.tau - z.p.theiler;
+            pairs += a * (a + 1) / 2;
+            L0 = std::max(L0, a);
+        }
+        const uint64_t tiles = pairs / TILE_W / hist_segment_for(c, L0, pairs);
         for (uint32_t b : {1024u, 512u, 256u, 128u, 64u})
             if (hist_lds_bytes(job.hist_kp, b) <= c->max_lds) {
                 hist_block = b;
-                break;
+                if (tiles > (uint64_t)c->num_cu * (b / 2 / TILE_W)) break;
             }
         if (!hist_block) return fail(RQA_ERR_UNSUPPORTED, "the histogram pass does not fit in LDS");
     }
@@ -442,7 +454,7 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         const uint64_t nv = z.n - (uint64_t)(z.p.m - 1) * z.p.tau;
         const uint64_t L0 = nv - z.p.theiler;
         SeriesDesc& d = sd[i];
-        const uint32_t T = hist ? hist_segment_for(c, L0) : segment_for(c, nv, z.p, K, pairs);
+        const uint32_t T = hist ? hist_segment_for(c, L0, pairs) : segment_for(c, nv, z.p, K, pairs);
         d.y = job.base + z.offset;
         d.n = (uint32_t)z.n;
         d.nv = (uint32_t)nv;

@@ -1958,40 +1958,63 @@ hipError_t launch_sweep_prep(hipStream_t st, const DevBufs& b)
 // Full line-length histogram P_j(l) at given thresholds (the histogram behind
 // Eq. 4).  Tiles are the (band, segment) tiles of the sweep.  Each lane keeps
 // a stack of the cells of its segment that were larger in rank than every
-// later cell so far ("previous greater" chain): ranks strictly decrease from
-// the bottom (a sentinel at position t0 - 1, above every rank) to the top.
+// later cell so far ("previous greater" chain).  Ranks in it differ, so the
+// stack is a set of ranks, one bit each, with the smallest rank on top, and
+// per rank the start of its run: the cell after the last one of larger rank.
+// (Positions count from HIST_SHORT on, and a run from the segment's first cell
+// starts at 0: such a run is never taken for a short line.)
 // A new cell of rank r at position t pops every entry of rank <= r; popping
-// entry (r_i, p_i) with (r_n, p_n) below it ends, for every threshold j in
-// [r_i, min(r_n, r)), the run of cells p_n + 1 .. t - 1 (at threshold j the
-// last cell before t that is not recurrent is p_n).  A run inside the
+// entry (r_i, start s_i) with r_n below it ends, for every threshold j in
+// [r_i, min(r_n, r)), the run of cells s_i .. t - 1.  The new entry's run
+// starts where the last popped one did, else at t.  A run inside the
 // segment is a line: one +1 / -1 pair in a difference histogram over j for
 // its length, so the work per cell is amortised O(1) whatever the number of
 // thresholds, and P_j(l) is the prefix sum over j.  A run that starts at the
-// segment's first cell (p_n is the sentinel) or ends at its last may continue
+// segment's first cell (start 0) or ends at its last may continue
 // in the neighbouring segment: per lane and threshold the segment records
 // the length of its leading run (pre_j) and trailing run (suf_j), and a join
 // pass walks each diagonal's segments in order and counts the lines that
 // cross segment borders.  Cells past the end of a diagonal have rank Kp
-// (recurrent at no threshold).  The top two stack entries live in registers;
-// entries pack (rank << 24) | (position + 1).
+// (recurrent at no threshold).
+//
+// The number of pops differs from lane to lane.  With every lane popping in
+// lockstep, cell by cell, a cell cost the longest pop chain among 64 lanes.
+// Instead each lane first lists the cells that do anything (a cell of rank Kp
+// after another does not).  When some lane's list may not take another block,
+// each works through its own list, a pop and a push per step: lanes wait for
+// each other once per list.
 constexpr uint32_t HIST_SHORT = 64;     // lengths below this count in LDS
 constexpr uint32_t HIST_MAX_K = RQA_MAX_HIST_K;  // distinct thresholds
 static_assert(HIST_MAX_K == HIST_MAX_K_HOST, "histogram limits");
-static_assert(HIST_MAX_K + 1 < 256, "ranks are packed into 8 bits");
-static_assert(HIST_MAX_SEG_HOST < 65536, "run lengths are stored in 16 bits");
+static_assert(HIST_MAX_K <= 32, "a lane's stack is a set of 32 ranks");
+static_assert(HIST_MAX_SEG_HOST + HIST_SHORT < 65536, "positions are stored in 16 bits");
+constexpr uint32_t HIST_LIST_MIN = 12, HIST_LIST_MAX = 36;  // cells on a lane's list: at least a walk block
+// Row of the short lines' counters: odd, so that one length at different
+// thresholds lies in different banks.
+constexpr uint32_t HIST_ROW = HIST_SHORT + 1;
 
-__host__ __device__ __forceinline__ size_t hist_lds_bytes_dev(uint32_t Kp, uint32_t block)
+// LDS of the histogram pass: rank table, thresholds, starts and lists of block
+// threads, short lines' counters.  A list takes what the LDS leaves a workgroup
+// of 1024 threads, which is what the registers allow a CU (longer lists, fewer
+// waits: 24 / 36 cells at 20 thresholds 1.26 / 1.19 ms).
+__host__ __device__ __forceinline__ size_t hist_lds_bytes_dev(uint32_t Kp, uint32_t list, uint32_t block)
 {
-    return RHO_TABLE * sizeof(uint2) + RANK_MAX * 4 + (size_t)(Kp + 1) * block * 4 +
-           (size_t)HIST_SHORT * (Kp + 1) * 4;
+    return RHO_TABLE * sizeof(uint2) + RANK_MAX * 4 + (size_t)(Kp + list) * block * 2 + (size_t)HIST_ROW * (Kp + 1) * 4;
+}
+__host__ __device__ __forceinline__ uint32_t hist_list(uint32_t Kp)
+{
+    const uint32_t rows = (uint32_t)((LDS_PER_CU - 16 - hist_lds_bytes_dev(Kp, 0, 0)) / (1024 * 2));
+    const uint32_t n = rows < Kp + HIST_LIST_MIN ? HIST_LIST_MIN : rows - Kp;
+    return n < HIST_LIST_MAX ? n : HIST_LIST_MAX;
 }
 
 template <int NORM, int MC, int TC>
 struct HistBody {
     uint2* stab;          // LDS [RHO_TABLE]
     uint32_t* ses;        // LDS [RANK_MAX]
-    uint32_t* stk;        // LDS [Kp + 1][blockDim] stack entries below the top two (column = thread)
-    uint32_t* dsh;        // LDS [Kp + 1][HIST_SHORT] difference counts of short lines
+    uint16_t* start;      // LDS [Kp][blockDim] start of the run of a rank in the stack (column = thread)
+    uint16_t* events;     // LDS [hist_list][blockDim] list of cells: rank + (position - base << 6)
+    uint32_t* dsh;        // LDS [Kp + 1][HIST_ROW] difference counts of short lines
     const SeriesDesc* sds;
     const uint2* rtab;
     SeriesWork* works;
@@ -2001,19 +2024,18 @@ struct HistBody {
     uint32_t hist_len;
     uint32_t kcap;        // Kp + 1 of the launch (row stride)
     uint32_t chunk_tiles;
+    uint32_t short_end;   // lengths below this count in LDS
     RhoCtx rc;
     uint64_t* dser;       // this series' rows
     uint32_t tbase;       // this series' first tile in pre / suf
     bool multi;
     bool active = true;
-    // lane state: the top and next entries of the stack (packed); LDS rows
-    // [0, sp) hold the bottom sentinel and then the entries below next (sp >= 1),
-    // addressed by byte offsets: so = row sp of this lane, so0 / so1 = rows 0 / 1;
-    // pm is the largest rank so far in the segment.  A cell of rank Kp ends every
-    // run: it replaces the whole stack as a new bottom sentinel (rank Kp + 1 at
-    // its position), so runs of such cells cost no pops.  Only the segment's own
-    // sentinel has position t0.
-    uint32_t top, nx, so, so0, so1, bd4, pm, t0;
+    uint32_t stack;       // ranks in this lane's stack
+    uint32_t stride;      // bytes of an LDS row of start and events
+    uint32_t room;        // bytes of a list
+    uint32_t filled;      // end of this lane's list (byte offset)
+    uint32_t base;        // position in the segment that the list's positions count from
+    bool off;             // the last cell had rank Kp
     uint32_t sh3;         // bucket shift - 3
     uint16_t* lpre;       // this lane's pre / suf column in the current tile
     uint16_t* lsuf;
@@ -2024,7 +2046,7 @@ struct HistBody {
         for (uint32_t i = threadIdx.x; i < RHO_TABLE; i += blockDim.x)
             stab[i] = rho_table_entry(rtab[(size_t)s * RHO_TABLE + i]);
         for (uint32_t i = threadIdx.x; i < RANK_MAX; i += blockDim.x) ses[i] = w.esorted[i];
-        for (uint32_t i = threadIdx.x; i < HIST_SHORT * kcap; i += blockDim.x) dsh[i] = 0u;
+        for (uint32_t i = threadIdx.x; i < HIST_ROW * kcap; i += blockDim.x) dsh[i] = 0u;
         rc.table = stab;
         rc.es = ses;
         rc.emin = __uint_as_float(uniform(w.emin));
@@ -2044,32 +2066,12 @@ struct HistBody {
     {
         for (uint32_t i = threadIdx.x; i < HIST_SHORT * kcap; i += blockDim.x) {
             const uint32_t j = i / HIST_SHORT, l = i % HIST_SHORT;
-            const int32_t v = (int32_t)dsh[i];
+            const int32_t v = (int32_t)dsh[j * HIST_ROW + l];
             if (v && l < hist_len)
                 atomicAdd((unsigned long long*)&dser[(size_t)l * kcap + j], (unsigned long long)(int64_t)v);
         }
     }
-    // one line of length l at thresholds [a, b)
-    __device__ __forceinline__ void line(uint32_t l, uint32_t a, uint32_t b)
-    {
-        const uint32_t lb = min(l, hist_len - 1);
-        if (lb < HIST_SHORT) {
-            atomicAdd(&dsh[a * HIST_SHORT + lb], 1u);
-            atomicAdd(&dsh[b * HIST_SHORT + lb], 0xFFFFFFFFu);
-        } else {
-            atomicAdd((unsigned long long*)&dser[(size_t)lb * kcap + a], 1ull);
-            atomicAdd((unsigned long long*)&dser[(size_t)lb * kcap + b], ~0ull);
-        }
-    }
-    __device__ __forceinline__ uint32_t& at(uint32_t off) { return *(uint32_t*)((unsigned char*)stk + off); }
-    static constexpr uint32_t POS = 0xFFFFFFu;
-    __device__ __forceinline__ void pop()
-    {
-        top = nx;
-        // row 0 is the bottom sentinel: below it is the sentinel again
-        nx = at(so - bd4);
-        so = max(so - bd4, so1);
-    }
+    static __device__ __forceinline__ uint16_t& at(uint16_t* column, uint32_t off) { return *(uint16_t*)((unsigned char*)column + off); }
     // rank of a key (at most Kp)
     template <bool MULTI>
     __device__ __forceinline__ uint32_t rank(uint32_t u, const RhoCtx& c) const
@@ -2077,31 +2079,76 @@ struct HistBody {
         if constexpr (MULTI) return rho_of<true>(u, c);
         else return rho_fast(u, c, sh3);
     }
-    // cell of rank r <= Kp at position t
-    __device__ __forceinline__ void cell(uint32_t r, uint32_t t)
+    // Lists the first cnt cells of a block, of ranks rk[u] <= Kp, from position
+    // x on.
+    template <int HU>
+    __device__ __forceinline__ void cells(const uint32_t (&rk)[HU], uint32_t x, int cnt)
     {
-        if (r > pm) {
-            // first cell above thresholds [pm, r): the leading runs there end before t
+        static_assert(HU <= HIST_LIST_MIN && HIST_MAX_K < 64, "event list");
+        if (__any(filled > room - HU * stride) || x + HU - base > 1024u) {
+            work_off();
+            base = x;
+        }
+        const uint32_t at0 = (x - base) << 6;
+#pragma unroll
+        for (int u = 0; u < HU; ++u) {
+            if (u >= cnt) break;
+            const bool last = off;
+            off = rk[u] == rc.Kp;
+            at(events, filled) = (uint16_t)(rk[u] + at0 + ((uint32_t)u << 6));
+            filled += off && last ? 0u : stride;
+        }
+    }
+    // smallest rank of a set; 2^32 - 1 if it is empty
+    static __device__ __forceinline__ uint32_t lowest(uint32_t set)
+    {
+        uint32_t r;
+        asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(set));
+        return r;
+    }
+    // The loop runs while any lane has cells left: left to itself, each lane
+    // would wait after its pops for the others', once per cell.
+    __device__ __forceinline__ void work_off()
+    {
+        const uint32_t end = filled;
+        filled = 0;
+        uint32_t next = 0;
+        uint32_t ev = at(events, 0);
+        uint32_t r = ev & 63u, t = base + (ev >> 6), from = t;
+        while (__any(next != end)) {
+            const bool on = next != end;
+            uint32_t top = lowest(stack);
+            if (on && top <= r) {
+                // thresholds [top, b): none where b = top, and then the two
+                // counts below cancel
+                stack &= stack - 1u;
+                const uint32_t below = lowest(stack), b = min(below, r);
+                from = at(start, top * stride);
+                const uint32_t l = t - from;
+                if (l < short_end) {
+                    atomicAdd(&dsh[top * HIST_ROW + l], 1u);
+                    atomicAdd(&dsh[b * HIST_ROW + l], 0xFFFFFFFFu);
+                } else if (from != 0) {
+                    const uint32_t lb = min(l, hist_len - 1u);
+                    atomicAdd((unsigned long long*)&dser[(size_t)lb * kcap + top], 1ull);
+                    atomicAdd((unsigned long long*)&dser[(size_t)lb * kcap + b], ~0ull);
+                } else {
 #pragma unroll 1
-            for (uint32_t j = pm; j < r; ++j) lpre[(size_t)j * TILE_W] = (uint16_t)(t - t0);
-            pm = r;
+                    for (uint32_t j = top; j < b; ++j) lpre[(size_t)j * TILE_W] = (uint16_t)(t - HIST_SHORT);
+                }
+                top = below;
+            }
+            if (on && top > r) {
+                if (r < rc.Kp) {
+                    at(start, r * stride) = (uint16_t)from;
+                    stack |= 1u << r;
+                }
+                next += stride;
+                ev = at(events, next);
+                r = ev & 63u;
+                from = t = base + (ev >> 6);
+            }
         }
-        // pop while the top's rank is <= r (ranks sit in the high byte)
-        const uint32_t rhi = (r << 24) | POS;
-        while (top <= rhi) {
-            const uint32_t tr = top >> 24, np1 = nx & POS;
-            // next is the segment's sentinel: a leading run, recorded above
-            const uint32_t b = np1 == t0 ? tr : min(nx >> 24, r);
-            if (tr < b) line(t - np1, tr, b);
-            pop();
-        }
-        const bool reset = r == rc.Kp;
-        const uint32_t snt = ((rc.Kp + 1) << 24) | (t + 1);
-        // push: a cell below the top sends next to LDS (a sentinel next is row 0 already)
-        at(reset ? so0 : so) = reset ? snt : nx;
-        so = reset ? so1 : so + (nx < ((rc.Kp + 1) << 24) ? bd4 : 0u);
-        nx = reset ? snt : top;
-        top = reset ? snt : (r << 24) | (t + 1);
     }
     __device__ __forceinline__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
@@ -2116,54 +2163,40 @@ struct HistBody {
         const size_t col = ((size_t)(tbase + tile_id) * kcap) * TILE_W + lane;
         lpre = pre + col;
         lsuf = suf + col;
-        t0 = (uint32_t)g.t0;
-        // sentinel (rank Kp + 1 at position t0 - 1) as top, next and LDS row 0
-        bd4 = blockDim.x * 4u;
-        so0 = threadIdx.x * 4u;
-        so1 = so0 + bd4;
-        so = so1;
-        top = nx = ((Kp + 1) << 24) | t0;
-        at(so0) = top;
-        pm = 0;
+        // every threshold's run starts at the first cell
+        stack = 1u;
+        at(start, 0) = 0;
+        filled = 0;
+        base = HIST_SHORT;
+        off = false;
         constexpr int HU = walk_block<NORM, MC, TC>();
         const RhoCtx c = rc;
-        uint32_t t = t0;
+        uint32_t t = HIST_SHORT;
         walk<NORM, MC, TC>(
             sd, g, g.t0, g.t1,
             [&](const uint32_t(&k)[HU]) {
                 uint32_t rk[HU];
 #pragma unroll
                 for (int u = 0; u < HU; ++u) rk[u] = rank<MULTI>(k[u], c);
-#pragma unroll
-                for (int u = 0; u < HU; ++u) cell(rk[u], t + (uint32_t)u);
+                cells(rk, t, HU);
                 t += HU;
             },
             [&](const uint32_t(&k)[HU], int x) {
                 uint32_t rk[HU];
 #pragma unroll
                 for (int u = 0; u < HU; ++u) rk[u] = x + u < g.len ? min(rank<MULTI>(k[u], c), Kp) : Kp;
-#pragma unroll
-                for (int u = 0; u < HU; ++u)
-                    if (x + u < g.t1) cell(rk[u], (uint32_t)(x + u));
+                cells(rk, HIST_SHORT + (uint32_t)(x - g.t0), g.t1 - x);
             });
-        // trailing runs: below the last cell's rank empty, then one per stack entry
-        const uint32_t e = (uint32_t)g.t1;
-        #pragma unroll 1
-        for (uint32_t j = 0; j < min(top >> 24, Kp); ++j) lsuf[(size_t)j * TILE_W] = 0;
-        while ((top >> 24) <= Kp) {
-            const uint32_t tr = top >> 24, hi = min(nx >> 24, Kp), np1 = nx & POS;
-            if (np1 == t0) {
-                // every cell of the segment recurrent at [tr, Kp)
-                #pragma unroll 1
-                for (uint32_t j = tr; j < hi; ++j) {
-                    lpre[(size_t)j * TILE_W] = (uint16_t)(e - t0);
-                    lsuf[(size_t)j * TILE_W] = (uint16_t)(e - t0);
-                }
-            } else {
-                #pragma unroll 1
-                for (uint32_t j = tr; j < hi; ++j) lsuf[(size_t)j * TILE_W] = (uint16_t)(e - np1);
-            }
-            pop();
+        work_off();
+        // trailing runs: the run of the largest rank in the stack up to j
+        const uint32_t e = HIST_SHORT + (uint32_t)(g.t1 - g.t0);
+        uint32_t from = e;
+#pragma unroll 1
+        for (uint32_t j = 0; j < Kp; ++j) {
+            if (stack >> j & 1u) from = at(start, j * stride);
+            // from 0: every cell of the segment recurrent at j
+            lsuf[(size_t)j * TILE_W] = (uint16_t)(e - max(from, HIST_SHORT));
+            if (from == 0) lpre[(size_t)j * TILE_W] = (uint16_t)(e - HIST_SHORT);
         }
     }
 };
@@ -2179,8 +2212,13 @@ k_hist(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks, uint32_
     HistBody<NORM, MC, TC> body;
     body.stab = (uint2*)smem;
     body.ses = (uint32_t*)(smem + RHO_TABLE * sizeof(uint2));
-    body.stk = body.ses + RANK_MAX;
-    body.dsh = body.stk + (size_t)(Kp + 1) * blockDim.x;
+    body.start = (uint16_t*)(body.ses + RANK_MAX);
+    body.events = body.start + (size_t)Kp * blockDim.x;
+    body.dsh = (uint32_t*)(body.events + (size_t)hist_list(Kp) * blockDim.x);
+    body.start += threadIdx.x;
+    body.events += threadIdx.x;
+    body.stride = blockDim.x * 2u;
+    body.room = hist_list(Kp) * body.stride;
     body.sds = sds;
     body.rtab = rtab;
     body.works = works;
@@ -2188,6 +2226,7 @@ k_hist(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks, uint32_
     body.pre = pre;
     body.suf = suf;
     body.hist_len = hist_len;
+    body.short_end = min(HIST_SHORT, hist_len);
     body.kcap = Kp + 1;
     body.chunk_tiles = chunk_tiles;
     body.multi = false;
@@ -2197,7 +2236,7 @@ k_hist(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks, uint32_
             for (uint32_t s = 0; s < S; ++s) atomicOr(&works[s].status, 64u);
         return;
     }
-    chunk_loop(sds, S, nchunks, ticket, body, (uint32_t*)(smem + hist_lds_bytes_dev(Kp, blockDim.x)));
+    chunk_loop(sds, S, nchunks, ticket, body, (uint32_t*)(smem + hist_lds_bytes_dev(Kp, hist_list(Kp), blockDim.x)));
 }
 
 // Lines across segment borders: thread (diagonal, threshold) walks the
@@ -2270,35 +2309,45 @@ k_hist_join(const SeriesDesc* __restrict__ sds, const SeriesWork* __restrict__ w
 }
 
 // P_r(l) from the difference counts: the prefix over thresholds up to the
-// caller's threshold r (dmap), written as rows out[s][r][l] (thread per l).
+// caller's threshold r (dmap), written as rows out[s][r][l].  A workgroup takes
+// 64 lengths: their counts, contiguous, go to LDS, a thread per length sums
+// them there, and every wave writes some of the rows (reading and summing a
+// length's counts per thread and row: 72 us for four series of 20,000 lengths).
+constexpr uint32_t FINISH_LENGTHS = 64;
+
 __global__ void __launch_bounds__(256)
 k_hist_finish(const SeriesDesc* __restrict__ sds, const SeriesWork* __restrict__ works,
               const uint64_t* __restrict__ dglob, uint64_t* __restrict__ out, uint32_t hist_len, uint32_t kcap)
 {
-    const uint32_t s = blockIdx.y;
-    const uint32_t l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= hist_len) return;
-    const uint32_t K = sds[s].K;
+    __shared__ uint64_t sum[FINISH_LENGTHS * (HIST_MAX_K + 2)];
+    const uint32_t s = blockIdx.y, l0 = blockIdx.x * FINISH_LENGTHS;
+    const uint32_t lengths = min(FINISH_LENGTHS, hist_len - l0);
+    const uint32_t K = sds[s].K, row = kcap | 1u;  // odd: lengths in different banks
     const SeriesWork& w = works[s];
-    const uint64_t* d = dglob + ((size_t)s * hist_len + l) * kcap;
-    uint64_t* o = out + (size_t)s * K * hist_len + l;
-    for (uint32_t r = 0; r < K; ++r) {
-        const uint32_t top = min(w.dmap[r], kcap - 1);
+    const uint64_t* d = dglob + ((size_t)s * hist_len + l0) * kcap;
+    for (uint32_t i = threadIdx.x; i < lengths * kcap; i += blockDim.x) sum[i / kcap * row + i % kcap] = d[i];
+    __syncthreads();
+    if (threadIdx.x < lengths) {
         uint64_t acc = 0;  // two's complement: the sum of the signed differences
-        for (uint32_t j = 0; j <= top; ++j) acc += d[j];
-        o[(size_t)r * hist_len] = acc;
+        for (uint32_t j = 0; j < kcap; ++j) sum[threadIdx.x * row + j] = acc += sum[threadIdx.x * row + j];
     }
+    __syncthreads();
+    const uint32_t l = threadIdx.x % FINISH_LENGTHS;
+    if (l >= lengths) return;
+    uint64_t* o = out + (size_t)s * K * hist_len + l0 + l;
+    for (uint32_t r = threadIdx.x / FINISH_LENGTHS; r < K; r += 256 / FINISH_LENGTHS)
+        o[(size_t)r * hist_len] = sum[l * row + min(w.dmap[r], kcap - 1u)];
 }
 
 hipError_t launch_hist_finish(hipStream_t st, const DevBufs& b, const uint64_t* dglob, uint64_t* out,
                               uint32_t hist_len, uint32_t Kp)
 {
-    hipLaunchKernelGGL(k_hist_finish, dim3((hist_len + 255) / 256, b.S), dim3(256), 0, st, b.sd, b.work, dglob, out,
+    hipLaunchKernelGGL(k_hist_finish, dim3((hist_len + FINISH_LENGTHS - 1) / FINISH_LENGTHS, b.S), dim3(256), 0, st, b.sd, b.work, dglob, out,
                        hist_len, Kp + 1);
     return hipGetLastError();
 }
 
-size_t hist_lds_bytes(uint32_t Kp, uint32_t block) { return hist_lds_bytes_dev(Kp, block) + 16; }
+size_t hist_lds_bytes(uint32_t Kp, uint32_t block) { return hist_lds_bytes_dev(Kp, hist_list(Kp), block) + 16; }
 
 using HistFn = void (*)(const SeriesDesc*, uint32_t, uint32_t, uint32_t, uint32_t*, SeriesWork*, const uint2*,
                         uint64_t*, uint16_t*, uint16_t*, uint32_t, uint32_t);
