@@ -2313,37 +2313,51 @@ k_hist_join(const SeriesDesc* __restrict__ sds, const SeriesWork* __restrict__ w
 // 64 lengths: their counts, contiguous, go to LDS, a thread per length sums
 // them there, and every wave writes some of the rows (reading and summing a
 // length's counts per thread and row: 72 us for four series of 20,000 lengths).
-constexpr uint32_t FINISH_LENGTHS = 64;
-
 __global__ void __launch_bounds__(256)
 k_hist_finish(const SeriesDesc* __restrict__ sds, const SeriesWork* __restrict__ works,
-              const uint64_t* __restrict__ dglob, uint64_t* __restrict__ out, uint32_t hist_len, uint32_t kcap)
+              const uint64_t* __restrict__ dglob, uint64_t* __restrict__ out, uint32_t hist_len, uint32_t kcap,
+              uint64_t* __restrict__ stage, uint32_t stage_len, uint32_t* __restrict__ flags)
 {
-    __shared__ uint64_t sum[FINISH_LENGTHS * (HIST_MAX_K + 2)];
-    const uint32_t s = blockIdx.y, l0 = blockIdx.x * FINISH_LENGTHS;
-    const uint32_t lengths = min(FINISH_LENGTHS, hist_len - l0);
+    __shared__ uint32_t lines;
+    __shared__ uint64_t sum[HIST_BLOCK_LENGTHS * (HIST_MAX_K + 2)];
+    const uint32_t s = blockIdx.y, l0 = blockIdx.x * HIST_BLOCK_LENGTHS;
+    const uint32_t lengths = min(HIST_BLOCK_LENGTHS, hist_len - l0);
     const uint32_t K = sds[s].K, row = kcap | 1u;  // odd: lengths in different banks
     const SeriesWork& w = works[s];
     const uint64_t* d = dglob + ((size_t)s * hist_len + l0) * kcap;
     for (uint32_t i = threadIdx.x; i < lengths * kcap; i += blockDim.x) sum[i / kcap * row + i % kcap] = d[i];
     __syncthreads();
-    if (threadIdx.x < lengths) {
-        uint64_t acc = 0;  // two's complement: the sum of the signed differences
-        for (uint32_t j = 0; j < kcap; ++j) sum[threadIdx.x * row + j] = acc += sum[threadIdx.x * row + j];
+    if (threadIdx.x < HIST_BLOCK_LENGTHS) {  // one wave
+        uint64_t acc = 0, any = 0;  // two's complement: the sum of the signed differences
+        if (threadIdx.x < lengths)
+            for (uint32_t j = 0; j < kcap; ++j) {
+                sum[threadIdx.x * row + j] = acc += sum[threadIdx.x * row + j];
+                any |= acc;
+            }
+        const bool some = __any(any != 0);
+        if (threadIdx.x == 0) {
+            lines = some;
+            if (stage_len) flags[(size_t)s * gridDim.x + blockIdx.x] = some;
+        }
     }
     __syncthreads();
-    const uint32_t l = threadIdx.x % FINISH_LENGTHS;
+    const uint32_t l = threadIdx.x % HIST_BLOCK_LENGTHS;
     if (l >= lengths) return;
     uint64_t* o = out + (size_t)s * K * hist_len + l0 + l;
-    for (uint32_t r = threadIdx.x / FINISH_LENGTHS; r < K; r += 256 / FINISH_LENGTHS)
-        o[(size_t)r * hist_len] = sum[l * row + min(w.dmap[r], kcap - 1u)];
+    uint64_t* h = stage + (size_t)s * K * stage_len + l0 + l;
+    const bool staged = lines && l0 < stage_len;
+    for (uint32_t r = threadIdx.x / HIST_BLOCK_LENGTHS; r < K; r += 256 / HIST_BLOCK_LENGTHS) {
+        const uint64_t v = sum[l * row + min(w.dmap[r], kcap - 1u)];
+        o[(size_t)r * hist_len] = v;
+        if (staged) h[(size_t)r * stage_len] = v;
+    }
 }
 
 hipError_t launch_hist_finish(hipStream_t st, const DevBufs& b, const uint64_t* dglob, uint64_t* out,
-                              uint32_t hist_len, uint32_t Kp)
+                              uint32_t hist_len, uint32_t Kp, uint64_t* stage, uint32_t stage_len, uint32_t* flags)
 {
-    hipLaunchKernelGGL(k_hist_finish, dim3((hist_len + FINISH_LENGTHS - 1) / FINISH_LENGTHS, b.S), dim3(256), 0, st, b.sd, b.work, dglob, out,
-                       hist_len, Kp + 1);
+    hipLaunchKernelGGL(k_hist_finish, dim3((hist_len + HIST_BLOCK_LENGTHS - 1) / HIST_BLOCK_LENGTHS, b.S), dim3(256), 0, st, b.sd, b.work, dglob, out,
+                       hist_len, Kp + 1, stage, stage_len, flags);
     return hipGetLastError();
 }
 

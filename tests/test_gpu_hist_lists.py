@@ -48,3 +48,21 @@ def test_lists(ctx, K, kind, low):
             ref = want[:, :rows].copy()
             ref[:, -1] += want[:, rows:].sum(1).astype(ref.dtype)  # the last entry holds all longer lines
             assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("S,K", [(3, 32), (24, 32), (70, 9)])
+def test_rows_of_a_batch(ctx, S, K):
+    # lines shorter and longer than the lengths that fit the pinned staging,
+    # next to series that have short ones only
+    import torch
+    ys = [signal(("noise", "steps", "sine")[i % 3], 300 + 1000 * ((7 * i) % S) // S) for i in range(S)]
+    offs = np.concatenate([[0], np.cumsum([len(y) for y in ys])]).astype(np.uint64)
+    prm = [(1, 1, 0, 1, 2) if i % 2 else (3, 5, 1, 1, 2) for i in range(S)]
+    rr = np.tile(np.linspace(0.01, 0.4, K), (S, 1))
+    dev = torch.from_numpy(np.concatenate(ys)).to("cuda:0")
+    for rows in (1301, 129, 64):
+        print(f"[rows] S={S} K={K} rows={rows}", flush=True)
+        got = ctx.batch_hist(dev, offs, prm, rr, rows)
+        for i, y in enumerate(ys):
+            want = oracle.lines(y, *prm[i], got["eps"][i], hist_len=rows)["hist"]
+            assert np.array_equal(got["hist"][i], want), i
