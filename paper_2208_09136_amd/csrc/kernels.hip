@@ -653,7 +653,7 @@ struct SelPass1 {
         if constexpr (P1_COPIES == 1) atomicAdd(&bins[__builtin_amdgcn_ubfe(u, SEL_SH1, SEL_B1)], 1u);
         else atomicAdd(&bins[__builtin_amdgcn_ubfe(u, SEL_SH1, SEL_B1) * P1_COPIES + copy], 1u);
     }
-    __device__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
+    __device__ __forceinline__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
         copy = (uint32_t)lane & (P1_COPIES - 1);
         select_tile<NORM, MC, TC>(sd, tile_id, lane, *this);
@@ -705,7 +705,7 @@ struct SelPass2 {
     {
         atomicAdd(&bins[off != NO_BIN ? off + __builtin_amdgcn_ubfe(u, SEL_SH2, SEL_B2) : dummy], 1u);
     }
-    __device__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
+    __device__ __forceinline__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
         dummy = G * SEL_N2 + (uint32_t)lane;
         select_tile<NORM, MC, TC>(sd, tile_id, lane, *this);
@@ -790,7 +790,7 @@ struct SelPass3 {
         }
         __device__ __forceinline__ void count(uint32_t, uint32_t idx) const { wave_add(b.dst, idx, idx != P3_NONE); }
     };
-    __device__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
+    __device__ __forceinline__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
         if (over) {
             Slots v{*this};
@@ -1279,6 +1279,59 @@ __device__ __forceinline__ uint32_t code_of(uint32_t u, const CodeCtx& c)
     return *(const __attribute__((address_space(3))) uint8_t*)(size_t)off;
 }
 
+// Line values for any lmin <= LMIN_MAX, a block of HU cells at a time: the
+// largest of the last lmin values of a lane's diagonal, then the smallest of
+// the last lmin of those.  A window grows by doubling, and then by the rest of
+// lmin in powers of two: a stage takes the window from w to w + D <= 2 w values
+// with one operation per cell, and keeps its last D inputs for the next block.
+// All register indexes are constants; only which stages run depends on lmin.
+// Rings of the last 16 values, rescanned for every cell, and a key formed cell
+// by cell: 121 us for the range sweep of one N = 5003 series (m = 2, lmin = 5),
+// now 52.
+template <int HU>
+struct LineWindow {
+    static_assert(LMIN_MAX == 16 && HU >= 8, "stages");
+    uint32_t d1[1], d2[2], d4[4], d8[8], r4[4], r2[2], r1[1];
+
+    template <int D>
+    static __device__ __forceinline__ void fill(uint32_t (&h)[D], uint32_t v)
+    {
+#pragma unroll
+        for (int i = 0; i < D; ++i) h[i] = v;
+    }
+    __device__ __forceinline__ void reset(uint32_t v)
+    {
+        fill(d1, v); fill(d2, v); fill(d4, v); fill(d8, v);
+        fill(r4, v); fill(r2, v); fill(r1, v);
+    }
+    template <bool MAX, int D>
+    static __device__ __forceinline__ void stage(uint32_t (&v)[HU], uint32_t (&h)[D])
+    {
+        uint32_t tail[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i) tail[i] = v[HU - D + i];
+#pragma unroll
+        for (int u = HU - 1; u >= 0; --u) {
+            const uint32_t o = u >= D ? v[u >= D ? u - D : 0] : h[u < D ? u : 0];
+            v[u] = MAX ? max(v[u], o) : min(v[u], o);
+        }
+#pragma unroll
+        for (int i = 0; i < D; ++i) h[i] = tail[i];
+    }
+    // v[u]: over the lmin values up to the block's u-th
+    template <bool MAX>
+    __device__ __forceinline__ void apply(uint32_t (&v)[HU], uint32_t lmin)
+    {
+        if (lmin >= 2) stage<MAX>(v, d1);
+        if (lmin >= 4) stage<MAX>(v, d2);
+        if (lmin >= 8) stage<MAX>(v, d4);
+        if (lmin >= 16) stage<MAX>(v, d8);
+        if (lmin >= 8 && (lmin & 4u)) stage<MAX>(v, r4);
+        if (lmin >= 4 && (lmin & 2u)) stage<MAX>(v, r2);
+        if (lmin >= 2 && (lmin & 1u)) stage<MAX>(v, r1);
+    }
+};
+
 // Sum of a histogram row of cols (a power of two, at least 32) columns; at most
 // 2^32 - 1, as all cells counted between two flushes.  Thread j starts at column
 // j, so that neighbouring threads' rows are read from different banks.
@@ -1360,10 +1413,18 @@ struct SweepBody {
     }
     // rho, lam <= Kp: the row Kp absorbs cells that recur at no threshold, so
     // the counting is branch-free
+    __device__ __forceinline__ void emit_rho(uint32_t rho) const
+    {
+        atomicAdd((uint32_t*)((unsigned char*)brho + ((rho << csh) + lcol)), 1u);
+    }
+    __device__ __forceinline__ void emit_lam(uint32_t lam) const
+    {
+        atomicAdd((uint32_t*)((unsigned char*)blam + ((lam << csh) + lcol)), 1u);
+    }
     __device__ __forceinline__ void emit(uint32_t rho, uint32_t lam, int) const
     {
-        if constexpr (RHO) atomicAdd((uint32_t*)((unsigned char*)brho + ((rho << csh) + lcol)), 1u);
-        atomicAdd((uint32_t*)((unsigned char*)blam + ((lam << csh) + lcol)), 1u);
+        if constexpr (RHO) emit_rho(rho);
+        emit_lam(lam);
     }
     template <bool MULTI>
     __device__ __forceinline__ uint32_t rho_at(const SeriesScalars& sd, const TileGeo& g, int x) const
@@ -1374,7 +1435,7 @@ struct SweepBody {
         const uint32_t r = rho_of<MULTI>(__float_as_uint(pair_key<NORM, MC, TC>(sd.y, i, j, sd.m, sd.tau)), rc);
         return ok ? r : rc.Kp;
     }
-    __device__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
+    __device__ __forceinline__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
         if (multi) tile_impl<true>(sd, tile_id, lane);
         else tile_impl<false>(sd, tile_id, lane);
@@ -1432,34 +1493,35 @@ struct SweepBody {
                     }
                 });
         } else {
-            // general lmin <= LMIN_MAX: rings of the last lmin ranks and of the
-            // last lmin window maxima; output lags the newest rank by h = lmin-1.
+            // any lmin: the line rank of a cell is known h = lmin - 1 cells later
             const int h = (int)lmin - 1;
-            uint32_t rr[LMIN_MAX], ww[LMIN_MAX];
+            LineWindow<HU> largest, smallest;
+            largest.reset(rc.Kp);
+            smallest.reset(rc.Kp);
+            int x = max(g.t0 - h, 0);
+            auto block = [&](auto masked, const uint32_t(&k)[HU]) __attribute__((always_inline)) {
+                uint32_t r[HU];
 #pragma unroll
-            for (int i = 0; i < LMIN_MAX; ++i) { rr[i] = rc.Kp; ww[i] = rc.Kp; }
-            for (int x = g.t0 - h; x < g.t1 + h; ++x) {
-                const uint32_t r = rho_at<MULTI>(sd, g, x);
-#pragma unroll
-                for (int i = 0; i < LMIN_MAX - 1; ++i) rr[i] = rr[i + 1];
-                rr[LMIN_MAX - 1] = r;
-                uint32_t wmax = 0, rold = rc.Kp;
-#pragma unroll
-                for (int i = 0; i < LMIN_MAX; ++i) {
-                    if (i >= LMIN_MAX - 1 - h) wmax = max(wmax, rr[i]);
-                    if (i == LMIN_MAX - 1 - h) rold = rr[i];
+                for (int u = 0; u < HU; ++u) {
+                    r[u] = rho_of<MULTI>(k[u], c);
+                    if constexpr (masked)
+                        if (x + u >= g.len) r[u] = rc.Kp;
                 }
+                if constexpr (RHO) {
 #pragma unroll
-                for (int i = 0; i < LMIN_MAX - 1; ++i) ww[i] = ww[i + 1];
-                ww[LMIN_MAX - 1] = wmax;
-                if (x >= g.t0 + h) {
-                    uint32_t lam = rc.Kp;
-#pragma unroll
-                    for (int i = 0; i < LMIN_MAX; ++i)
-                        if (i >= LMIN_MAX - 1 - h) lam = min(lam, ww[i]);
-                    emit(rold, lam, lane);
+                    for (int u = 0; u < HU; ++u)
+                        if (x + u >= g.t0 && x + u < g.t1) emit_rho(r[u]);
                 }
-            }
+                largest.template apply<true>(r, lmin);
+                smallest.template apply<false>(r, lmin);
+#pragma unroll
+                for (int u = 0; u < HU; ++u)
+                    if (x + u >= g.t0 + h && x + u < g.t1 + h) emit_lam(r[u]);
+                x += HU;
+            };
+            walk<NORM, MC, TC>(
+                sd, g, x, g.t1 + h, [&](const uint32_t(&k)[HU]) { block(std::false_type{}, k); },
+                [&](const uint32_t(&k)[HU], int) { block(std::true_type{}, k); });
         }
     }
 };
@@ -1509,7 +1571,7 @@ struct RangeBody {
     uint32_t ngroups, nfine;
     bool active = true;
 
-    __device__ void begin(uint32_t s)
+    __device__ __forceinline__ void begin(uint32_t s)
     {
         const SeriesWork& w = works[s];
         active = uniform(w.range_ok) != 0;
@@ -1531,7 +1593,7 @@ struct RangeBody {
         dk = (unsigned long long*)(fineK + (size_t)s * fine_stride);
         dl = (unsigned long long*)(fineL + (size_t)s * fine_stride);
     }
-    __device__ void flush(uint32_t s)
+    __device__ __forceinline__ void flush(uint32_t s)
     {
         if (!active || LMC == 1) return;
         SeriesWork& w = works[s];
@@ -1593,7 +1655,7 @@ struct RangeBody {
     {
         return key == 0xFFFFFFFFu ? spare : code_of(key, rc);
     }
-    __device__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
+    __device__ __forceinline__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
         const TileGeo g = tile_geo(sd, tile_id, lane);
         constexpr int HU = walk_block<NORM, MC, TC>();
@@ -1676,40 +1738,52 @@ struct RangeBody {
                 sd, g, g.t0 + 1, g.t1 + 1, [&](uint32_t(&k)[HU]) { block(std::false_type{}, k, 0); },
                 [&](uint32_t(&k)[HU], int x) { block(std::true_type{}, k, x); });
         } else {
-            // general lmin <= LMIN_MAX: rings of the last lmin keys and of the
-            // last lmin window maxima (keys; ranks follow); the counted cell lags
-            // the newest key by h = lmin-1
+            // any lmin: the line value of a cell is known h = lmin - 1 cells later
             const int h = (int)lmin - 1;
-            uint32_t kk[LMIN_MAX], wk[LMIN_MAX];
+            LineWindow<HU> largest, smallest;
+            largest.reset(0xFFFFFFFFu);  // outside the diagonal: above every group
+            smallest.reset(0xFFFFFFFFu);
+            int x = max(g.t0 - h, 0);
+            auto block = [&](auto masked, uint32_t(&k)[HU]) __attribute__((always_inline)) {
+                uint32_t r[HU];
+                uint32_t acc = 0;
 #pragma unroll
-            for (int i = 0; i < LMIN_MAX; ++i) { kk[i] = 0xFFFFFFFFu; wk[i] = 0xFFFFFFFFu; }
-            for (int x = g.t0 - h; x < g.t1 + h; ++x) {
-                const uint32_t key = key_at(sd, g, x);
-#pragma unroll
-                for (int i = 0; i < LMIN_MAX - 1; ++i) kk[i] = kk[i + 1];
-                kk[LMIN_MAX - 1] = key;
-                uint32_t wmax = 0, kold = 0xFFFFFFFFu;
-#pragma unroll
-                for (int i = 0; i < LMIN_MAX; ++i) {
-                    if (i >= LMIN_MAX - 1 - h) wmax = max(wmax, kk[i]);
-                    if (i == LMIN_MAX - 1 - h) kold = kk[i];
-                }
-#pragma unroll
-                for (int i = 0; i < LMIN_MAX - 1; ++i) wk[i] = wk[i + 1];
-                wk[LMIN_MAX - 1] = wmax;
-                if (x >= g.t0 + h) {
-                    uint32_t lkey = 0xFFFFFFFFu;
-#pragma unroll
-                    for (int i = 0; i < LMIN_MAX; ++i)
-                        if (i >= LMIN_MAX - 1 - h) lkey = min(lkey, wk[i]);
-                    const uint32_t rk = code_at(kold), lam = code_at(lkey);
-                    emit(lam);
-                    if (__ballot((rk | lam) & 1u)) {
-                        fine_key(rk, kold);
-                        fine_line(lam, lkey);
+                for (int u = 0; u < HU; ++u) {
+                    r[u] = code_of(k[u], c);
+                    if constexpr (masked) {
+                        if (x + u >= g.len) {
+                            r[u] = spare;
+                            k[u] = 0xFFFFFFFFu;
+                        }
                     }
+                    acc |= r[u];
                 }
-            }
+                if (__ballot(acc & 1u)) {   // rare: an odd key code
+#pragma unroll
+                    for (int u = 0; u < HU; ++u)
+                        if (x + u >= g.t0 && x + u < g.t1 && __ballot(r[u] & 1u)) fine_key(r[u], k[u]);
+                }
+                largest.template apply<true>(k, lmin);
+                smallest.template apply<false>(k, lmin);
+                acc = 0;
+#pragma unroll
+                for (int u = 0; u < HU; ++u) {
+                    r[u] = k[u] == 0xFFFFFFFFu ? spare : code_of(k[u], c);
+                    acc |= r[u];
+                }
+#pragma unroll
+                for (int u = 0; u < HU; ++u)
+                    if (x + u >= g.t0 + h && x + u < g.t1 + h) emit(r[u]);
+                if (__ballot(acc & 1u)) {   // rare: an odd line code
+#pragma unroll
+                    for (int u = 0; u < HU; ++u)
+                        if (x + u >= g.t0 + h && x + u < g.t1 + h && __ballot(r[u] & 1u)) fine_line(r[u], k[u]);
+                }
+                x += HU;
+            };
+            walk<NORM, MC, TC>(
+                sd, g, x, g.t1 + h, [&](uint32_t(&k)[HU]) { block(std::false_type{}, k); },
+                [&](uint32_t(&k)[HU], int) { block(std::true_type{}, k); });
         }
     }
 };
@@ -1727,7 +1801,7 @@ __host__ __device__ __forceinline__ size_t sweep_lds_bytes_dev(uint32_t rows, bo
 // registers, two workgroups).  Both ranks at 100 given thresholds, N = 1e4
 // (two workgroups of 32 columns): 45 us, as one of 64 columns and 1024 threads.
 template <int NORM, int MC, int TC, int LMC, bool RHO>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6)))
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(LMC == 0 ? 4 : 6)))
 k_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
         uint32_t* __restrict__ ticket, SeriesWork* __restrict__ works, const uint2* __restrict__ rtab, uint32_t Kcap)
 {
@@ -1746,7 +1820,7 @@ k_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
     body.multi = false;
     // the generic line class reads lmin from the descriptors: launches group
     // series of one lmin
-    body.lmin = LMC == 0 ? sds[0].lmin : (uint32_t)LMC;
+    body.lmin = LMC == 0 ? uniform(sds[0].lmin) : (uint32_t)LMC;
     chunk_loop(sds, S, nchunks, ticket, body, (uint32_t*)(smem + sweep_lds_bytes_dev(Kcap, false, RHO)));
 }
 
@@ -1756,7 +1830,7 @@ k_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
 // extra waves hide the rank-table and series loads better (about 10% faster
 // at K = 20 than the four waves 105 registers allow).
 template <int NORM, int MC, int TC, int LMC>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6)))
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(LMC == 0 ? 4 : 6)))
 k_range_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
               uint32_t* __restrict__ ticket, SeriesWork* __restrict__ works, const uint2* __restrict__ rtab,
               uint32_t rows, uint64_t* __restrict__ fineK, uint64_t* __restrict__ fineL, uint32_t fine_stride)
@@ -1781,7 +1855,7 @@ k_range_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
     body.rows = rows;
     body.ngroups = 0;
     body.nfine = 0;
-    body.lmin = LMC == 0 ? sds[0].lmin : (uint32_t)LMC;
+    body.lmin = LMC == 0 ? uniform(sds[0].lmin) : (uint32_t)LMC;
     // code_of addresses the code table by its offset from LDS byte 0: the
     // kernel's dynamic LDS must start there (it has no static LDS); a launch
     // where it does not marks every series (the host reports a device error)
@@ -2910,7 +2984,7 @@ struct WinPass1 {
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     }
-    __device__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
+    __device__ __forceinline__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
         select_tile<NORM, MC, TC>(sd, tile_id, lane, *this);
     }
@@ -2951,7 +3025,7 @@ struct WinPass2 {
         const uint32_t sub = (u - lo) & ((1u << shift) - 1u);
         wave_add(dst, sl * (1u << WIN_MAX_SHIFT) + sub, sl != NO_SLOT);
     }
-    __device__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
+    __device__ __forceinline__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
         select_tile<NORM, MC, TC>(sd, tile_id, lane, *this);
     }
