@@ -1,9 +1,11 @@
 // capi.hip -- host runtime and C ABI of the averaged-RQA library (include/rqa.h).
 //
-// A call builds one descriptor per series, uploads it with the targets, and
-// runs the phases on the context stream without a host round trip:
-//   finite check -> [selection: pass 1, scan 1, pass 2, scan 2, pass 3, scan 3]
-//   -> [sweep: rank tables, line sweep] -> one copy of the results to the host.
+// A call builds one descriptor per series and runs the phases on the context
+// stream without a host round trip: set-up (descriptors, targets, clearing,
+// finite check) -> selection (pass 1, scan 1, pass 2, scan 2, or a window pass
+// and its scan) -> range sweep and its scan; or pass 3 and scan 3, and the
+// threshold sweep.  For a few series the kernels read descriptors and targets
+// from, and write results to, pinned host memory; else copies do.
 // The host then turns the integer counts into RR, DET and the averaged DET in
 // double precision.
 #include <hip/hip_runtime.h>
@@ -243,9 +245,9 @@ uint32_t segment_for(const rqa_ctx* c, uint64_t nv, const rqa_params& p, uint32_
 
 // Segment of the histogram pass: the caller's override (at most
 // HIST_MAX_SEG_HOST), else what spreads the call's pairs over eight waves per
-// CU, but at least 64 and at most 448 cells (four N = 2e4 series with 256 / 448
-// / 640: 1.45 / 1.38 / 1.39 ms); beyond, about 48 segments on the longest
-// diagonal, up to 4096 (the runs at segment borders take 4 bytes per segment,
+// CU, but at least 64 and at most 448 cells (the pass, join and rows of four N =
+// 2e4 series with 256 / 448: 1.68 / 1.62 ms, with faster lists 448 / 640: 1.38 /
+// 1.39); beyond, about 48 segments on the longest diagonal, up to 4096 (the runs at segment borders take 4 bytes per segment,
 // diagonal and threshold).
 uint32_t hist_segment_for(const rqa_ctx* c, uint64_t L0, uint64_t pairs)
 {
@@ -1002,10 +1004,11 @@ rqa_status check_flags_select(uint32_t flags, int* sel)
 // RQA_SEL_AUTO: the sample window (two passes over the pairs, exact, plain
 // fallback) for calls of at least AUTO_WINDOW_PAIRS pairs in all, else the
 // plain radix passes.  Measured on MI355X at K = 20 (ms per call, plain /
-// sample window): two N = 1e5 series 9.2 / 7.3, the 600-series ensemble
-// 12.4 / 11.3, 15 series of N = 1e4 in one call 1.54 / 1.49, ten of N = 1e3
-// 0.33 / 0.44, one N = 1e4 series 0.43 / 0.49 (the sketch and window set-up
-// cost about 0.1 ms per call).
+// sample window): ten N = 1e3 series 0.11 / 0.17, one N = 1e4 0.18 / 0.24, one
+// N = 2e4 0.32 / 0.33, nine, eleven and fifteen N = 1e4 series 0.52 / 0.48,
+// 0.59 / 0.56 and 0.76 / 0.64, two N = 1e5 7.7 / 4.7 (the sketch and window
+// set-up cost about 0.06 ms per call).  The two are level near 2^28 pairs; the
+// line is the documented one.
 constexpr uint64_t AUTO_WINDOW_PAIRS = 1ull << 29;
 
 int resolve_method(const Job& job, int sel)

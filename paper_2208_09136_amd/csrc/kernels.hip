@@ -1287,7 +1287,7 @@ __device__ __forceinline__ uint32_t code_of(uint32_t u, const CodeCtx& c)
 // All register indexes are constants; only which stages run depends on lmin.
 // Rings of the last 16 values, rescanned for every cell, and a key formed cell
 // by cell: 121 us for the range sweep of one N = 5003 series (m = 2, lmin = 5),
-// now 52.
+// now 51.
 template <int HU>
 struct LineWindow {
     static_assert(LMIN_MAX == 16 && HU >= 8, "stages");
@@ -1825,10 +1825,12 @@ k_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
 }
 
 // Six waves per SIMD (three workgroups of 512 per CU, which the LDS allows up
-// to K = 38 with 64 histogram columns and up to K = 76 with 32, in 1280-byte
+// to K = 39 with 64 histogram columns and up to K = 76 with 32, in 1280-byte
 // units): the register budget drops to 80 and a few spill, but the
 // extra waves hide the rank-table and series loads better (about 10% faster
-// at K = 20 than the four waves 105 registers allow).
+// at K = 20 than the four waves 105 registers allow).  Any other lmin holds two
+// windows besides and takes four waves of 127 registers: with 96 or 80 it spills
+// a hundred and more, and was a quarter slower.
 template <int NORM, int MC, int TC, int LMC>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(LMC == 0 ? 4 : 6)))
 k_range_sweep(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
@@ -2056,7 +2058,9 @@ hipError_t launch_sweep_prep(hipStream_t st, const DevBufs& b)
 // Instead each lane first lists the cells that do anything (a cell of rank Kp
 // after another does not).  When some lane's list may not take another block,
 // each works through its own list, a pop and a push per step: lanes wait for
-// each other once per list.
+// each other once per list (the pass over four N = 2e4 series, 20 thresholds:
+// 1.80 -> 1.30 ms).  What is left is that work: keys and ranks alone 0.25 ms,
+// with the lists 0.45; lanes of one wave differ threefold in list length.
 constexpr uint32_t HIST_SHORT = 64;     // lengths below this count in LDS
 constexpr uint32_t HIST_MAX_K = RQA_MAX_HIST_K;  // distinct thresholds
 static_assert(HIST_MAX_K == HIST_MAX_K_HOST, "histogram limits");
@@ -2070,7 +2074,8 @@ constexpr uint32_t HIST_ROW = HIST_SHORT + 1;
 // LDS of the histogram pass: rank table, thresholds, starts and lists of block
 // threads, short lines' counters.  A list takes what the LDS leaves a workgroup
 // of 1024 threads, which is what the registers allow a CU (longer lists, fewer
-// waits: 24 / 36 cells at 20 thresholds 1.26 / 1.19 ms).
+// waits: with 24 / 36 cells the pass, join and rows of four N = 2e4 series take
+// 1.45 / 1.38 ms; 16 cells in 24 waves per CU and spilled registers 1.55).
 __host__ __device__ __forceinline__ size_t hist_lds_bytes_dev(uint32_t Kp, uint32_t list, uint32_t block)
 {
     return RHO_TABLE * sizeof(uint2) + RANK_MAX * 4 + (size_t)(Kp + list) * block * 2 + (size_t)HIST_ROW * (Kp + 1) * 4;
@@ -2194,7 +2199,9 @@ struct HistBody {
             uint32_t top = lowest(stack);
             if (on && top <= r) {
                 // thresholds [top, b): none where b = top, and then the two
-                // counts below cancel
+                // counts of a short line cancel (cheaper than a test; for long
+                // lines, at high recurrence rates mostly such pops, it is not:
+                // the thresholds of RR 75 .. 98 % took 15.3 ms instead of 4.3)
                 stack &= stack - 1u;
                 const uint32_t below = lowest(stack), b = min(below, r);
                 from = at(start, top * stride);
@@ -2202,7 +2209,7 @@ struct HistBody {
                 if (l < short_end) {
                     atomicAdd(&dsh[top * HIST_ROW + l], 1u);
                     atomicAdd(&dsh[b * HIST_ROW + l], 0xFFFFFFFFu);
-                } else if (from != 0) {
+                } else if (from != 0 && top < b) {
                     const uint32_t lb = min(l, hist_len - 1u);
                     atomicAdd((unsigned long long*)&dser[(size_t)lb * kcap + top], 1ull);
                     atomicAdd((unsigned long long*)&dser[(size_t)lb * kcap + b], ~0ull);
