@@ -506,6 +506,7 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         for (uint32_t i = g.begin; i < g.end; ++i) {
             SeriesDesc& d = sd[i];
             d.ctiles = auto_chunks ? (uint32_t)std::max<uint64_t>(CT, chunk_steps / d.T) : CT;
+            d.ctiles = std::min(d.ctiles, chunk_tiles_limit(d.T));
             d.nchunks = (d.ntiles + d.ctiles - 1) / d.ctiles;
             d.chunk_begin = g.nchunks;  // chunk numbering restarts in every group
             g.nchunks += d.nchunks;

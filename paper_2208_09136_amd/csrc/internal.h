@@ -6,12 +6,9 @@
 #include <stdint.h>
 
 #include "../../include/rqa.h"
+#include "shape.h"
 
 namespace rqa {
-
-// One wavefront walks a band of TILE_W consecutive diagonals; lane L owns
-// diagonal d0 + L and steps along it.
-constexpr int TILE_W = 64;
 
 // Radix split of the 31 significant bits of a key (the sign bit is always 0):
 // pass 1 histograms the top SEL_B1 bits for every pair; pass 2 the next SEL_B2
@@ -221,6 +218,7 @@ size_t hist_lds_bytes(uint32_t Kp, uint32_t block);
 int hist_blocks_per_cu(int select_variant, uint32_t Kp, uint32_t block);
 constexpr uint32_t HIST_MAX_K_HOST = RQA_MAX_HIST_K;
 constexpr uint32_t HIST_MAX_SEG_HOST = 32768;
+static_assert(chunk_tiles_limit(HIST_MAX_SEG_HOST) >= 1024 / TILE_W, "a histogram chunk: a tile per wave");
 // Window selection.  Sources of the window: predicted offsets [S][20] with
 // half-widths (network), or the sorted sketch sample (sample quantiles).
 struct WinBufs {

@@ -483,7 +483,8 @@ hipError_t launch_pack_results(hipStream_t st, const DevBufs& b, bool lines, uin
 // without a barrier until the series changes; the last quarter is drawn chunk
 // by chunk from a ticket, so that all workgroups end together.  Per-series LDS
 // state is switched, and accumulated counts are flushed, when the series
-// changes, when 32-bit LDS counters could overflow, and at the end.  With every
+// changes, when 32-bit LDS counters could overflow (a single chunk's cells fit
+// them: chunk_tiles_limit), and at the end.  With every
 // chunk drawn from the ticket, a workgroup moved to another series at nearly
 // every chunk (fifteen N = 1e4 series: window pass 520 us, most of it flushes
 // of 39,936 bins) and paid a ticket, two barriers and the wait for the chunk's
