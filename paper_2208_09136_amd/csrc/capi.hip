@@ -648,15 +648,35 @@ rqa_status run_job(rqa_ctx* c, Job& job)
             h_tgt[(size_t)i * K + r] = !has_tgt ? 0 : as_rank ? job.k[(size_t)s * K + r] : job.eps_bits[(size_t)s * K + r];
     }
 
+    // what a launch may not fit is found before the first one, so that no call
+    // ends between its launches
+    uint32_t slots2 = 1, ngroups2 = 1;  // pass 2: targets counted per launch row, rows
+    if (radix) {
+        if (!pass2_slots(c, K, &slots2)) return fail(RQA_ERR_UNSUPPORTED, "pass 2 does not fit the LDS");
+        ngroups2 = (K + slots2 - 1) / slots2;
+        if (!fused && select_lds_bytes(3, K, 0) > c->max_lds)
+            return fail(RQA_ERR_UNSUPPORTED, "K=%u does not fit the LDS of pass 3", K);
+    }
+    const size_t launches = (window ? (fused ? 1 : 2) : radix ? 1 + ngroups2 + (fused ? 0 : 1) : 0) + (hist ? 1 : 0) +
+                            ((job.mode & MODE_SWEEP) || fused ? 1 : 0);
+    if (groups.size() * launches > (size_t)NUM_TICKETS)
+        return fail(RQA_ERR_UNSUPPORTED, "too many kernel launches in one call");
+
     Timer tm(c);
     hipStream_t sm = c->stream;
-    // on an early return the kernels already launched may still read the
-    // staging, which the next call overwrites
+    // on an early return (a device error) the kernels already launched, on both
+    // streams, may still use the staging and the scratch, which the next call
+    // overwrites
     struct Drain {
-        hipStream_t s;
+        rqa_ctx* c;
         bool armed;
-        ~Drain() { if (armed) (void)hipStreamSynchronize(s); }
-    } drain{sm, true};
+        ~Drain()
+        {
+            if (!armed) return;
+            if (c->aux) (void)hipStreamSynchronize(c->aux);
+            (void)hipStreamSynchronize(c->stream);
+        }
+    } drain{c, true};
     HIP_TRY(tm.begin(PH_OTHER));
     // A few series: kernels read descriptors and targets from the pinned
     // staging and write the results there, over the bus, instead of waiting for
@@ -705,9 +725,8 @@ rqa_status run_job(rqa_ctx* c, Job& job)
     };
 
     uint32_t ticket = 0;
-    auto take = [&](uint32_t n) -> int {
-        if (ticket + n > (uint32_t)NUM_TICKETS) return -1;
-        int t = (int)ticket;
+    auto take = [&](uint32_t n) {
+        const uint32_t t = ticket;
         ticket += n;
         return t;
     };
@@ -750,9 +769,8 @@ rqa_status run_job(rqa_ctx* c, Job& job)
                 const int per_cu = window_blocks_per_cu(pass, var, block);
                 const uint32_t grid = c->grid ? c->grid
                                               : std::max<uint32_t>(1, std::min<uint32_t>(g.nchunks, (uint32_t)(c->num_cu * per_cu)));
-                const int t = take(1);
-                if (t < 0) return fail(RQA_ERR_UNSUPPORTED, "too many kernel launches in one call");
-                HIP_TRY(launch_window_pass(gstream(gi), v, wv, pass, var, grid, block, (uint32_t)t));
+                const uint32_t t = take(1);
+                HIP_TRY(launch_window_pass(gstream(gi), v, wv, pass, var, grid, block, t));
             }
             HIP_TRY(join());
             HIP_TRY(tm.end());
@@ -772,10 +790,8 @@ rqa_status run_job(rqa_ctx* c, Job& job)
                 uint32_t block = 512;
                 uint32_t G = 1, ngroups = 1;
                 if (pass == 2) {
-                    if (!pass2_slots(c, K, &G)) return fail(RQA_ERR_UNSUPPORTED, "pass 2 does not fit the LDS");
-                    ngroups = (K + G - 1) / G;
-                } else if (pass == 3 && select_lds_bytes(3, K, 0) > c->max_lds) {
-                    return fail(RQA_ERR_UNSUPPORTED, "K=%u does not fit the LDS of pass 3", K);
+                    G = slots2;
+                    ngroups = ngroups2;
                 }
                 const size_t lds = select_lds_bytes(pass, K, G);
                 int per_cu = select_blocks_per_cu(pass, var, block, lds);
@@ -784,9 +800,8 @@ rqa_status run_job(rqa_ctx* c, Job& job)
                 if (pass == 2 && per_cu == 1) block = 1024;
                 const uint32_t grid = c->grid ? c->grid
                                               : std::max<uint32_t>(1, std::min<uint32_t>(g.nchunks, (uint32_t)(c->num_cu * per_cu)));
-                const int t = take(ngroups);
-                if (t < 0) return fail(RQA_ERR_UNSUPPORTED, "too many kernel launches in one call");
-                HIP_TRY(launch_select_pass(gstream(gi), v, pass, var, grid, block, ngroups, G, (uint32_t)t));
+                const uint32_t t = take(ngroups);
+                HIP_TRY(launch_select_pass(gstream(gi), v, pass, var, grid, block, ngroups, G, t));
             }
             HIP_TRY(join());
             HIP_TRY(tm.end());
@@ -808,13 +823,12 @@ rqa_status run_job(rqa_ctx* c, Job& job)
             const int per_cu = hist_blocks_per_cu(g.sel, job.hist_kp, hist_block);
             const uint32_t grid = c->grid ? c->grid
                                           : std::max<uint32_t>(1, std::min<uint32_t>(g.nchunks, (uint32_t)(c->num_cu * per_cu)));
-            const int t = take(1);
-            if (t < 0) return fail(RQA_ERR_UNSUPPORTED, "too many kernel launches in one call");
+            const uint32_t t = take(1);
             uint64_t* dg = (uint64_t*)(pool + o_dh) + (size_t)g.begin * job.hist_len * kc;
             uint16_t* pre = (uint16_t*)(pool + o_pre) + g_tile[gi] * kc * TILE_W;
             uint16_t* suf = (uint16_t*)(pool + o_suf) + g_tile[gi] * kc * TILE_W;
             HIP_TRY(launch_hist(gstream(gi), v, g.sel, grid, hist_block, dg, pre, suf, job.hist_len, job.hist_kp,
-                                (uint32_t)t));
+                                t));
             uint32_t items = 1;
             for (uint32_t i = g.begin; i < g.end; ++i) items = std::max(items, sd[i].B * ((job.hist_kp + 3) / 4));
             const uint32_t jgrid = std::min<uint32_t>(items, (uint32_t)c->num_cu * 4);
@@ -841,9 +855,8 @@ rqa_status run_job(rqa_ctx* c, Job& job)
             const int per_cu = sweep_blocks_per_cu(g.swp, fused, rho, block, lds);
             const uint32_t grid = c->grid ? c->grid
                                           : std::max<uint32_t>(1, std::min<uint32_t>(g.nchunks, (uint32_t)(c->num_cu * per_cu)));
-            const int t = take(1);
-            if (t < 0) return fail(RQA_ERR_UNSUPPORTED, "too many kernel launches in one call");
-            HIP_TRY(launch_sweep(gstream(gi), v, g.swp, fused, rho, grid, block, (uint32_t)t));
+            const uint32_t t = take(1);
+            HIP_TRY(launch_sweep(gstream(gi), v, g.swp, fused, rho, grid, block, t));
         }
         HIP_TRY(join());
         HIP_TRY(tm.end());
