@@ -2080,7 +2080,19 @@ rqa_status rqa_mlp_forward(rqa_ctx* c, const float* x_dev, uint32_t B, float* y_
     rqa_status st = check_model(c, B);
     if (st) return st;
     if (!x_dev || !y_dev) return fail(RQA_ERR_INVALID_ARG, "a device pointer is NULL");
-    HIP_TRY(mlp_forward(c->stream, c->mlp, x_dev, (int)B, y_dev));
+    // a workgroup writes its rows while others still read theirs: an output that
+    // shares memory with the input is formed elsewhere first
+    const uintptr_t xb = (uintptr_t)x_dev, yb = (uintptr_t)y_dev;
+    const bool shared = xb < yb + sizeof(float) * MLP_OUT * (size_t)B && yb < xb + sizeof(float) * MLP_IN * (size_t)B;
+    float* y = y_dev;
+    if (shared) {
+        MlpActs a;
+        if ((st = ensure_acts(c, B, a))) return st;
+        y = a.dY;
+    }
+    HIP_TRY(mlp_forward(c->stream, c->mlp, x_dev, (int)B, y));
+    if (shared)
+        HIP_TRY(hipMemcpyAsync(y_dev, y, sizeof(float) * MLP_OUT * (size_t)B, hipMemcpyDeviceToDevice, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return RQA_OK;
 }
