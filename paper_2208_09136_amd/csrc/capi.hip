@@ -210,29 +210,6 @@ TuneKey tune_key(uint64_t nv, const rqa_params& p, uint32_t K)
     return {log2_floor(nv), variant_of(p.norm, p.m, p.tau, p.lmin), K <= 32 ? 0 : 1};
 }
 
-// Default segment length when nothing is tuned, from the work of the whole call
-// (pairs over all series) per wave of one 8-wave workgroup on every CU: a call
-// with up to 512 steps for each gives each one tile, so that no CU waits for a
-// second round of short tiles; a larger one about six, of 256 to 1024 steps.
-// Measured (us per call, K = 20, m = 1 unless said): one N = 1e4 series
-// (381 steps) T = 128 / 256 / 512 / 1024: 233 / 181 / 175 / 231; twenty
-// N = 3000 (686): 128 / 256 / 512: 339 / 289 / 326; N = 30,000 (3433): 128 /
-// 512 / 1024: 549 / 510 / 547; the 600-series ensemble (87,000): 128 / 512 /
-// 960: 6663 / 6331 / 5796.  From the walker's unit on (the two half-blocks of
-// its ring and 64: 320 for m = 3, tau = 5, 192 for tau = 3, 64 else) a multiple
-// of it, so that no segment ends with a part of a half-block, which takes the
-// walker's edge path (two N = 1e5 series, tau = 5: 512 / 640: 5337 / 4787).
-uint32_t default_segment(uint64_t pairs, int num_cu, const rqa_params& p)
-{
-    const uint64_t steps = pairs / TILE_W / ((uint64_t)num_cu * 8);
-    // an eighth more than its share, or a few workgroups would not find a CU
-    if (steps <= 512) return (uint32_t)((steps * 9 / 8 + 63) / 64 * 64 + (steps ? 0 : 64));
-    const uint64_t t = std::min<uint64_t>(std::max<uint64_t>(steps / 6, 256), 1024);
-    const int cls = select_variant_of(p.norm, p.m, p.tau) % NUM_MCLASS;
-    const uint64_t unit = cls == 3 ? 320 : cls == 2 ? 192 : 64;
-    return (uint32_t)(t >= unit ? t / unit * unit : t / 64 * 64);
-}
-
 constexpr uint32_t DEFAULT_CHUNK = 8;
 
 uint32_t segment_for(const rqa_ctx* c, uint64_t nv, const rqa_params& p, uint32_t K, uint64_t pairs)
@@ -240,7 +217,9 @@ uint32_t segment_for(const rqa_ctx* c, uint64_t nv, const rqa_params& p, uint32_
     if (c->seg) return c->seg;
     auto it = c->tune.find(tune_key(nv, p, K));
     if (it != c->tune.end()) return it->second.seg;
-    return default_segment(pairs, c->num_cu, p);
+    // the walker's unit of the embedding class
+    const int cls = select_variant_of(p.norm, p.m, p.tau) % NUM_MCLASS;
+    return default_segment(nv - p.theiler, pairs, c->num_cu, cls == 3 ? 320 : cls == 2 ? 192 : 64);
 }
 
 // Segment of the histogram pass: the caller's override (at most
@@ -474,8 +453,8 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         d.q = T / TILE_W;
         d.B = (uint32_t)((L0 + TILE_W - 1) / TILE_W);
         d.Smax = (uint32_t)((L0 + T - 1) / T);
-        const uint64_t ntiles = (uint64_t)d.Smax * d.B - (uint64_t)d.q * ((uint64_t)d.Smax * (d.Smax - 1) / 2);
-        if (ntiles >= (1ull << 31)) return fail(RQA_ERR_UNSUPPORTED, "too many tiles; raise the segment length");
+        const uint64_t ntiles = tile_count(L0, T);
+        if (ntiles >= MAX_TILES) return fail(RQA_ERR_UNSUPPORTED, "too many tiles; raise the segment length");
         d.ntiles = (uint32_t)ntiles;
         d.variant = (uint32_t)swp_var[s];
         d.seed = job.seed + s;
