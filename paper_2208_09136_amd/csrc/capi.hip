@@ -1151,6 +1151,7 @@ void finish_lines(Job& job)
 #endif
 constexpr uint32_t FUSED_MAX_K_PLAIN = RQA_FUSED_MAX_K_PLAIN;
 constexpr uint32_t FUSED_MAX_K_WINDOW = RQA_FUSED_MAX_K_WINDOW;
+static_assert(2 * FUSED_MAX_K_PLAIN <= 255 && 2 * FUSED_MAX_K_WINDOW <= 255, "a code of the range sweep is one byte");
 
 bool use_fused(const rqa_ctx* c, uint32_t K, int sel)
 {
