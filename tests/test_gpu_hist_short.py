@@ -26,3 +26,25 @@ def test_row_lengths(hist_len, m, tau, norm):
             want = oracle.lines(y, m, tau, norm, w, 2, eps, hist_len=hist_len)
             assert np.array_equal(got["hist"], want["hist"]), (w, segment)
             assert np.array_equal(got["det"], want["det"])
+
+
+@pytest.mark.parametrize("kind", ["sine", "constant", "staircase", "two_values"])
+@pytest.mark.parametrize("n", [64, 1500])
+def test_runs_of_one_rank(kind, n):
+    # neighbouring cells of equal rank, across blocks, full lists and segments
+    import torch
+    from paper_2208_09136_amd import rqa
+    t = np.arange(n)
+    y = {"sine": np.sin(2 * np.pi / 37.3 * t), "constant": 0 * t, "staircase": np.floor(t / 13) % 17,
+         "two_values": (t // 9) % 2}[kind].astype(np.float32)
+    dev = torch.from_numpy(y).cuda()
+    with rqa.Context(0, torch.cuda.current_stream()) as ctx:
+        for p in ((1, 1, 0, 1, 2), (3, 3, 1, 2, 2), (2, 2, 0, 1, 2)):
+            eps = np.sort(np.concatenate([oracle.select(y, *p[:4], np.linspace(0.05, 1.0, 9))[0], [0.0, 0.5, 50.0]]))
+            want = oracle.lines(y, *p, eps.astype(np.float32), hist_len=n + 1)["hist"]
+            for segment in (0, 64, 1024):
+                print(f"[runs] {kind} n={n} {p} segment={segment}", flush=True)
+                ctx.set_shape(segment, 0)
+                got = ctx.det_curve(dev, p, eps, hist_len=n + 1)["hist"]
+                ctx.set_shape(0, 0)
+                assert np.array_equal(got, want)
