@@ -479,17 +479,21 @@ hipError_t launch_pack_results(hipStream_t st, const DevBufs& b, bool lines, uin
 // Work loop shared by the counting kernels (s_chunk_slot: one LDS word shared
 // by the workgroup).  The launch's chunks (chunk_begin, nchunks and ctiles of
 // the series) are worked on in two parts: first every workgroup takes its own
-// run of consecutive chunks, three quarters of them in all, without tickets and
-// without a barrier until the series changes; the last quarter is drawn chunk
-// by chunk from a ticket, so that all workgroups end together.  Per-series LDS
-// state is switched, and accumulated counts are flushed, when the series
-// changes, when 32-bit LDS counters could overflow (a single chunk's cells fit
-// them: chunk_tiles_limit), and at the end.  With every
-// chunk drawn from the ticket, a workgroup moved to another series at nearly
-// every chunk (fifteen N = 1e4 series: window pass 520 us, most of it flushes
-// of 39,936 bins) and paid a ticket, two barriers and the wait for the chunk's
-// slowest wave for each.  Now: that window pass 230 us, the 600-series ensemble
-// 6.74 -> 5.98 ms, one N = 30,000 series 614 -> 572 us per call.
+// run of consecutive chunks, half of them in all, without tickets and without a
+// barrier until the series changes; the other half is drawn chunk by chunk from
+// a ticket, so that all workgroups end together.  Per-series LDS state is
+// switched, and accumulated counts are flushed, when the series changes, when
+// 32-bit LDS counters could overflow (a single chunk's cells fit them:
+// chunk_tiles_limit), and at the end.  With every chunk drawn from the ticket, a
+// workgroup moved to another series at nearly every chunk (fifteen N = 1e4
+// series: window pass 520 us, most of it flushes of 39,936 bins) and paid a
+// ticket, two barriers and the wait for the chunk's slowest wave for each; that
+// window pass now takes 260 us.  A half: the workgroups of drawn chunks work near
+// each other and share the row samples in the scalar cache, those of own runs do
+// not.  With a quarter / a half / three quarters in own runs (ms): one N = 1e5
+// series at 20 given thresholds 1.73 / 1.74 / 1.86, two N = 1e5 series 4.66 /
+// 4.63 / 4.67, a hundred N = 1e4 series at K = 99 5.34 / 5.21 / 5.40, the
+// 600-series ensemble 6.08 / 6.05 / 6.02.
 template <class Body>
 __device__ __forceinline__ void chunk_loop(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
                                            uint32_t* __restrict__ ticket, Body& body, uint32_t* s_chunk_slot)
@@ -505,7 +509,7 @@ __device__ __forceinline__ void chunk_loop(const SeriesDesc* __restrict__ sds, u
     // own run [c, own_end), then tickets from W * per on; with a workgroup per
     // chunk there is nothing left to draw
     const bool one_each = nchunks <= W;
-    const uint32_t per = one_each ? 1u : (uint32_t)((uint64_t)nchunks * 3 / 4 / W);
+    const uint32_t per = one_each ? 1u : nchunks / 2u / W;
     uint32_t c = min(blockIdx.x * per, nchunks);
     const uint32_t own_end = min(c + per, nchunks);
     SeriesScalars ss{};
