@@ -212,14 +212,14 @@ TuneKey tune_key(uint64_t nv, const rqa_params& p, uint32_t K)
 
 constexpr uint32_t DEFAULT_CHUNK = 8;
 
-uint32_t segment_for(const rqa_ctx* c, uint64_t nv, const rqa_params& p, uint32_t K, uint64_t pairs)
+uint32_t segment_for(const rqa_ctx* c, uint64_t nv, const rqa_params& p, uint32_t K, uint64_t pairs, uint32_t tiles)
 {
     if (c->seg) return c->seg;
     auto it = c->tune.find(tune_key(nv, p, K));
     if (it != c->tune.end()) return it->second.seg;
     // the walker's unit of the embedding class
     const int cls = select_variant_of(p.norm, p.m, p.tau) % NUM_MCLASS;
-    return default_segment(nv - p.theiler, pairs, c->num_cu, cls == 3 ? 320 : cls == 2 ? 192 : 64);
+    return default_segment(nv - p.theiler, pairs, c->num_cu, cls == 3 ? 320 : cls == 2 ? 192 : 64, tiles);
 }
 
 // Segment of the histogram pass: the caller's override (at most
@@ -426,6 +426,7 @@ rqa_status run_job(rqa_ctx* c, Job& job)
     std::vector<Group> groups;
     uint64_t pairs = 0;
     for (uint64_t m : job.M) pairs += m;
+    const uint32_t tiles = S == 1 && (job.mode & MODE_SELECT) && job.sel != 0 ? 9 : 6;  // see default_segment
     uint32_t maxn = 0;
     for (uint32_t i = 0; i < S; ++i) {
         const uint32_t s = order[i];
@@ -438,7 +439,7 @@ rqa_status run_job(rqa_ctx* c, Job& job)
         const uint64_t nv = z.n - (uint64_t)(z.p.m - 1) * z.p.tau;
         const uint64_t L0 = nv - z.p.theiler;
         SeriesDesc& d = sd[i];
-        const uint32_t T = hist ? hist_segment_for(c, L0, pairs) : segment_for(c, nv, z.p, K, pairs);
+        const uint32_t T = hist ? hist_segment_for(c, L0, pairs) : segment_for(c, nv, z.p, K, pairs, tiles);
         d.y = job.base + z.offset;
         d.n = (uint32_t)z.n;
         d.nv = (uint32_t)nv;

@@ -27,13 +27,14 @@ int main()
     // nowhere below, whatever the walker's unit
     const uint64_t longest = 16776640;
     if (tile_count(longest, 1024) >= MAX_TILES || tile_count(longest + 64, 1024) < MAX_TILES) return std::printf("limit\n");
+    for (uint32_t tiles : {6u, 9u})
     for (uint32_t unit : {64u, 192u, 320u})
         for (int cus : {1, 64, 256})
             for (uint64_t L0 = 1; L0 <= longest + 64; L0 += L0 < 16200000 ? L0 / 50 + 1 : 64) {
-                const uint32_t T = default_segment(L0, L0 * (L0 + 1) / 2, cus, unit);
+                const uint32_t T = default_segment(L0, L0 * (L0 + 1) / 2, cus, unit, tiles);
                 if (T < 64 || T > 1024 || T % 64) return std::printf("segment %u of %lu\n", T, L0);
                 if ((tile_count(L0, T) < MAX_TILES) != (L0 <= longest)) return std::printf("refused %lu unit %u\n", L0, unit);
-                if (L0 > 300000 && L0 < 16200000 && T != 1024 / unit * unit) return std::printf("unit %u of %lu\n", unit, L0);
+                if (L0 > 450000 && L0 < 16200000 && T != 1024 / unit * unit) return std::printf("unit %u of %lu\n", unit, L0);
             }
     std::printf("ok\n");
 }
