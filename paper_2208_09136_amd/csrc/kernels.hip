@@ -555,32 +555,60 @@ __device__ __forceinline__ void chunk_loop(const SeriesDesc* __restrict__ sds, u
     if (cur != 0xFFFFFFFFu) body.flush(cur);
 }
 
-// Adds 1 to slot base[idx] for every active lane.  Usually one or two lanes hit:
-// a lane alone adds directly, without the twenty instructions of the search for
-// ties (K = 99, N = 30,000: pass 3 0.28 -> 0.21 ms, window pass 2 0.41 -> 0.34).
-// Several lanes merge into one atomic per distinct idx, however few they are:
-// series of few distinct values (integers, an analogue-digital converter's
-// steps) wait for atomics on few addresses, whose number is what counts (K = 20,
-// N = 5000 of 20 and of 300 values: an atomic per lane up to eight lanes 7.47 and
-// 2.78 ms per call, merged 2.46 and 2.10; three targets, N = 10,000: pass 3 18.3
-// and 7.9 ms).
-__device__ __forceinline__ void wave_add(unsigned long long* base, uint32_t idx, bool active)
+// Keeps, of the active lanes with equal idx, the first one active and returns
+// their number to it.  Called by any lanes together: the leaders are among them.
+__device__ __forceinline__ uint32_t merge_lanes(uint32_t idx, bool& active, uint32_t& distinct)
 {
     uint64_t mask = __ballot(active);
-    if (!mask) return;
     uint32_t n = 1;
-    if (__builtin_expect((mask & (mask - 1)) != 0, 0)) {
-        do {
-            const int leader = __ffsll((unsigned long long)mask) - 1;
-            const uint32_t li = __builtin_amdgcn_readlane(idx, leader);
-            const bool mine = active && idx == li;
-            const uint64_t same = __ballot(mine);
-            if (mine) {
-                n = (uint32_t)__popcll(same);
-                active = (int)__lane_id() == leader;
-            }
-            mask &= ~same;
-        } while (mask);
+    distinct = 0;
+    while (mask) {
+        const int leader = __ffsll((unsigned long long)mask) - 1;
+        const uint32_t li = __builtin_amdgcn_readlane(idx, leader);
+        const bool mine = active && idx == li;
+        const uint64_t same = __ballot(mine);
+        if (mine) {
+            n = (uint32_t)__popcll(same);
+            active = (int)__lane_id() == leader;
+        }
+        mask &= ~same;
+        ++distinct;
+    }
+    return n;
+}
+
+// Adds 1 to slot base[idx] for every active lane.  Usually one or two lanes hit:
+// a lane alone adds directly, without the twenty instructions of the search for
+// ties (K = 99, N = 30,000: pass 3 0.28 -> 0.21 ms).  Several lanes merge into one
+// atomic per distinct idx, however few they are: series of few distinct values
+// (integers, an analogue-digital converter's steps) wait for atomics on few
+// addresses, whose number is what counts (K = 20, N = 5000 of 20 and of 300
+// values: an atomic per lane up to eight lanes 7.47 and 2.78 ms per call, merged
+// 2.46 and 2.10; three targets, N = 10,000: pass 3 18.3 and 7.9 ms).
+__device__ __forceinline__ void wave_add(unsigned long long* base, uint32_t idx, bool active)
+{
+    const uint64_t mask = __ballot(active);
+    if (!mask) return;
+    uint32_t n = 1, distinct;
+    if (__builtin_expect((mask & (mask - 1)) != 0, 0)) n = merge_lanes(idx, active, distinct);
+    if (active) atomicAdd(base + idx, (unsigned long long)n);
+}
+
+// wave_add for a path where several lanes hit often (window pass 2, whose
+// bins are wider): up to FEW_LANES add by themselves until merge, a flag of the
+// wave, says that its lanes tie; more lanes merge always and set it anew.  K = 99,
+// N = 30,000 and 52,000: pass 0.34 -> 0.26 and 0.86 -> 0.74 ms; three targets, N =
+// 10,000 of 300 values, 18.6 ms with an atomic per lane, 7.9 with either form.
+constexpr uint32_t FEW_LANES = 4;
+__device__ __forceinline__ void wave_add(unsigned long long* base, uint32_t idx, bool active, bool& merge)
+{
+    const uint64_t mask = __ballot(active);
+    if (!mask) return;
+    const uint32_t lanes = (uint32_t)__popcll(mask);
+    uint32_t n = 1, distinct;
+    if (lanes > (merge ? 1u : FEW_LANES)) {
+        n = merge_lanes(idx, active, distinct);
+        if (lanes > FEW_LANES) merge = distinct < lanes;
     }
     if (active) atomicAdd(base + idx, (unsigned long long)n);
 }
@@ -596,7 +624,9 @@ __device__ __attribute__((noinline)) void fine_add(unsigned long long* base, uin
 
 // Shared tile driver of the counting passes.  For every cell of the lane's
 // diagonal in the tile: look = body.look(key) (LDS table reads, issued for a
-// whole block of keys first), then body.count(key, look).
+// whole block of keys first), then body.count(key, look, on).  The whole wave
+// calls count; on says which lanes have a cell, so that wave-uniform state that
+// count keeps stays the same in all lanes.
 template <int NORM, int MC, int TC, class Body>
 __device__ __forceinline__ void select_tile(const SeriesScalars& sd, uint32_t tile_id, int lane, Body& body)
 {
@@ -610,15 +640,14 @@ __device__ __forceinline__ void select_tile(const SeriesScalars& sd, uint32_t ti
 #pragma unroll
             for (int u = 0; u < HU; ++u) lk[u] = body.look(k[u]);
 #pragma unroll
-            for (int u = 0; u < HU; ++u) body.count(k[u], lk[u]);
+            for (int u = 0; u < HU; ++u) body.count(k[u], lk[u], true);
         },
         [&](const uint32_t(&k)[HU], int x) {
             uint32_t lk[HU];
 #pragma unroll
             for (int u = 0; u < HU; ++u) lk[u] = body.look(k[u]);
 #pragma unroll
-            for (int u = 0; u < HU; ++u)
-                if (x + u < lim) body.count(k[u], lk[u]);
+            for (int u = 0; u < HU; ++u) body.count(k[u], lk[u], x + u < lim);
         });
 }
 
@@ -660,8 +689,9 @@ struct SelPass1 {
         }
     }
     __device__ __forceinline__ uint32_t look(uint32_t) const { return 0u; }
-    __device__ __forceinline__ void count(uint32_t u, uint32_t) const
+    __device__ __forceinline__ void count(uint32_t u, uint32_t, bool on) const
     {
+        if (!on) return;
         if constexpr (P1_COPIES == 1) atomicAdd(&bins[__builtin_amdgcn_ubfe(u, SEL_SH1, SEL_B1)], 1u);
         else atomicAdd(&bins[__builtin_amdgcn_ubfe(u, SEL_SH1, SEL_B1) * P1_COPIES + copy], 1u);
     }
@@ -713,8 +743,9 @@ struct SelPass2 {
     // keys outside this group's target buckets count into a spare word per
     // lane, so the count needs no branch (and no divergence)
     uint32_t dummy = 0;
-    __device__ __forceinline__ void count(uint32_t u, uint32_t off) const
+    __device__ __forceinline__ void count(uint32_t u, uint32_t off, bool on) const
     {
+        if (!on) return;
         atomicAdd(&bins[off != NO_BIN ? off + __builtin_amdgcn_ubfe(u, SEL_SH2, SEL_B2) : dummy], 1u);
     }
     __device__ __forceinline__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
@@ -789,7 +820,7 @@ struct SelPass3 {
             const uint32_t ent = hx ? e.x : e.y;
             return (hx || hy) ? ((ent & 127u) << SEL_B3) | lo : P3_NONE;
         }
-        __device__ __forceinline__ void count(uint32_t, uint32_t idx) const { wave_add(b.dst, idx, idx != P3_NONE); }
+        __device__ __forceinline__ void count(uint32_t, uint32_t idx, bool on) const { wave_add(b.dst, idx, on && idx != P3_NONE); }
     };
     struct Slots {
         const SelPass3& b;
@@ -800,7 +831,7 @@ struct SelPass3 {
             const uint32_t s3 = b.gT2[s2 * SEL_N2 + __builtin_amdgcn_ubfe(u, SEL_SH2, SEL_B2)];
             return s3 != NO_SLOT ? s3 * SEL_N3 + (u & (SEL_N3 - 1)) : P3_NONE;
         }
-        __device__ __forceinline__ void count(uint32_t, uint32_t idx) const { wave_add(b.dst, idx, idx != P3_NONE); }
+        __device__ __forceinline__ void count(uint32_t, uint32_t idx, bool on) const { wave_add(b.dst, idx, on && idx != P3_NONE); }
     };
     __device__ __forceinline__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
@@ -3003,11 +3034,11 @@ struct WinPass1 {
     // window key v in bin ((v - win_lo) >> shift) + 1.  A branch: most keys
     // lie above the window, and an atomic per key would cost more than the
     // divergence.
-    __device__ __forceinline__ void count(uint32_t u, uint32_t)
+    __device__ __forceinline__ void count(uint32_t u, uint32_t, bool on)
     {
         // the bins sit at LDS byte 0 (k_window checks it): the bin's byte
         // offset is its LDS address
-        if (u <= hi) {
+        if (on && u <= hi) {
             const uint32_t a = (__builtin_elementwise_sub_sat(u, base) >> sh2) & ~3u;
             __hip_atomic_fetch_add((__attribute__((address_space(3))) uint32_t*)(size_t)a, 1u, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -3030,10 +3061,12 @@ struct WinPass2 {
     uint32_t K;
     uint32_t lo, span, shift;
     unsigned long long* dst;
+    bool merge = false;   // see wave_add
     bool active = true;
     __device__ void begin(uint32_t s)
     {
         const SeriesWork& w = works[s];
+        merge = false;
         lo = uniform(w.win_lo);
         span = uniform(w.win_span);
         shift = uniform(w.win_shift);
@@ -3049,10 +3082,10 @@ struct WinPass2 {
         const uint32_t sl = table[fb];
         return rel <= span ? sl : (uint32_t)NO_SLOT;
     }
-    __device__ __forceinline__ void count(uint32_t u, uint32_t sl) const
+    __device__ __forceinline__ void count(uint32_t u, uint32_t sl, bool on)
     {
         const uint32_t sub = (u - lo) & ((1u << shift) - 1u);
-        wave_add(dst, sl * (1u << WIN_MAX_SHIFT) + sub, sl != NO_SLOT);
+        wave_add(dst, sl * (1u << WIN_MAX_SHIFT) + sub, on && sl != NO_SLOT, merge);
     }
     __device__ __forceinline__ void tile(const SeriesScalars& sd, uint32_t tile_id, int lane)
     {
