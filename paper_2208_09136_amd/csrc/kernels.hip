@@ -479,21 +479,23 @@ hipError_t launch_pack_results(hipStream_t st, const DevBufs& b, bool lines, uin
 // Work loop shared by the counting kernels (s_chunk_slot: one LDS word shared
 // by the workgroup).  The launch's chunks (chunk_begin, nchunks and ctiles of
 // the series) are worked on in two parts: first every workgroup takes its own
-// run of consecutive chunks, half of them in all, without tickets and without a
-// barrier until the series changes; the other half is drawn chunk by chunk from
-// a ticket, so that all workgroups end together.  Per-series LDS state is
-// switched, and accumulated counts are flushed, when the series changes, when
-// 32-bit LDS counters could overflow (a single chunk's cells fit them:
-// chunk_tiles_limit), and at the end.  With every chunk drawn from the ticket, a
-// workgroup moved to another series at nearly every chunk (fifteen N = 1e4
-// series: window pass 520 us, most of it flushes of 39,936 bins) and paid a
-// ticket, two barriers and the wait for the chunk's slowest wave for each; that
-// window pass now takes 260 us.  A half: the workgroups of drawn chunks work near
-// each other and share the row samples in the scalar cache, those of own runs do
-// not.  With a quarter / a half / three quarters in own runs (ms): one N = 1e5
-// series at 20 given thresholds 1.73 / 1.74 / 1.86, two N = 1e5 series 4.66 /
-// 4.63 / 4.67, a hundred N = 1e4 series at K = 99 5.34 / 5.21 / 5.40, the
-// 600-series ensemble 6.08 / 6.05 / 6.02.
+// run of consecutive chunks, without tickets and without a barrier until the
+// series changes; the others are drawn chunk by chunk from a ticket, so that all
+// workgroups end together.  Per-series LDS state is switched, and accumulated
+// counts are flushed, when the series changes, when 32-bit LDS counters could
+// overflow (a single chunk's cells fit them: chunk_tiles_limit), and at the end.
+// With every chunk drawn from the ticket, a workgroup moved to another series at
+// nearly every chunk (fifteen N = 1e4 series: window pass 520 us, most of it
+// flushes of 39,936 bins) and paid a ticket, two barriers and the wait for the
+// chunk's slowest wave for each; that window pass now takes 220 us.
+// Three quarters of the chunks go into own runs, but half in the line sweeps
+// where that leaves a workgroup two chunks and more: workgroups of drawn chunks
+// work near each other and share the row samples in the scalar cache, and the
+// sweeps, of three workgroups per CU, gain more from that than their smaller
+// flushes cost.  Three quarters / half (us): sweep of eight N = 5e4 series 2886 /
+// 2588, of the 600-series ensemble 3259 / 2880, of one N = 1e5 series (m = 1) at
+// 20 given thresholds 1811 / 1697; window pass of a hundred N = 1e4 series 1105 /
+// 1176, pass 2 of five 136 / 158.
 template <class Body>
 __device__ __forceinline__ void chunk_loop(const SeriesDesc* __restrict__ sds, uint32_t S, uint32_t nchunks,
                                            uint32_t* __restrict__ ticket, Body& body, uint32_t* s_chunk_slot)
@@ -509,7 +511,8 @@ __device__ __forceinline__ void chunk_loop(const SeriesDesc* __restrict__ sds, u
     // own run [c, own_end), then tickets from W * per on; with a workgroup per
     // chunk there is nothing left to draw
     const bool one_each = nchunks <= W;
-    const uint32_t per = one_each ? 1u : nchunks / 2u / W;
+    const uint32_t quarters = Body::LINE_SWEEP && nchunks >= 4u * W ? 2u : 3u;
+    const uint32_t per = one_each ? 1u : (uint32_t)((uint64_t)nchunks * quarters / 4u / W);
     uint32_t c = min(blockIdx.x * per, nchunks);
     const uint32_t own_end = min(c + per, nchunks);
     SeriesScalars ss{};
@@ -672,6 +675,7 @@ __host__ __device__ __forceinline__ size_t select_lds_bytes_dev(int pass, uint32
 // Pass 1: histogram of the top SEL_B1 bits of every key.
 template <int NORM, int MC, int TC>
 struct SelPass1 {
+    static constexpr bool LINE_SWEEP = false;
     uint32_t* bins;   // LDS [SEL_N1][P1_COPIES]
     uint64_t* h1;     // global [S][SEL_N1]
     bool active = true;
@@ -707,6 +711,7 @@ struct SelPass1 {
 constexpr uint16_t NO_BIN = 0xFFFF;
 template <int NORM, int MC, int TC>
 struct SelPass2 {
+    static constexpr bool LINE_SWEEP = false;
     uint16_t* sOff;   // LDS [SEL_N1]: first bin of the bucket's slot in this group, or NO_BIN
     uint32_t* bins;   // LDS [G][SEL_N2] + one spare word per lane
     const uint8_t* T1;
@@ -768,6 +773,7 @@ static_assert(RQA_MAX_K <= 128, "pass-3 slots take 7 bits of a prefix-table entr
 
 template <int NORM, int MC, int TC>
 struct SelPass3 {
+    static constexpr bool LINE_SWEEP = false;
     uint2* sH;        // LDS [P3_SETS]: two entries prefix << 7 | pass-3 slot
     uint16_t* sB;     // LDS [RQA_MAX_K]: pass-1 bucket of each pass-2 slot
     uint32_t* sOver;  // LDS word: some set overflowed
@@ -1413,6 +1419,7 @@ __host__ __device__ __forceinline__ uint32_t rank_sweep_cols(uint32_t rows, bool
 
 template <int NORM, int MC, int TC, int LMC, bool RHO>
 struct SweepBody {
+    static constexpr bool LINE_SWEEP = true;
     uint2* stab;          // LDS [RHO_TABLE]
     uint32_t* ses;        // LDS [RANK_MAX]
     uint32_t* brho;       // LDS [Kcap+1][cols]: row Kp collects cells that recur at no threshold
@@ -1594,6 +1601,7 @@ __host__ __device__ __forceinline__ uint32_t range_cols(uint32_t rows)
 
 template <int NORM, int MC, int TC, int LMC>
 struct RangeBody {
+    static constexpr bool LINE_SWEEP = true;
     uint32_t* blam;       // LDS [rows][cols]; codes are 0 .. 2 ngroups <= rows - 1
     uint32_t* hx;         // LDS [rows] line values with an odd code, by exact rank
     uint32_t* sglo;       // LDS [gcap] group starts (gcap = K + 2 > ngroups)
@@ -2135,6 +2143,7 @@ __host__ __device__ __forceinline__ uint32_t hist_list(uint32_t Kp)
 
 template <int NORM, int MC, int TC>
 struct HistBody {
+    static constexpr bool LINE_SWEEP = false;
     uint2* stab;          // LDS [RHO_TABLE]
     uint32_t* ses;        // LDS [RANK_MAX]
     uint16_t* start;      // LDS [Kp][blockDim] start of the run of a rank in the stack (column = thread)
@@ -3000,6 +3009,7 @@ hipError_t launch_window_from_sample(hipStream_t st, const DevBufs& b, const uin
 // WIN_BINS fine bins.
 template <int NORM, int MC, int TC>
 struct WinPass1 {
+    static constexpr bool LINE_SWEEP = false;
     uint32_t* bins;       // LDS [1 + WIN_BINS]: [0] keys below the window, [1 + f] fine bin f
     uint64_t* gbins;      // global [S][WIN_BINS]
     SeriesWork* works;
@@ -3054,6 +3064,7 @@ struct WinPass1 {
 // sub-bins in global memory (few keys qualify).
 template <int NORM, int MC, int TC>
 struct WinPass2 {
+    static constexpr bool LINE_SWEEP = false;
     uint8_t* table;       // LDS [WIN_BINS] fine bin -> slot
     const uint8_t* gtable;
     uint64_t* fine;       // global [S][K][1 << WIN_MAX_SHIFT]
