@@ -86,7 +86,7 @@ enum {
     RQA_SEL_SAMPLE = 4,  /* as RQA_SEL_LEARNED with the window from sketch-sample quantiles (no network) */
     RQA_SEL_WINDOW = 8,  /* as RQA_SEL_LEARNED with the window set by rqa_set_window (for tests) */
     RQA_SEL_PLAIN = 16   /* exact selection by radix passes over all pairs (three; the line sweep
-                            takes the third when DET is asked for) */
+                            takes the third when DET is asked for at up to 44 targets) */
 };
 
 /* Create a context on HIP device `device`.  hip_stream is a hipStream_t on
@@ -313,7 +313,9 @@ rqa_status rqa_set_window(rqa_ctx *ctx, float lo, float hi);
  * around each target rate q (default 5). */
 rqa_status rqa_set_sample_width(rqa_ctx *ctx, float z);
 /* Statistics of the last selection on this context: full counting passes
- * over all pairs (3 plain, 2 windowed, 5 windowed with fallback), series
+ * over all pairs (3 plain, 2 windowed, 5 windowed with fallback; one more
+ * where DET at many targets takes a line sweep of its own: more than 44 plain,
+ * 40 windowed), series
  * that fell back to plain selection, targets outside their window.  Any
  * pointer may be NULL. */
 rqa_status rqa_selection_stats(rqa_ctx *ctx, uint32_t *full_passes, uint32_t *series_fallback,

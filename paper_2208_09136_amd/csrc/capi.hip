@@ -226,8 +226,8 @@ uint32_t segment_for(const rqa_ctx* c, uint64_t nv, const rqa_params& p, uint32_
 // HIST_MAX_SEG_HOST), else what spreads the call's pairs over eight waves per
 // CU, but at least 64 and at most 448 cells (the pass, join and rows of four N =
 // 2e4 series with 256 / 448: 1.68 / 1.62 ms, with faster lists 448 / 640: 1.38 /
-// 1.39); beyond, about 48 segments on the longest diagonal, up to 4096 (the runs at segment borders take 4 bytes per segment,
-// diagonal and threshold).
+// 1.39); beyond, about 48 segments on the longest diagonal, up to 4096 (the runs
+// at segment borders take 4 bytes per segment, diagonal and threshold).
 uint32_t hist_segment_for(const rqa_ctx* c, uint64_t L0, uint64_t pairs)
 {
     if (c->seg) return std::min<uint32_t>(c->seg, HIST_MAX_SEG_HOST);
@@ -321,8 +321,8 @@ struct Timer {
 // MODE_FUSED: counting passes, then the range sweep, which resolves the
 // last bits of every threshold and counts C and D at it in one pass.
 // MODE_BOTH: three counting passes, then the sweep at the thresholds found.
-// MODE_HIST: full line-length histogram at given thresholds (whole-diagonal
-// tiles, after the rank tables of the sweep).
+// MODE_HIST: full line-length histogram at given thresholds ((band, segment)
+// tiles, after the rank tables of the sweep, and a join of their borders).
 enum Mode { MODE_SELECT = 1, MODE_SWEEP = 2, MODE_BOTH = 3, MODE_SKETCH = 4, MODE_LINES = 8, MODE_FUSED = 9,
             MODE_HIST = 16 };
 
@@ -997,12 +997,14 @@ rqa_status check_flags_select(uint32_t flags, int* sel)
 
 // RQA_SEL_AUTO: the sample window (two passes over the pairs, exact, plain
 // fallback) for calls of at least AUTO_WINDOW_PAIRS pairs in all, else the
-// plain radix passes.  Measured on MI355X at K = 20 (ms per call, plain /
-// sample window): ten N = 1e3 series 0.11 / 0.17, one N = 1e4 0.18 / 0.24, one
-// N = 2e4 0.32 / 0.33, nine, eleven and fifteen N = 1e4 series 0.52 / 0.48,
-// 0.59 / 0.56 and 0.76 / 0.64, two N = 1e5 7.7 / 4.7 (the sketch and window
-// set-up cost about 0.06 ms per call).  The two are level near 2^28 pairs; the
-// line is the documented one.
+// plain radix passes.  Measured on MI355X at K = 20 (us per call, plain /
+// sample window; m = 1, and m = 3 with tau = 5): one N = 1e4 series 157 / 242,
+// 164 / 238; N = 20,000 294 / 294, 300 / 310; N = 26,000 383 / 371, 381 / 396; N =
+// 30,000 457 / 415, 466 / 421; nine N = 1e4 series 508 / 460, 506 / 465; six
+// hundred N = 1e3 979 / 1122, 983 / 1091 (the sketch and window set-up cost about
+// 60 us per call, and more per series).  For a few series the window is level
+// from 2^28 pairs on and about 9 % faster at 4.5e8; the line is the one that
+// include/rqa.h documents.
 constexpr uint64_t AUTO_WINDOW_PAIRS = 1ull << 29;
 
 int resolve_method(const Job& job, int sel)
@@ -1139,11 +1141,15 @@ void finish_lines(Job& job)
 // threshold sweep.  The range sweep's cost grows with K (line-rank histograms
 // of 2K + 1 rows in LDS, which keep three workgroups per CU up to K = 76, and
 // more keys inside candidate ranges take its fine-counter path), the
-// threshold sweep's hardly does.  Measured on MI355X (two N = 60,000 series,
-// targets 1..K %, range sweep / complete selection, ms per call): plain
-// selection 4.29 / 4.36 at K = 48, 4.86 / 4.41 at 56, and one N = 1e4 series
-// 0.263 / 0.295 at K = 36, 0.324 / 0.303 at 48; with the sample window, whose
-// candidate ranges are wider, 2.95 / 3.10 at K = 40, 3.53 / 3.14 at 48.
+// threshold sweep's hardly does.  Measured on MI355X (targets 1..K %, m = 1,
+// range sweep / complete selection, us per call), plain selection at K = 40, 44
+// and 48: one N = 1e3 series 115 / 143, 123 / 144, 127 / 142; one N = 1e4 295 /
+// 291, 309 / 300, 331 / 303; N = 30,000 664 / 693, 704 / 701, 743 / 707; two N =
+// 60,000 3624 / 3895, 3796 / 3920, 3983 / 3949: the line lies where the larger
+// calls cross.  With the sample window, whose candidate ranges are wider, at K =
+// 36, 40 and 44: N = 1e4 334 / 311, 350 / 312, 372 / 319; N = 30,000 526 / 586,
+// 568 / 603, 611 / 610; two N = 60,000 2389 / 2733, 2617 / 2746, 2854 / 2765;
+// fifteen N = 1e4 924 / 979, 996 / 990, 1057 / 993.
 #ifndef RQA_FUSED_MAX_K_PLAIN
 #define RQA_FUSED_MAX_K_PLAIN 44
 #endif
@@ -1229,7 +1235,6 @@ rqa_status build_batch_job(Job& job, uint32_t S, const float* concat, const uint
     return RQA_OK;
 }
 
-// Best host wall time (ms) of `reps` calls of the job; each call synchronises.
 // Device time of the job's phases (HIP events on the context stream), the
 // fastest of `reps` runs: the host's share of a call does not depend on the
 // launch shape and would only add noise to the comparison.
@@ -1671,7 +1676,7 @@ rqa_status rqa_batch_static(rqa_ctx* c, uint32_t S, const float* concat, const u
     if (st) return st;
     int sel = 0;
     if ((st = check_flags_select(flags, &sel))) return st;
-    // the network's activations live in allocated memory
+    // refused as documented: this call needs no network, whose memory is allocated
     if (sel == 1)
         return fail(RQA_ERR_UNSUPPORTED, "rqa_batch_static takes RQA_SEL_AUTO, RQA_SEL_PLAIN, RQA_SEL_SAMPLE or "
                                          "RQA_SEL_WINDOW");

@@ -55,8 +55,8 @@ __host__ __device__ __forceinline__ uint32_t lds_blocks_fit(size_t bytes)
     return units ? (uint32_t)(LDS_PER_CU / (units * LDS_UNIT)) : 1u << 16;
 }
 
-// Entries of the sweep's threshold list: K thresholds, or two boundaries per
-// candidate range.
+// Most line ranks of the sweeps: K with given thresholds, 2 per group of
+// candidate ranges in the range sweep.
 constexpr int RANK_MAX = 2 * RQA_MAX_K;
 
 // Per-series descriptor (device copy built by the host for every call).
@@ -97,12 +97,12 @@ struct SeriesWork {
     uint32_t eps_bits[RQA_MAX_K]; // selected (or given) thresholds, caller order
     uint64_t count[RQA_MAX_K];    // #{key <= eps} from selection
     uint64_t dcount[RQA_MAX_K];   // D: recurrences on lines of length >= lmin at eps
-    // sweep: rank table over ascending thresholds (given thresholds) or over
-    // the boundaries of the candidate ranges (range sweep)
-    uint32_t esorted[RANK_MAX];   // ascending thresholds / boundaries
+    // sweeps: rank table over the ascending thresholds (given thresholds) or
+    // code table over the groups of candidate ranges (range sweep)
+    uint32_t esorted[RANK_MAX];   // ascending thresholds (given thresholds)
     uint32_t dmap[RQA_MAX_K];     // caller index -> distinct threshold index
-    uint32_t Kp;                  // thresholds / boundaries in esorted
-    uint32_t shift, emin, emax;   // rank-table geometry
+    uint32_t Kp;                  // thresholds in esorted; range sweep: twice the groups
+    uint32_t shift, emin, emax;   // table geometry
     uint32_t multi;               // some bucket of the rank table holds several thresholds
     uint64_t hrho[RANK_MAX + 2];  // cells with rank rho
     uint64_t hlam[RANK_MAX + 2];  // cells with line rank lambda

@@ -5,9 +5,10 @@
 // band of 64 consecutive diagonals times one segment of T steps along them;
 // lane L of the wavefront that owns the tile walks diagonal d0 + L.  Tiles are
 // enumerated segment-major (all bands of segment 0, then of segment 1, ...),
-// grouped into chunks of consecutive tiles of one series, and chunks are
-// handed to persistent workgroups through an atomic ticket.  The recurrence
-// matrix is never stored: every key is recomputed from the series.
+// grouped into chunks of consecutive tiles of one series, and persistent
+// workgroups take first their own run of chunks, then chunks by an atomic ticket
+// (chunk_loop).  The recurrence matrix is never stored: every key is recomputed
+// from the series.
 //
 // Keys follow Eq. 1 of the paper with the maximum norm, or the squared
 // Euclidean norm folded left over the embedding components; all float
@@ -552,7 +553,7 @@ __device__ __forceinline__ void chunk_loop(const SeriesDesc* __restrict__ sds, u
             for (uint32_t tile = tb + wave; tile < te; tile += nwaves) body.tile(ss, uniform(tile), lane);
         }
         acc += cells;
-        c = end < own_end ? end : max(end, own_end);
+        c = end;
     }
     __syncthreads();
     if (cur != 0xFFFFFFFFu) body.flush(cur);
@@ -2032,10 +2033,11 @@ __device__ __forceinline__ uint32_t count_below(const uint32_t* es, uint32_t n, 
     return lo;
 }
 
-// Rank table of one series over the ascending thresholds es[0..kp): spans the buckets (key >> shift) from es[0] to es[kp-1] with the
-// smallest shift that fits RHO_TABLE buckets; bucket a (mod RHO_TABLE) stores
-// the number of thresholds below a << shift, and the first threshold
-// inside the bucket (several inside: flagged, the count in the high half).
+// Rank table of one series over the ascending thresholds es[0..kp): spans the
+// buckets (key >> shift) from es[0] to es[kp-1] with the smallest shift that fits
+// RHO_TABLE buckets; bucket a (mod RHO_TABLE) stores the number of thresholds
+// below a << shift, and the first threshold inside the bucket (several inside:
+// flagged, the count in the high half).
 // Called by a whole block after es is complete in LDS.
 __device__ void build_rank_table(SeriesWork& w, const uint32_t* es, uint32_t kp, uint2* tab, uint32_t* s_shift)
 {
